@@ -230,13 +230,15 @@ cis_status cis_split_workspace_size(const cis_model *model, const cis_shape *sha
  * dtype CIS_F64 or CIS_F32), computed in two launches for throughput on many
  * intervals.  The first integrates the nominal state, the integral rows and
  * S, and stores every RK stage's Jacobian coefficients in `ws` (a compact
- * record per stage); the second integrates the columns of Phi_x, B- and B+
- * from those records, one wave per leg and one column per lane, reading the
- * coefficients with scalar loads.  Results equal those of cis_discretize up
- * to the order of floating-point sums.  waves (1 or 2): register budget of
- * the second launch in waves per SIMD (2: two workgroups share a compute
- * unit).  ws must hold cis_split_workspace_size bytes, 8-byte aligned; its
- * contents are scratch.  Models without legs with links: CIS_ERR_UNSUPPORTED.
+ * record per stage, and sums of the integral rows' coefficients over the
+ * stages).  The second integrates the columns of Phi_x, B- and B+ that are
+ * coupled through the body angles (and, on a sinusoid, the feet's translation)
+ * from those records, one column per lane; the translations that only the
+ * controls drive have a closed form.  Results equal those of cis_discretize up
+ * to the order of floating-point sums.  waves: 1 or 2 (one kernel serves both;
+ * kept for callers that passed a register budget).  ws must hold
+ * cis_split_workspace_size bytes, 8-byte aligned; its contents are scratch.
+ * Models without legs with links: CIS_ERR_UNSUPPORTED.
  */
 cis_status cis_discretize_split(const cis_model *model, const cis_shape *shape, const void *X,
                                 const void *U, const void *s, const void *params,
@@ -341,7 +343,7 @@ enum { CIS_FORM_ONE_LAUNCH = 0, CIS_FORM_SPLIT = 1, CIS_FORM_BLOCKED = 2 };
 typedef struct {
     int32_t form;            /* CIS_FORM_*                                     */
     int32_t layout;          /* one-launch form: cis_shape.layout (1..4)       */
-    int32_t waves;           /* split form: register budget (1 or 2)          */
+    int32_t waves;           /* split form: its `waves` argument              */
     int32_t blocks;          /* blocked form: substep blocks (divides K)      */
     int32_t compose;         /* blocked form: CIS_COMPOSE_*                   */
     int32_t from_cache;      /* 1: read from the CIS_TUNE_CACHE file           */
@@ -351,8 +353,8 @@ typedef struct {
 /*
  * Tuner of the discretize step for one trajectory shape: times, on the
  * caller's inputs, the one-launch kernel in each of its four workgroup
- * layouts (the threads-per-interval mapping), the split form with one and two
- * waves per SIMD (models with legs with links), and (FP64) the substep-blocked
+ * layouts (the threads-per-interval mapping), the split form (models with legs
+ * with links), and (FP64) the substep-blocked
  * form for every block count 2..8 dividing K with VALU and MFMA composition;
  * each candidate best of three runs (HIP events on `stream`).  Returns the
  * fastest in *choice and leaves its outputs in A, Bm, Bp, S, defect, xprop.
@@ -431,7 +433,7 @@ enum { CIS_SCHED_ADJ_1 = 0x10, CIS_SCHED_ADJ_2 = 0x20, CIS_SCHED_ADJ_3 = 0x30,
  * size allows; CIS_SCHED_WAVES_2 holds it to 256 registers per lane so that
  * two workgroups can share a compute unit (latency hiding, at the price of
  * spills to scratch; CIS_F64 only, else CIS_ERR_DTYPE, except together with
- * CIS_SCHED_SPLIT, whose tangent launch has both budgets in both types).  Workgroups of more
+ * CIS_SCHED_SPLIT, which takes either bit and runs one kernel).  Workgroups of more
  * than four waves (models with many tangent columns) are held to 256
  * registers in both forms.  Without either bit both FP64 forms are timed
  * with CIS_SCHED_TUNE, and the first is used otherwise.  Setting both bits
@@ -451,11 +453,10 @@ enum { CIS_SCHED_DEF_BODY = 0x200, CIS_SCHED_DEF_LANE = 0x400 };
  * CIS_SCHED_SPLIT takes the two-launch form of cis_discretize_split for every
  * model with legs with links (others keep the one-launch form);
  * CIS_SCHED_FUSED takes the one-launch form.  Without either bit both forms
- * (and, for the split form, both register budgets of its tangent launch, which
- * CIS_SCHED_WAVES_1/2 otherwise fix) are timed with CIS_SCHED_TUNE, and the
- * one-launch form is used otherwise.  The split form keeps its stage records
- * in plan memory (about 8 (8 + 4 n_j + 4 K R) bytes per interval in FP64, R
- * the record length: 280 for quad13, 120 for cheetah7).  Setting both bits is
+ * are timed with CIS_SCHED_TUNE, and the one-launch form is used otherwise.
+ * The split form keeps its stage records in plan memory (about 32 K R bytes
+ * per interval in FP64, R the record length: 96 for quad13 and 48 for cheetah7
+ * on flat ground).  Setting both bits is
  * an error (CIS_ERR_DIM). */
 enum { CIS_SCHED_SPLIT = 0x800, CIS_SCHED_FUSED = 0x1000 };
 

@@ -36,9 +36,10 @@ struct Group {
     int def_waves = 0;         // waves per interval of the chosen defects pass
     size_t fdesc_off = 0, ddesc_off = 0, adesc_off = 0, items_off = 0, cursor_off = 0;
     // split form: record offsets per item (device), the group's part of the
-    // record memory (elements), and whether the chosen discretize form is it
+    // record memory (elements; the stage sums after its records), and whether
+    // the chosen discretize form is it
     bool split_ok = false, split = false;
-    size_t recoff_off = 0, rec_base = 0;
+    size_t recoff_off = 0, rec_base = 0, sums_at = 0;
     std::vector<int64_t> rec_off;
     BatchGroupDev dev{};
     KLaunch disc, disc_b, def, adj;   // disc_b: tangent launch of the split form
@@ -450,7 +451,12 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
         g.rec_off.resize(g.items.size());
         for (size_t it = 0; it < g.items.size(); ++it) {
             g.rec_off[it] = cum;
-            cum += split_elems_per_interval(g.model, trajs[g.trajs[g.items[it].x]].substeps);
+            cum += split_record_elems(g.model, trajs[g.trajs[g.items[it].x]].substeps);
+        }
+        g.sums_at = (size_t)cum;
+        for (size_t it = 0; it < g.items.size(); ++it) {
+            const int K = trajs[g.trajs[g.items[it].x]].substeps;
+            cum += split_elems_per_interval(g.model, K) - split_record_elems(g.model, K);
         }
         rec_total += (size_t)cum;
         rec_total = (rec_total + 31) / 32 * 32;
@@ -596,6 +602,7 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
         g.dev.cursor = (int*)(d + g.cursor_off);
         g.dev.rec = g.split_ok ? (void*)(p->recmem + g.rec_base * es) : nullptr;
         g.dev.rec_off = g.split_ok ? (const int64_t*)(d + g.recoff_off) : nullptr;
+        g.dev.sums = g.split_ok ? (void*)(p->recmem + (g.rec_base + g.sums_at) * es) : nullptr;
         cis_status st;
         std::string key;
         TuneChoice want, made;
@@ -622,20 +629,18 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
             struct Cand { KLaunch l, lb; int pblocks, waves; bool split; };
             std::vector<Cand> cands;
             if (g.split_ok) {
-                for (int w = 1; w <= 2; ++w) {
-                    if (waves_force ? w != waves_force : (sched != CIS_SCHED_TUNE && w != 1))
-                        continue;
-                    Cand c;
-                    c.pblocks = 0;
-                    c.waves = w;
-                    c.split = true;
-                    st = prep_split_batch(g.model, dtype, g.dev, w, &c.l, &c.lb);
-                    if (st != CIS_OK) {
-                        plan_free(p);
-                        return st;
-                    }
-                    cands.push_back(c);
+                // one kernel for both register budgets (the budget asked for is
+                // reported back)
+                Cand c;
+                c.pblocks = 0;
+                c.waves = waves_force ? waves_force : 1;
+                c.split = true;
+                st = prep_split_batch(g.model, dtype, g.dev, &c.l, &c.lb);
+                if (st != CIS_OK) {
+                    plan_free(p);
+                    return st;
                 }
+                cands.push_back(c);
             }
             for (int w = 1; w <= (dtype == CIS_F64 ? 2 : 1); ++w) {
                 if (split_force == 1 && g.split_ok) break;
@@ -670,7 +675,8 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
             bool hit = false;
             if (cands.size() > 1 && want.split >= 0) {
                 for (size_t c = 0; c < cands.size(); ++c)
-                    if ((cands[c].split ? 1 : 0) == want.split && cands[c].waves == want.waves &&
+                    if ((cands[c].split ? 1 : 0) == want.split &&
+                        (cands[c].split || cands[c].waves == want.waves) &&
                         (cands[c].pblocks > 0 ? 1 : 0) == want.persist) {
                         best = c;
                         hit = true;

@@ -468,8 +468,7 @@ extern "C" cis_status cis_single_tune(const cis_model* model, const cis_shape* s
     if (!hit) {
         std::vector<cis_single_choice> cands;
         for (int l = 1; l <= 4; ++l) cands.push_back({CIS_FORM_ONE_LAUNCH, l, 0, 0, 0, 0, 0.0f});
-        if (legs)
-            for (int w = 1; w <= 2; ++w) cands.push_back({CIS_FORM_SPLIT, 0, w, 0, 0, 0, 0.0f});
+        if (legs) cands.push_back({CIS_FORM_SPLIT, 0, 1, 0, 0, 0, 0.0f});
         for (int b = 2; f64 && b <= 8 && b <= K; ++b)
             if (K % b == 0)
                 for (int c = CIS_COMPOSE_VALU; c <= CIS_COMPOSE_MFMA; ++c)

@@ -33,10 +33,10 @@ __device__ __forceinline__ int contact_of(int b) {
 }
 
 // DPP row shifts by one lane: prev_lane(v) in lane b is v of lane b-1, next_lane(v) that
-// of lane b+1 (within rows of 16 lanes; the value at a row edge is unspecified).
+// of lane b+1 (within rows of 16 lanes; 0 at a row edge).
 template <int CTRL>
 __device__ __forceinline__ int dpp_row(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
 }
 template <int CTRL>
 __device__ __forceinline__ double dpp_row(double v) {

@@ -2,417 +2,444 @@
 // Sec. IV-B eq. intg-aug-sys-param; sensitivities by internal numerical
 // differentiation, Sec. VI).  Two kernels per batch of intervals:
 //
-//   k_coefrec : per interval three waves, the nominal RK4 recursion on body
-//               lanes, the right-hand side and Jacobian coefficients of
-//               every stage, and the dilation column S on body lanes; writes
-//               F~, the defect, S, the integral-state columns of A, and a
-//               compact record of every stage's coefficients (CoefRec) to a
-//               workspace in device memory.
-//   k_tangent : per (interval, block of 64 tangent columns) one wave per leg.
-//               Lane c holds column c of Z = [Phi_x | B- | B+] on the rows of
-//               the torso and of the wave's leg; every coefficient a wave
-//               needs is the same for all its lanes, so it is read with
-//               scalar loads from the stage record and enters the FMAs as a
-//               scalar operand (no LDS traffic for coefficients, no wait on
-//               the nominal recursion).  The torso rows are integrated
-//               identically in every leg wave; the only exchange is the hip
-//               stiffness and damping torque of each leg on the torso (one
-//               value per column and stage, through LDS).
-//
-// The two kernels exchange per interval 8 + 4 n_j constants and 4 K records
-// of CoefRec<TP>::GLOBAL elements.
+//   k_coefrec : the nominal RK4 recursion with the dilation column S, and the
+//               coefficients of every stage (compact records and sums,
+//               cis_pack.hpp), four intervals per workgroup of two waves; writes
+//               F~, the defect and S.
+//   k_tangent : the coupled columns of Z = [Phi_x | B- | B+], one per lane
+//               (cis_reduced.hpp), and the closed-form entries of A, B-, B+.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
 
 #include "../../include/cis.h"
-#include "cis_body.hpp"
 #include "cis_debug.hpp"
 #include "cis_host.hpp"
 #include "cis_launch.hpp"
 #include "cis_model.hpp"
-#include "cis_split.hpp"
+#include "cis_pack.hpp"
+#include "cis_reduced.hpp"
 
 namespace cis {
 
-template <class T, class TP>
-struct RecShared {
-    Interval<T, TP> iv;
-    T xring[4][TP::NX];        // stage inputs from the state wave
-    T csring[4][TP::NB][2];    // their rotations
-    T fring[4][3 * TP::NB];    // their accelerations
-    T coef[2][CoefRec<TP>::SIZE];
-};
-
-// ---------------------------------------------------------------------------
-// k_coefrec: interval k by two waves, one workgroup barrier per step:
-//   wave 0 (state, S column): stage t of the nominal recursion at step t, and
-//                          the S column's stage t-2 from coef[(t-2) & 1] with
-//                          the copy of that record to device memory;
-//   wave 1 (coefficients): stage t-1 at step t, into coef[(t-1) & 1].
-// ---------------------------------------------------------------------------
-template <class T, class TP>
-__device__ __forceinline__ void coefrec_item(RecShared<T, TP>& sh, const FwdArgs<T>& a,
-                                             const MConst<TP::NB, TP::NJ, TP::NC>& mc,
-                                             const int k, T* __restrict__ rec) {
-    constexpr int NB = TP::NB, NX = TP::NX, NXT = TP::NXT, NY = TP::NY, NQ = TP::NQ;
-    constexpr int NC = TP::NC, NJ = TP::NJ, L = TP::L, D = TP::D;
-    using R = CoefRec<TP>;
-    using SR = SplitRec<TP>;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    constexpr int nth = 128;
-    load_interval<T, TP>(sh.iv, a, mc, k, tid, nth);
-    for (int e = tid; e < 2 * R::SIZE; e += nth) (&sh.coef[0][0])[e] = T(0);
-    __syncthreads();
-    coefrec_constants<T, TP>(sh.iv, sh.coef[0], tid, nth);
-    coefrec_constants<T, TP>(sh.iv, sh.coef[1], tid, nth);
-    // per-interval constants of the tangent kernel
-    for (int e = tid; e < SR::CRS; e += nth) {
-        T v = T(0);
-        if (e == 0) v = sh.iv.s;
-        else if (e == 1) v = sh.iv.h;
-        else if (e == 2) v = sh.iv.h6;
-        else if (e >= 8 && e < 8 + 4 * NJ) v = sh.iv.kc[(e - 8) >> 2][(e - 8) & 3];
-        rec[e] = v;
-    }
+// Four intervals by two waves, one workgroup barrier per stage: wave 0 the
+// nominal recursion and the S column (stage t at step t), wave 1 the
+// coefficients, sums and integral rows (stage t - 1 at step t), both on rows of
+// 16 body lanes.  k, a: the lane's interval; item: its index in the launch (of
+// n); on: not a repeat; most: the largest substep count of the four.
+//
+// Bound by the length of the two chains (VALU busy 41 % for 12,800 quad13
+// intervals), so they are shared between two waves, four intervals fill a wave
+// that one would leave three quarters idle, and the constants of the bodies stay
+// in LDS.  quad13, K = 20: 200 intervals 70 us, 12,800 370 us (with the
+// closed-form rows 560 us); one wave doing both chains held 330 registers and took
+// 127 and 540 us; one interval per workgroup of two waves 145 and 1,810 us.
+template <class T, class TP, bool FLAT>
+__device__ __forceinline__ void coefrec_item(const FwdArgs<T>& a,
+                                             const MConst<TP::NB, TP::NJ, TP::NC>& mc, int k,
+                                             T* __restrict__ rec, T* __restrict__ sums, int64_t n,
+                                             bool on, int most, PackShared<T>& sh) {
+    constexpr int NQ = TP::NQ, NX = TP::NX, NC = TP::NC;
+    using R = PackRec<TP, FLAT>;
+    const int me = threadIdx.x & 63;
+    PackBody<T, TP, FLAT> c;
+    c.lc = &sh.lc.v[0][me];
+    c.load(a, mc, k, me & 15);   // both waves store the same constants
     const int nst = 4 * a.K;
-    const int nsteps = nst + 2;
-    const int64_t ldi = a.ldi;
+    const T s = c.s, Kt = T(a.K), h = T(1) / Kt, h6 = T(1) / (T(6) * Kt);
+    const T sK = s / Kt, s6 = s / (T(6) * Kt);   // the weights with s (one rounding each)
+    T* sr = rec + R::HDR;
     __syncthreads();
-
-    if (wave == 0) {
-        // ---- state wave: stage t at step t; S column: stage t-2 at step t ----
-        const BodyConst<T, TP> c = body_const<T, TP>(sh.iv, mc, lane);
-        BodyRK<T> bs;
+    if (threadIdx.x < 64) {
+        if (on) pack_header(c, h, rec);
+        T xb[6], xs[6], xa[6], zb[6], zs[6], za[6];
 #pragma unroll
-        for (int kk = 0; kk < 3; ++kk) {
-            bs.xb[kk] = sh.iv.x0[3 * c.b + kk];
-            bs.xb[3 + kk] = sh.iv.x0[NQ + 3 * c.b + kk];
+        for (int q = 0; q < 6; ++q) {
+            xb[q] = a.X[(q < 3 ? 3 * c.b + q : NQ + 3 * c.b + q - 3) * a.ldn + k];
+            xs[q] = xb[q];
+            zb[q] = zs[q] = T(0);
         }
-#pragma unroll
-        for (int kk = 0; kk < 6; ++kk) {
-            bs.xs[kk] = bs.xb[kk];
-            bs.xa[kk] = T(0);
-        }
-        SLane<T, TP> z;
-#pragma unroll
-        for (int r = 0; r < 6; ++r) z.zs[r] = z.zb[r] = z.za[r] = T(0);
-#pragma unroll
-        for (int l = 0; l < SLane<T, TP>::NCL; ++l) z.ycc[l] = T(0);
-        z.yct = T(0);
-        const T Kt = T(a.K);
-        T* out = rec + SR::CRS;
-        // steps t = 4 j + ST, t < nsteps: one barrier each (both stage indices
-        // known at compile time inside the unrolled substep)
-        auto step = [&](auto st_c, int j) {
+        auto stage = [&](auto st_c, int t) {
             constexpr int ST = decltype(st_c)::value;
-            constexpr int SS = (ST + 2) & 3;   // S stage of this step
-            const int t = 4 * j + ST;
-            if (t < nst) {
-                const T jt = T(j);
-                const T tau = ST == 0 ? jt / Kt : (ST == 3 ? (jt + T(1)) / Kt : (jt + T(0.5)) / Kt);
-                state_stage<T, TP, ST>(sh.iv, mc, c, bs, tau, sh.xring[(ST + 1) & 3],
-                                       sh.csring[ST], sh.fring[ST], lane);
-            }
-            if (t >= 2) {
-                const T* cf = sh.coef[SS & 1];
-                s_stage<T, TP, SS, R>(sh.iv, c, z, cf, lane);
+            if (t < nst) {   // whole rows of 16 lanes
+                const T jt = T(t >> 2) + (ST == 0 ? T(0) : (ST == 3 ? T(1) : T(0.5)));
+                T f[3], kz[3], cth, cb, sb;
+                pack_state<T, TP, FLAT>(c, mc, xs, zs, quotient(jt, Kt, h), f, kz, cth, cb, sb);
+                constexpr int sl = ST & 1;
+                using Pair = typename PackConst<T>::Pair;
+                sh.cs[sl][me] = Pair{cb, sb};
+                sh.xy[sl][me] = Pair{xs[0], xs[1]};
 #pragma unroll
-                for (int e = lane; e < R::GLOBAL; e += 64) out[e] = cf[e];
-                out += R::GLOBAL;
+                for (int q = 0; q < 3; ++q) sh.v[sl][q][me] = xs[3 + q];
+#pragma unroll
+                for (int q = 0; q < 6; ++q) sh.z[sl][q][me] = zs[q];
+                if (on && c.body) sr[R::CTH + c.b] = cth;
+                sr += R::STAGE;
+                // pose rows s v (and + v of the nominal state in the S column),
+                // velocity rows s f
+                constexpr bool outer = ST == 0 || ST == 3;
+                const T wx = outer ? h6 : T(2) * h6, ux = outer ? s6 : T(2) * s6;
+                const T an = ST == 2 ? h : T(0.5) * h, un = ST == 2 ? sK : T(0.5) * sK;
+                T kp[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    kp[q] = s * zs[3 + q] + xs[3 + q];
+                    // the substep's increments apart: one rounding of the running
+                    // value per substep
+                    if constexpr (ST == 0) {
+                        xa[q] = ux * xs[3 + q];
+                        xa[3 + q] = ux * f[q];
+                        za[q] = wx * kp[q];
+                        za[3 + q] = wx * kz[q];
+                    } else {
+                        xa[q] += ux * xs[3 + q];
+                        xa[3 + q] += ux * f[q];
+                        za[q] += wx * kp[q];
+                        za[3 + q] += wx * kz[q];
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    if constexpr (ST < 3) {
+                        xs[q] = xb[q] + un * xs[3 + q];
+                        xs[3 + q] = xb[3 + q] + un * f[q];
+                        zs[q] = zb[q] + an * kp[q];
+                        zs[3 + q] = zb[3 + q] + an * kz[q];
+                    } else {
+                        xs[q] = xb[q] += xa[q];
+                        xs[3 + q] = xb[3 + q] += xa[3 + q];
+                        zs[q] = zb[q] += za[q];
+                        zs[3 + q] = zb[3 + q] += za[3 + q];
+                    }
+                }
             }
             __syncthreads();
         };
-        for (int j = 0; 4 * j < nsteps; ++j) {
-            step(std::integral_constant<int, 0>{}, j);
-            step(std::integral_constant<int, 1>{}, j);
-            if (4 * j + 2 < nsteps) {
-                step(std::integral_constant<int, 2>{}, j);
-                step(std::integral_constant<int, 3>{}, j);
-            }
+        for (int t = 0; t < 4 * most; t += 4) {
+            stage(std::integral_constant<int, 0>{}, t);
+            stage(std::integral_constant<int, 1>{}, t + 1);
+            stage(std::integral_constant<int, 2>{}, t + 2);
+            stage(std::integral_constant<int, 3>{}, t + 3);
         }
-        if (lane < NB) {
+        sh.fin[me] = xb[2] + xb[5];
+        // a foot's translation takes 0 x the slope of its contact force on flat
+        // ground: nothing, or a NaN of its angle
+        if (FLAT && c.contact)
 #pragma unroll
-            for (int kk = 0; kk < 6; ++kk) {
-                const int r = kk < 3 ? 3 * c.b + kk : NQ + 3 * c.b + kk - 3;
-                if (a.xprop) a.xprop[r * ldi + k] = bs.xb[kk];
-                a.defect[r * ldi + k] = bs.xb[kk] - sh.iv.xk1[r];
+            for (int q = 0; q < 2; ++q) {
+                zb[q] += T(0) * zb[2];
+                zb[3 + q] += T(0) * zb[2];
             }
-        }
-        T yct = T(0);
+        __syncthreads();
+        if (on && c.body)
 #pragma unroll
-        for (int e = 0; e < NB; ++e) yct += lane_value(z.yct, e);
-        if (lane < NB) {
-#pragma unroll
-            for (int kk = 0; kk < 3; ++kk) {
-                a.S[(int64_t)(3 * c.b + kk) * ldi + k] = z.zb[kk];
-                a.S[(int64_t)(NQ + 3 * c.b + kk) * ldi + k] = z.zb[3 + kk];
-            }
-            if (c.contact) a.S[(int64_t)(NX + c.i) * ldi + k] = z.ycc[0];
-            if (lane == 0) a.S[(int64_t)(NX + NC) * ldi + k] = yct;
-        }
+            for (int q = 0; q < 6; ++q)
+                pack_output(a, k, q < 3 ? 3 * c.b + q : NQ + 3 * c.b + q - 3, xb[q], zb[q]);
     } else {
-        // ------- coefficient wave: stage tc at step tc + 1; integral rows -------
-        const BodyConst<T, TP> c = body_const<T, TP>(sh.iv, mc, lane);
-        const int ycc_row = NX + c.i;
-        T ycb = c.contact ? sh.iv.x0[ycc_row] : T(0), yca = T(0);
-        T ytb = lane == 0 ? sh.iv.x0[NX + NC] : T(0), yta = T(0);
-        const T s = sh.iv.s;
-        __syncthreads();
-        for (int tc = 0; tc < nst; ++tc) {
-            const int st = tc & 3;
-            const T tau = (T(tc >> 2) + T(stage_c(st))) / T(a.K);
-            T ycc = T(0), yct = T(0);
-            coef_stage<T, TP, false, true, R, 2>(sh.iv, mc, c,
-                                                     tc == 0 ? sh.iv.x0 : sh.xring[tc & 3],
-                                                     sh.csring[tc & 3], sh.fring[tc & 3], tau,
-                                                     sh.coef[tc & 1], ycc, yct, lane);
-            const T wk = (st == 0 || st == 3) ? T(1) : T(2);
-            if (st == 0) {
-                yca = wk * s * ycc;
-                yta = wk * s * yct;
+        T ycc = c.contact ? a.X[(NX + c.i) * a.ldn + k] : T(0);
+        T yct = c.torso && c.body ? a.X[(NX + NC) * a.ldn + k] : T(0);
+        PackSums<T, TP, FLAT> sm;
+        sm.clear();
+        StageHold<T> hd;
+        T vm0 = T(0), vp0 = T(0), xm0 = T(0), xp0 = T(0), yca = T(0), yta = T(0);
+        auto stage = [&](auto st_c, int t) {
+            constexpr int ST = decltype(st_c)::value;
+            __syncthreads();   // the state wave has left stage t
+            if (t >= nst) return;
+            const T jt = T(t >> 2) + (ST == 0 ? T(0) : (ST == 3 ? T(1) : T(0.5)));
+            // response of a unit mass to the hold weights at the stage input
+            const T tp = hd.tau, vmp = hd.vm, vpp = hd.vp;
+            hd.tau = quotient(jt, Kt, h);
+            constexpr bool outer = ST == 0 || ST == 3;
+            hd.w = outer ? h6 : T(2) * h6;
+            hd.sw = outer ? s6 : T(2) * s6;
+            if constexpr (ST == 0) {
+                hold_nodes(hd.tau, vm0, vp0, xm0, xp0);
+                hd.vm = vm0;
+                hd.vp = vp0;
+                hd.xm = xm0;
+                hd.xp = xp0;
             } else {
-                yca += wk * s * ycc;
-                yta += wk * s * yct;
+                const T hh = ST == 3 ? h : T(0.5) * h;
+                hd.vm = vm0 + hh * (T(1) - tp);
+                hd.vp = vp0 + hh * tp;
+                hd.xm = xm0 + hh * vmp;
+                hd.xp = xp0 + hh * vpp;
             }
-            if (st == 3) {
-                ycb += sh.iv.h6 * yca;
-                ytb += sh.iv.h6 * yta;
+            T cc, ct;
+            if constexpr (ST == 0) yca = yta = T(0);
+            pack_coef<T, TP, FLAT, true>(c, mc, sh, ST & 1, hd, cc, ct, sm, sr, on);
+            sr += R::STAGE;
+            yca += hd.sw * cc;
+            yta += hd.sw * ct;
+            if constexpr (ST == 3) {
+                ycc += yca;
+                yct += yta;
             }
-            __syncthreads();
+        };
+        hd.tau = hd.vm = hd.vp = T(0);
+        for (int t = 0; t < 4 * most; t += 4) {
+            stage(std::integral_constant<int, 0>{}, t);
+            stage(std::integral_constant<int, 1>{}, t + 1);
+            stage(std::integral_constant<int, 2>{}, t + 2);
+            stage(std::integral_constant<int, 3>{}, t + 3);
         }
         __syncthreads();
-        {
-            T acc = T(0);
-#pragma unroll
-            for (int e = 0; e < NB; ++e) acc += lane_value(ytb, e);
-            ytb = acc;
-        }
-        if (c.contact) {
-            if (a.xprop) a.xprop[ycc_row * ldi + k] = ycb;
-            a.defect[ycc_row * ldi + k] = ycb - sh.iv.xk1[ycc_row];
-        }
-        if (lane == 0) {
-            if (a.xprop) a.xprop[(NX + NC) * ldi + k] = ytb;
-            a.defect[(NX + NC) * ldi + k] = ytb - sh.iv.xk1[NX + NC];
-        }
-        // A[:, n:] = [0; I]: the integral states feed back into nothing
-        for (int e = lane; e < NXT * NY; e += 64) {
-            const int r = e / NY, cc = NX + e % NY;
-            a.A[((int64_t)r * NXT + cc) * ldi + k] = (r == cc) ? T(1) : T(0);
-        }
-    }
-    (void)L;
-    (void)D;
-}
-
-// ---------------------------------------------------------------------------
-// k_tangent: one classical RK4 stage of a leg wave (derivative from
-// tangent_split_rhs, then the RK4 combination).
-// ---------------------------------------------------------------------------
-template <class T, class TP, int ST, bool FORCE, bool LDSF>
-__device__ __forceinline__ void tangent_split_stage(TanLane<T, TP>& z, const T* __restrict__ cr,
-                                                    const T* __restrict__ lr,
-                                                    const T* __restrict__ rs, T* xch, int leg,
-                                                    int lane, T tau, T wbm, T wbp,
-                                                    const unsigned (&off)[3 * (TP::D + 1)],
-                                                    unsigned offcc, T* fbuf,
-                                                    const T* rs_next) {
-    constexpr int LB = TP::D + 1;
-    constexpr int FBUF = SplitRec<TP>::FBUF;
-    const T s = cr[0], h = cr[1], h6 = cr[2];
-    T kv[3 * LB], kcc, kct;
-    // forcing regions alternate between the two LDS buffers stage by stage
-    // (4 stages per substep, so the parity of the stage is that of ST)
-    tangent_split_rhs<T, TP, FORCE, LDSF>(z.zs, cr, lr, rs, xch, leg, lane, tau, wbm, wbp, off,
-                                          offcc, kv, kcc, kct, fbuf + (ST & 1) * FBUF, rs_next,
-                                          fbuf + ((ST + 1) & 1) * FBUF);
-    // classical RK4 combination (stage ST known at compile time)
-    constexpr int WK = (ST == 0 || ST == 3) ? 1 : 2;
-    const T an = (ST == 2) ? h : T(0.5) * h;
-#pragma unroll
-    for (int r = 0; r < 3 * LB; ++r) {
-        const T kq = s * z.zs[3 * LB + r];
-        if (ST == 0) z.za[r] = kq;
-        else z.za[r] += T(WK) * kq;
-        if (ST < 3) z.zs[r] = z.zb[r] + an * kq;
-    }
-#pragma unroll
-    for (int r = 0; r < 3 * LB; ++r) {
-        const T kk = kv[r];
-        if (ST == 0) z.za[3 * LB + r] = kk;
-        else z.za[3 * LB + r] += T(WK) * kk;
-        if (ST < 3) z.zs[3 * LB + r] = z.zb[3 * LB + r] + an * kk;
-    }
-    z.ycc += (h6 * T(WK)) * kcc;
-    z.yct += (h6 * T(WK)) * kct;
-    if (ST == 3) {
-#pragma unroll
-        for (int r = 0; r < 6 * LB; ++r) {
-            z.zb[r] += h6 * z.za[r];
-            z.zs[r] = z.zb[r];
+        const T angles = row_sum(sh.fin[me]);
+        yct = row_sum(yct);
+        const T zct = row_sum(c.body ? sm.zct : T(0));
+        if (on) {
+            pack_sums(c, sm, angles, zct, sums, n);
+            if (c.contact) pack_output(a, k, NX + c.i, ycc, sm.zcc);
+            if (c.torso && c.body) pack_output(a, k, NX + NC, yct, zct);
         }
     }
 }
 
-template <class T, class TP, bool FORCE, bool LDSF>
-__device__ __forceinline__ void tangent_split_loop(TanLane<T, TP>& z, const T* __restrict__ cr,
-                                                   const T* __restrict__ rec0, T* xch, int leg,
-                                                   int lane, int K, T wbm, T wbp,
-                                                   const unsigned (&off)[3 * (TP::D + 1)],
-                                                   unsigned offcc, T* fbuf) {
-    using R = CoefRec<TP>;
-    constexpr int LEGB = R::LEGB, GL = R::GLOBAL, L = TP::L;
-    const T Kt = T(K);
-    const T* rs = rec0;
+// RK4 over one interval's coupled columns (one per lane).
+template <class T, class TP, bool FLAT>
+__device__ __forceinline__ void tangent_item(const T* __restrict__ rec, T* lds,
+                                             const RedCol& col, int K,
+                                             T (&pb)[RedTopo<TP, FLAT>::NP],
+                                             T (&vb)[RedTopo<TP, FLAT>::NP], T (&ycc)[TP::NC],
+                                             T& yct) {
+    using RT = RedTopo<TP, FLAT>;
+    using R = PackRec<TP, FLAT>;
+    using LN = RedLane<T, TP, FLAT>;
+    constexpr int NP = RT::NP;
+    const int lane = threadIdx.x & 63;
+    LN ln;
+    ln.init(rec, lds, col, lane);
+    // step weights in scalar registers: h / 2 and h, h / 6 and h / 3, and times s
+    // (one division each: their rounding is the same in every stage)
+    const T s = rec[0], Kt = uniform(T(K)), rK = uniform(T(1) / Kt);
+    const T h6 = T(1) / (T(6) * Kt), sK = s / Kt, s6 = s / (T(6) * Kt);
+    const T hh[2] = {uniform(T(0.5) * rK), rK}, hw[2] = {uniform(h6), uniform(T(2) * h6)};
+    const T sh[2] = {uniform(T(0.5) * sK), uniform(sK)}, sw[2] = {uniform(s6), uniform(T(2) * s6)};
+    const T* rs = rec + R::HDR;
+    const T* last = rs + (int64_t)(4 * K - 1) * R::STAGE;
+    T ps[NP], vs[NP], pa[NP], va[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        pb[p] = p < RT::NU && col.col == p ? T(1) : T(0);
+        vb[p] = p < RT::NU && col.col == RT::NU + p ? T(1) : T(0);
+        ps[p] = pb[p];
+        vs[p] = vb[p];
+    }
+#pragma unroll
+    for (int i = 0; i < TP::NC; ++i) ycc[i] = T(0);
+    T kc[R::NVK];
+    ln.vectors(rec + R::KC, kc);
+    // coefficient vectors and forcing entries of stages t and t + 1 (slot t & 1;
+    // a third set in flight spilled 90 bytes per lane, and a reload from scratch
+    // waits for every load issued before it)
+    T cv[2][R::NV], f[2][LN::NFL];
+    T yt[4] = {T(0), T(0), T(0), T(0)};
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        ln.vectors(rs + q * R::STAGE, cv[q]);
+        ln.fetch(rs + q * R::STAGE, f[q]);
+    }
+    ln.place(f[0]);
     for (int j = 0; j < K; ++j) {
         const T jt = T(j);
-        const T tau0 = jt / Kt, tauh = (jt + T(0.5)) / Kt, tau1 = (jt + T(1)) / Kt;
-        T* x0 = xch;
-        T* x1 = xch + L * 64;
-        tangent_split_stage<T, TP, 0, FORCE, LDSF>(z, cr, rs + leg * LEGB, rs, x0, leg, lane,
-                                                   tau0, wbm, wbp, off, offcc, fbuf, rs + GL);
-        rs += GL;
-        tangent_split_stage<T, TP, 1, FORCE, LDSF>(z, cr, rs + leg * LEGB, rs, x1, leg, lane,
-                                                   tauh, wbm, wbp, off, offcc, fbuf, rs + GL);
-        rs += GL;
-        tangent_split_stage<T, TP, 2, FORCE, LDSF>(z, cr, rs + leg * LEGB, rs, x0, leg, lane,
-                                                   tauh, wbm, wbp, off, offcc, fbuf, rs + GL);
-        rs += GL;
-        // the last stage of the interval copies its own region (never read)
-        tangent_split_stage<T, TP, 3, FORCE, LDSF>(z, cr, rs + leg * LEGB, rs, x1, leg, lane,
-                                                   tau1, wbm, wbp, off, offcc, fbuf,
-                                                   j + 1 < K ? rs + GL : rs);
-        rs += GL;
-    }
-}
-
-// Columns [64 cb, 64 cb + 64) of interval k, wave `leg` (all waves of the block).
-template <class T, class TP>
-__device__ __forceinline__ void tangent_item(const FwdArgs<T>& a, const T* __restrict__ rec,
-                                             const int k, const int cb, T* xch, T* fbuf) {
-    constexpr int D = TP::D, LB = D + 1;
-    using SR = SplitRec<TP>;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int leg = __builtin_amdgcn_readfirstlane(tid >> 6);
-    T wbm, wbp;
-    TanLane<T, TP> z;
-    const TanCol<TP> tc = tangent_column<T, TP>(cb, leg, lane, wbm, wbp, z.zb);
+        const T tau0 = uniform(quotient(jt, Kt, rK)), tauh = uniform(quotient(jt + T(0.5), Kt, rK));
+        const T tau1 = uniform(quotient(jt + T(1), Kt, rK));
+        auto stage = [&](auto st_c, T tau) {
+            constexpr int ST = decltype(st_c)::value;
+            constexpr int W = (ST == 0 || ST == 3) ? 0 : 1, H = ST == 2 ? 1 : 0;
+            T k[NP];
+            red_rates<T, TP, FLAT>(ln, kc, cv[ST & 1], tau, ps, vs, k, ycc, yt, f[(ST + 1) & 1]);
+            const T* ahead = rs + 2 * R::STAGE;
+            ahead = ahead < last ? ahead : last;
+            ln.vectors(ahead, cv[ST & 1]);
+            ln.fetch(ahead, f[ST & 1]);
 #pragma unroll
-    for (int r = 0; r < 6 * LB; ++r) {
-        z.zs[r] = z.zb[r];
-        z.za[r] = T(0);
+            for (int p = 0; p < NP; ++p) {
+                const T v = vs[p];
+                // the substep's increments apart: one rounding of the running
+                // value per substep
+                if constexpr (ST == 0) {
+                    pa[p] = sw[W] * v;
+                    va[p] = hw[W] * k[p];
+                } else {
+                    pa[p] += sw[W] * v;
+                    va[p] += hw[W] * k[p];
+                }
+                if constexpr (ST < 3) {
+                    ps[p] = pb[p] + sh[H] * v;
+                    vs[p] = vb[p] + hh[H] * k[p];
+                } else {
+                    ps[p] = pb[p] += pa[p];
+                    vs[p] = vb[p] += va[p];
+                }
+            }
+            rs += R::STAGE;
+            // FP64 fills the registers: work moved across stages spills
+            if constexpr (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
+        };
+        stage(std::integral_constant<int, 0>{}, tau0);
+        stage(std::integral_constant<int, 1>{}, tauh);
+        stage(std::integral_constant<int, 2>{}, tauh);
+        stage(std::integral_constant<int, 3>{}, tau1);
     }
-    z.ycc = T(0);
-    z.yct = T(0);
-    const T* cr = rec;
-    const T* rec0 = rec + SR::CRS;
-    // blocks holding no B-/B+ column skip the forcing code (uniform branch)
-    if constexpr (TP::L > 1) {
-        // every block stages the records (in blocks without B-/B+ columns
-        // only to bring the leg blocks into the L2 cache a stage early)
-        stage_store<T, TP>(fbuf, stage_load<T, TP>(rec0, leg, lane), leg, lane);
-    }
-    if ((cb + 1) * 64 <= TP::NX) {
-        tangent_split_loop<T, TP, false, (TP::L > 1)>(z, cr, rec0, xch, leg, lane, a.K, wbm, wbp,
-                                                      tc.off, tc.offcc, fbuf);
-    } else if constexpr (TP::L > 1) {
-        // forcing from the stage records staged in LDS (stage 0's record
-        // stored above, ordered before its reads by stage 0's barrier)
-        tangent_split_loop<T, TP, true, true>(z, cr, rec0, xch, leg, lane, a.K, wbm, wbp, tc.off,
-                                              tc.offcc, fbuf);
-    } else {
-        tangent_split_loop<T, TP, true, false>(z, cr, rec0, xch, leg, lane, a.K, wbm, wbp, tc.off,
-                                               tc.offcc, fbuf);
-    }
-    tangent_store<T, TP>(a, k, leg, lane, tc, z.zb, z.ycc, z.yct, xch);
+    yct = (yt[0] + yt[1]) + (yt[2] + yt[3]);
 }
 
-// Single trajectory: rec holds N interval parts of per_interval(K) elements.
-// FP32 at four waves per SIMD (128 VGPRs, a few bytes of scratch), FP64 at two.
-template <class T, class TP>
+// Single trajectory: items are its intervals; batch: the work list's.
+template <class T>
+struct ItemList {
+    const FwdArgs<T>* descs;   // NULL: one trajectory, `one`
+    const int2* items;
+    const int64_t* rec_off;    // batch: element offset of an item's records
+    T* rec;
+    T* sums;                   // [SUM][n]
+    int n;
+    FwdArgs<T> one;
+    int64_t per;               // one trajectory: elements of an interval's records
+
+    __device__ __forceinline__ int interval(int item) const {
+        return descs ? items[item].y : item;
+    }
+    __device__ __forceinline__ FwdArgs<T> args(int item) const {
+        FwdArgs<T> a = one;
+        if (descs) a = descs[items[item].x];
+        return a;
+    }
+    __device__ __forceinline__ T* records(int item) const {
+        return rec + (descs ? rec_off[item] : (int64_t)item * per);
+    }
+};
+
+template <class T, class TP, bool FLAT>
 __global__ void __launch_bounds__(128)
-    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
-    k_coefrec(FwdArgs<T> a, MConst<TP::NB, TP::NJ, TP::NC> mc,
-                                                 T* __restrict__ rec) {
-    __shared__ RecShared<T, TP> sh;
-    const int k = xcd_slot(blockIdx.x, gridDim.x);
-    coefrec_item<T, TP>(sh, a, mc, k, rec + (int64_t)k * SplitRec<TP>::per_interval(a.K));
+    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3)))
+    k_coefrec(ItemList<T> l, MConst<TP::NB, TP::NJ, TP::NC> mc) {
+    __shared__ PackShared<T> sh;
+    using RT = RedTopo<TP, FLAT>;
+    const int u = xcd_slot(blockIdx.x, gridDim.x);
+    const int blk = u / RT::RECU, w = u - blk * RT::RECU, lane = (int)threadIdx.x & 63;
+    if (w >= 16) {
+        const int want = blk * 64 + lane, item = want < l.n ? want : l.n - 1;
+        const FwdArgs<T> a = l.args(item);
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        const int r = 2 * (w - 16) + wave;
+        if (r < TP::NX) red_fill_early<T, TP, FLAT>(r, a, l.interval(item), want == item);
+        return;
+    }
+    const int want = blk * 64 + 4 * w + (lane >> 4);
+    if (blk * 64 + 4 * w >= l.n) return;
+    const int item = want < l.n ? want : l.n - 1;
+    const FwdArgs<T> a = l.args(item);
+    int most = a.K;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int v = __builtin_amdgcn_readlane(a.K, 16 * q);
+        most = v > most ? v : most;
+    }
+    coefrec_item<T, TP, FLAT>(a, mc, l.interval(item), l.records(item), l.sums + item, l.n,
+                              want == item, most, sh);
 }
 
-template <class T, class TP, int WAVES>
-__global__ void __launch_bounds__(64 * TP::L) __attribute__((amdgpu_waves_per_eu(WAVES)))
-    k_tangent(FwdArgs<T> a, const T* __restrict__ rec) {
-    __shared__ T xch[2 * TP::L * 64];
-    __shared__ T fbuf[2 * SplitRec<TP>::FBUF];
-    int item, cb;
-    unit_item(xcd_slot(blockIdx.x, gridDim.x), a.N, SplitRec<TP>::NBLK, item, cb);
-    tangent_item<T, TP>(a, rec + (int64_t)item * SplitRec<TP>::per_interval(a.K), item, cb, xch,
-                        fbuf);
-}
-
-// Batches: one launch per model over the work list; rec_off[item] is the
-// element offset of the item's part of the workspace.
-// FP32 at four waves per SIMD (128 VGPRs, a few bytes of scratch), FP64 at two.
-template <class T, class TP>
-__global__ void __launch_bounds__(128)
-    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
-    k_coefrec_batch(BatchArgs<FwdArgs<T>> b, MConst<TP::NB, TP::NJ, TP::NC> mc,
-                    T* __restrict__ rec, const int64_t* __restrict__ rec_off) {
-    __shared__ RecShared<T, TP> sh;
-    const int item = xcd_slot(blockIdx.x, gridDim.x);
-    const int2 it = b.items[item];
-    const FwdArgs<T> a = b.descs[it.x];
-    coefrec_item<T, TP>(sh, a, mc, it.y, rec + rec_off[item]);
-}
-
-template <class T, class TP, int WAVES>
-__global__ void __launch_bounds__(64 * TP::L) __attribute__((amdgpu_waves_per_eu(WAVES)))
-    k_tangent_batch(BatchArgs<FwdArgs<T>> b, const T* __restrict__ rec,
-                    const int64_t* __restrict__ rec_off) {
-    __shared__ T xch[2 * TP::L * 64];
-    __shared__ T fbuf[2 * SplitRec<TP>::FBUF];
-    int item, cb;
-    unit_item(xcd_slot(blockIdx.x, gridDim.x), b.n_items, SplitRec<TP>::NBLK, item, cb);
-    const int2 it = b.items[item];
-    const FwdArgs<T> a = b.descs[it.x];
-    tangent_item<T, TP>(a, rec + rec_off[item], it.y, cb, xch, fbuf);
+// Registers: six values per pair and lane, so FP64 holds two waves per SIMD up to
+// 13 pairs (256 registers, none spilled) and one beyond; FP32 three and two.
+// quad13, 12,800 intervals, K = 20: 1,010 us (VALU busy 69 %; 5,600 us with one
+// wave per leg and every row and column of Z), FP32 700 us (3,000 us).
+template <class T, class TP, bool FLAT>
+__global__ void __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu((RedTopo<TP, FLAT>::NP > 14 ? 1 : 2) +
+                                       (sizeof(T) == 4 ? 1 : 0))))
+    k_tangent(ItemList<T> l, const T* __restrict__ recs, const T* __restrict__ sums) {
+    using RT = RedTopo<TP, FLAT>;
+    using RG = RedGrid<TP, FLAT>;
+    __shared__ T lds[RT::LDS];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int u = xcd_slot(blockIdx.x, gridDim.x);
+    const int nblk = (l.n + 63) / 64;
+    if (u >= nblk * RG::UNITS) {
+        const int want = (u - nblk * RG::UNITS) * 64 + lane, item = want < l.n ? want : l.n - 1;
+        red_fill_late<T, TP, FLAT>(wave, RT::IPW, red_dst(l.args(item), l.interval(item)),
+                                   recs + (l.records(item) - l.rec), sums + item, l.n,
+                                   want == item);
+        return;
+    }
+    const int blk = u / RG::UNITS, w = u - blk * RG::UNITS;
+    const int cb = w / RG::GI, first = blk * 64 + (w - cb * RG::GI) * RT::IPW;
+    if (first >= l.n) return;
+    const int item = first + wave < l.n ? first + wave : l.n - 1;
+    const T* rec = recs + (l.records(item) - l.rec);
+    const RedCol col = red_column<TP, FLAT>(cb, lane);
+    T pb[RT::NP], vb[RT::NP], ycc[TP::NC], yct;
+    tangent_item<T, TP, FLAT>(rec, lds + wave * RT::GSZ, col, l.args(item).K, pb, vb, ycc, yct);
+    red_integrals<T, TP, FLAT>(col, rec, sums + item, l.n, ycc, yct);
+    red_store<T, TP, FLAT>(lds, cb, pb, vb, ycc, yct, l.n - first < RT::IPW ? l.n - first : RT::IPW,
+                           [&](int e) { return red_dst(l.args(first + e), l.interval(first + e)); });
 }
 
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-template <int L, int D>
-struct SplitTopo {
-    static constexpr bool ok = L >= 1 && D >= 1;
-};
-
 static bool split_supported(const cis_model* m) { return m->L >= 1 && m->D >= 1; }
 
 template <int L, int D>
-static int64_t split_elems_t(int K) {
-    if constexpr (L >= 1 && D >= 1) return SplitRec<Topo<L, D>>::per_interval(K);
+static int64_t split_elems_t(const cis_model* m, int K) {
+    if constexpr (L >= 1 && D >= 1)
+        return m->A == 0.0 ? PackRec<Topo<L, D>, true>::per_interval(K, 4)
+                           : PackRec<Topo<L, D>, false>::per_interval(K, 4);
     else return -1;
 }
 
 int64_t split_elems_per_interval(const cis_model* m, int K) {
 #define CIS_SPLIT_SZ(LL, DD) \
-    if (m->L == LL && m->D == DD) return split_elems_t<LL, DD>(K);
+    if (m->L == LL && m->D == DD) return split_elems_t<LL, DD>(m, K);
     CIS_TOPOLOGIES(CIS_SPLIT_SZ)
 #undef CIS_SPLIT_SZ
     return -1;
+}
+
+template <int L, int D>
+static int64_t split_records_t(const cis_model* m, int K) {
+    if constexpr (L >= 1 && D >= 1)
+        return m->A == 0.0 ? PackRec<Topo<L, D>, true>::records(K, 4)
+                           : PackRec<Topo<L, D>, false>::records(K, 4);
+    else return -1;
+}
+
+int64_t split_record_elems(const cis_model* m, int K) {
+#define CIS_SPLIT_REC(LL, DD) \
+    if (m->L == LL && m->D == DD) return split_records_t<LL, DD>(m, K);
+    CIS_TOPOLOGIES(CIS_SPLIT_REC)
+#undef CIS_SPLIT_REC
+    return -1;
+}
+
+// The two launches over an item list (FLAT: the model's terrain is flat).
+template <class T, class TP, bool FLAT>
+static void split_launches(const cis_model* m, const ItemList<T>& l, KLaunch* ka, KLaunch* kb) {
+    ka->arg(l);
+    ka->arg(make_const<TP::NB, TP::NJ, TP::NC>(m));
+    ka->func = (const void*)&k_coefrec<T, TP, FLAT>;
+    ka->grid = dim3(RedGrid<TP, FLAT>::rec_blocks(l.n));
+    ka->block = dim3(128);
+    kb->arg(l);
+    kb->arg((const T*)l.rec);
+    kb->arg((const T*)l.sums);
+    kb->func = (const void*)&k_tangent<T, TP, FLAT>;
+    kb->grid = dim3(RedGrid<TP, FLAT>::blocks(l.n));
+    kb->block = dim3(64 * RedTopo<TP, FLAT>::IPW);
 }
 
 template <class T, int L, int D>
 static cis_status launch_split_t(const cis_model* m, const cis_shape* sh, const void* X,
                                  const void* U, const void* s, const void* prm, void* A, void* Bm,
                                  void* Bp, void* S, void* defect, void* xprop, void* ws,
-                                 int waves, hipStream_t stream) {
+                                 hipStream_t stream) {
     if constexpr (L >= 1 && D >= 1) {
         using TP = Topo<L, D>;
-        auto mc = make_const<TP::NB, TP::NJ, TP::NC>(m);
-        FwdArgs<T> a;
-        std::memset(&a, 0, sizeof(a));
+        ItemList<T> l;
+        std::memset(&l, 0, sizeof(l));
+        FwdArgs<T>& a = l.one;
         a.X = (const T*)X;
         a.U = (const T*)U;
         a.s = (const T*)s;
@@ -428,16 +455,17 @@ static cis_status launch_split_t(const cis_model* m, const cis_shape* sh, const 
         a.N = sh->N;
         a.K = sh->substeps;
         a.C = 1;
-        T* rec = (T*)ws;
-        void* args_a[] = {&a, &mc, &rec};
-        hipError_t e = hipLaunchKernel((const void*)&k_coefrec<T, TP>, dim3(sh->N), dim3(128),
-                                       args_a, 0, stream);
+        l.n = sh->N;
+        l.rec = (T*)ws;
+        const bool flat = m->A == 0.0;
+        l.per = flat ? PackRec<TP, true>::records(a.K, 4) : PackRec<TP, false>::records(a.K, 4);
+        l.sums = l.rec + (int64_t)l.n * l.per;
+        KLaunch ka, kb;
+        if (flat) split_launches<T, TP, true>(m, l, &ka, &kb);
+        else split_launches<T, TP, false>(m, l, &ka, &kb);
+        hipError_t e = ka.launch(stream);
         if (e != hipSuccess) return fail(CIS_ERR_HIP, "k_coefrec launch: %s", hipGetErrorString(e));
-        const T* crec = rec;
-        void* args_b[] = {&a, &crec};
-        e = hipLaunchKernel(waves == 2 ? (const void*)&k_tangent<T, TP, 2>
-                                       : (const void*)&k_tangent<T, TP, 1>,
-                            dim3(sh->N * SplitRec<TP>::NBLK), dim3(64 * TP::L), args_b, 0, stream);
+        e = kb.launch(stream);
         if (e != hipSuccess) return fail(CIS_ERR_HIP, "k_tangent launch: %s", hipGetErrorString(e));
         return CIS_OK;
     } else {
@@ -446,29 +474,20 @@ static cis_status launch_split_t(const cis_model* m, const cis_shape* sh, const 
 }
 
 template <class T, int L, int D>
-static cis_status prep_split_t(const cis_model* m, const BatchGroupDev& g, int waves,
-                               KLaunch* ka, KLaunch* kb) {
+static cis_status prep_split_t(const cis_model* m, const BatchGroupDev& g, KLaunch* ka,
+                               KLaunch* kb) {
     if constexpr (L >= 1 && D >= 1) {
         using TP = Topo<L, D>;
-        BatchArgs<FwdArgs<T>> b;
-        b.descs = (const FwdArgs<T>*)g.fdesc;
-        b.items = g.items;
-        b.n_items = g.n_items;
-        b.cursor = g.cursor;
-        ka->arg(b);
-        ka->arg(make_const<TP::NB, TP::NJ, TP::NC>(m));
-        ka->arg((T*)g.rec);
-        ka->arg(g.rec_off);
-        ka->func = (const void*)&k_coefrec_batch<T, TP>;
-        ka->grid = dim3(g.n_items);
-        ka->block = dim3(128);
-        kb->arg(b);
-        kb->arg((const T*)g.rec);
-        kb->arg(g.rec_off);
-        kb->func = waves == 2 ? (const void*)&k_tangent_batch<T, TP, 2>
-                              : (const void*)&k_tangent_batch<T, TP, 1>;
-        kb->grid = dim3(g.n_items * SplitRec<TP>::NBLK);
-        kb->block = dim3(64 * TP::L);
+        ItemList<T> l;
+        std::memset(&l, 0, sizeof(l));
+        l.descs = (const FwdArgs<T>*)g.fdesc;
+        l.items = g.items;
+        l.rec_off = g.rec_off;
+        l.rec = (T*)g.rec;
+        l.sums = (T*)g.sums;
+        l.n = g.n_items;
+        if (m->A == 0.0) split_launches<T, TP, true>(m, l, ka, kb);
+        else split_launches<T, TP, false>(m, l, ka, kb);
         return ka->ok() && kb->ok() ? CIS_OK
                                     : fail(CIS_ERR_DIM, "prep_split_batch: launch record refused");
     } else {
@@ -477,11 +496,11 @@ static cis_status prep_split_t(const cis_model* m, const BatchGroupDev& g, int w
 }
 
 cis_status prep_split_batch(const cis_model* m, int32_t dtype, const BatchGroupDev& g,
-                            int waves, KLaunch* ka, KLaunch* kb) {
+                            KLaunch* ka, KLaunch* kb) {
 #define CIS_PREP_SPLIT(LL, DD)                                                        \
     if (m->L == LL && m->D == DD)                                                     \
-        return dtype == CIS_F64 ? prep_split_t<double, LL, DD>(m, g, waves, ka, kb)   \
-                                : prep_split_t<float, LL, DD>(m, g, waves, ka, kb);
+        return dtype == CIS_F64 ? prep_split_t<double, LL, DD>(m, g, ka, kb)          \
+                                : prep_split_t<float, LL, DD>(m, g, ka, kb);
     CIS_TOPOLOGIES(CIS_PREP_SPLIT)
 #undef CIS_PREP_SPLIT
     return fail(CIS_ERR_UNSUPPORTED, "prep_split_batch: topology has no compiled kernel");
@@ -538,9 +557,9 @@ static cis_status discretize_split_impl(const cis_model* model, const cis_shape*
     if (model->L == LL && model->D == DD)                                                      \
         return shape->dtype == CIS_F64                                                         \
                    ? launch_split_t<double, LL, DD>(model, shape, X, U, s, params, A, Bm, Bp, \
-                                                    S, defect, xprop, ws, waves, hs)           \
+                                                    S, defect, xprop, ws, hs)           \
                    : launch_split_t<float, LL, DD>(model, shape, X, U, s, params, A, Bm, Bp,  \
-                                                   S, defect, xprop, ws, waves, hs);
+                                                   S, defect, xprop, ws, hs);
     CIS_TOPOLOGIES(CIS_DISPATCH_SPLIT)
 #undef CIS_DISPATCH_SPLIT
     return fail(CIS_ERR_UNSUPPORTED, "cis_discretize_split: topology has no compiled kernel");

@@ -158,8 +158,8 @@ def bench_algorithmic_bytes():
         for ds, tn in ((8, "double"), (4, "float")):
             rec = sum(n * split_bytes(m_, ds)[0] for m_, n, k in items)
             tan = sum(n * split_bytes(m_, ds)[1] for m_, n, k in items)
-            out[f"k_coefrec_batch<{tn}, {t}"] = rec
-            out[f"k_tangent_batch<{tn}, {t}"] = tan
+            out[f"k_coefrec<{tn}, {t}"] = rec
+            out[f"k_tangent<{tn}, {t}"] = tan
     imodel, idata = synth.impact_workload("quad13_x64")
     out[f"k_impact<ImpTopo<{imodel.legs}, {imodel.depth}>"] = \
         idata["Xp"].shape[0] * impact_bytes(imodel)
@@ -171,9 +171,9 @@ def bench_algorithmic_bytes():
                                                 interval_bytes(m_, k, "discretize", dsize=4)
                                                 for m_, d, k in qb)
     for ds, tn in ((8, "double"), (4, "float")):
-        out[f"k_coefrec_batch<{tn}, {t}"] = sum(d["s"].shape[0] * split_bytes(m_, ds)[0]
+        out[f"k_coefrec<{tn}, {t}"] = sum(d["s"].shape[0] * split_bytes(m_, ds)[0]
                                                for m_, d, k in qb)
-        out[f"k_tangent_batch<{tn}, {t}"] = sum(d["s"].shape[0] * split_bytes(m_, ds)[1]
+        out[f"k_tangent<{tn}, {t}"] = sum(d["s"].shape[0] * split_bytes(m_, ds)[1]
                                                for m_, d, k in qb)
     return out
 
@@ -204,14 +204,21 @@ PHI_FJ = {2: 300, 5: 700, 7: 1000, 13: 2000}   # per-stage RHS + Jacobian FLOP b
 
 
 def interval_flops(model, K):
-    """Algorithmic forward FLOPs of one interval, K [8 nnz(J) c + 14 nx c + 4 phi_fJ],
-    and the tangent launch's share K [8 nnz(J) + 14 nx] (c - 1) in the split form."""
-    nnz = 2 * 3 * model.nb + 2 * model.nb + 4 * model.nj + 4 * model.nc
+    """Algorithmic forward FLOPs of one interval, K [8 nnz(J) c + 14 nx c + 4 phi_fJ]
+    (the sparse method on every column of Z), and those of the split form's two
+    launches: the nominal stages with the S column, and the coupled columns."""
+    nb, nj, nc = model.nb, model.nj, model.nc
+    nnz = 2 * 3 * nb + 2 * nb + 4 * nj + 4 * nc
     c = model.n + 2 * model.m + 1
-    phi = PHI_FJ.get(model.nb, 1000)
+    phi = PHI_FJ.get(nb, 1000)
     total = K * (8 * nnz * c + 14 * model.nx * c + 4 * phi)
-    tangent = K * (8 * nnz + 14 * model.nx) * (c - 1)
-    return total, tangent
+    record = K * (4 * phi + 8 * nnz + 14 * model.nx)
+    flat = model.terrain_amplitude == 0.0
+    pairs = nb + (0 if flat else 2 * nc)
+    cols = 2 * (nb + (0 if flat else nc)) + 2 * model.m
+    # per column and stage: own-angle and violation terms, joints, feet, forcing, RK
+    stage = 4 * nb + 10 * nj + (4 if flat else 26) * nc + 2 * pairs + 7 * pairs
+    return total, record, 4 * K * cols * stage
 
 
 def bench_algorithmic_flops():
@@ -225,12 +232,11 @@ def bench_algorithmic_flops():
     qb = synth.workload_batch("quad13_N200_K20_x64")
     groups[_topo(qb[0][0])] = [(m_, d["s"].shape[0], k) for m_, d, k in qb]
     for t, items in groups.items():
-        tot = sum(n * interval_flops(m_, k)[0] for m_, n, k in items)
-        tan = sum(n * interval_flops(m_, k)[1] for m_, n, k in items)
+        tot, rec, tan = (sum(n * interval_flops(m_, k)[e] for m_, n, k in items) for e in range(3))
         for tn in ("double", "float"):
             out[f"k_discretize_batch<{tn}, {t}"] = tot
-            out[f"k_coefrec_batch<{tn}, {t}"] = tot - tan
-            out[f"k_tangent_batch<{tn}, {t}"] = tan
+            out[f"k_coefrec<{tn}, {t}"] = rec
+            out[f"k_tangent<{tn}, {t}"] = tan
     return out
 
 
