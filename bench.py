@@ -56,15 +56,18 @@ def split_flops_per_interval(model, K):
 
 def rkf_flops_per_interval(model, K):
     """Per-interval FLOPs of the Runge-Kutta-Fehlberg form (K steps of the 4(5)
-    pair): K [10 nnz(J) c + 28 nx c + 6 phi_fJ] -- five propagated stages of
-    the tangent product, 14 FMAs per tangent element and step for the stage
-    inputs and the solution (partial sums), six right-hand side and Jacobian
-    evaluations per step (the sixth for the estimate)."""
+    pair): six right-hand side and Jacobian evaluations (the sixth for the
+    estimate), the S column's five stages, and the coupled columns of Z, per
+    column five stages of the tangent product and 33 FMAs per pair and step for
+    the stage inputs and the solution."""
     nb, nj, nc = model.nb, model.nj, model.nc
+    flat = model.terrain_amplitude == 0.0
+    pairs = nb + (0 if flat else 2 * nc)
+    cols = 2 * (nb + (0 if flat else nc)) + 2 * model.m
+    stage = 4 * nb + 10 * nj + (4 if flat else 26) * nc + 2 * pairs
     nnz = 2 * 3 * nb + 2 * nb + 4 * nj + 4 * nc
-    c = model.n + 2 * model.m + 1
-    phi = PHI_FJ.get(nb, 1000)
-    return K * (10 * nnz * c + 28 * model.nx * c + 6 * phi)
+    return K * (6 * PHI_FJ.get(nb, 1000) + 10 * nnz + 28 * model.nx
+                + cols * (5 * stage + 66 * pairs))
 
 
 def paper_flops_per_interval(model, K):
@@ -488,31 +491,26 @@ def main():
                                               *routs, vpr(rout["err"]), vpr(rws), rws.numel(),
                                               st_r))
 
-        def launch_rk4_split():   # the register budget the batch tuner picks for quad13
+        def launch_rk4_split():
             _lib.check(lib.cis_discretize_split(rcm.handle, ctypes.byref(rsh), *rargs, 2, *routs,
                                                 vpr(rws), rws.numel(), st_r))
-        # both register budgets of the tangent launch; the faster is reported
-        rkf_by_waves = {w: timed(lambda: launch_rkf(w), args.extra_steps, 2)[0] for w in (1, 2)}
-        rkf_w = min(rkf_by_waves, key=rkf_by_waves.get)
-        ms_rkf = rkf_by_waves[rkf_w]
+        ms_rkf, _ = timed(launch_rkf, args.extra_steps, 2)
         ms_rk4s, _ = timed(launch_rk4_split, args.extra_steps, 2)
-        launch_rkf(rkf_w)
+        launch_rkf()
         torch.cuda.synchronize()
         rkf_fl = rkf_flops_per_interval(rmodel, rK) * rN
         progress(f"rkf quad13 N={rN} K={rK}: {ms_rkf:.3f} ms (rk4 split {ms_rk4s:.3f} ms)")
         extras["rkf_quad13_N12800_K20_f64"] = {
             "value": rN / (ms_rkf * 1e-3), "unit": "intervals/s", "ms_per_step": ms_rkf,
             "rk4_split_ms_same_intervals": ms_rk4s,
-            "tangent_waves_per_simd": {"rkf": rkf_w, "rk4_split": 2},
-            "rkf_ms_by_tangent_waves": {str(w): v for w, v in rkf_by_waves.items()},
             "roofline": {"bound": "alu", "achieved": rkf_fl / (ms_rkf * 1e-3) / 1e12,
                          "peak": PEAK_FP64_VALU / 1e12, "unit": "TFLOP/s",
                          "frac": rkf_fl / (ms_rkf * 1e-3) / PEAK_FP64_VALU,
                          "algorithmic_flop_per_step": rkf_fl,
                          "traffic": {"records": committed_traffic(
-                                         f"k_rkf_rec<double, Topo<{rmodel.legs}, {rmodel.depth}, 6, 1, false>>"),
+                                         f"k_rkf_rec<double, Topo<{rmodel.legs}, {rmodel.depth}, 6, 1, false>, true>"),
                                      "tangent": committed_traffic(
-                                         f"k_rkf_tan<double, Topo<{rmodel.legs}, {rmodel.depth}, 6, 1, false>, {rkf_w}>")}},
+                                         f"k_rkf_tan<double, Topo<{rmodel.legs}, {rmodel.depth}, 6, 1, false>, true>")}},
             "step": "cis_discretize_rkf: Fehlberg 4(5), K=20 steps, records + tangent launches"}
         if not args.no_cpu_baseline:
             rks = [0, 6400, rN - 1]

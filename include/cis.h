@@ -262,8 +262,7 @@ cis_status cis_rkf_workspace_size(const cis_model *model, const cis_shape *shape
  * [N], element type of the shape): for each interval the largest embedded
  * error estimate |h sum_i (bh_i - b_i) K_i| over its steps and all nx rows,
  * bh the fifth-order weights.  Two launches (stage records, then tangent
- * columns) as cis_discretize_split; waves (1 or 2): register budget of the
- * second launch.  ws must hold cis_rkf_workspace_size bytes, 8-byte aligned;
+ * columns) as cis_discretize_split; waves: 1 or 2 as there.  ws must hold cis_rkf_workspace_size bytes, 8-byte aligned;
  * its contents are scratch.  dtype CIS_F64 or CIS_F32.  Models without legs
  * with links: CIS_ERR_UNSUPPORTED.
  */

@@ -299,12 +299,7 @@ __device__ __forceinline__ void state_stage(const Interval<T, TP>& iv,
 // one workgroup barrier; without WRITE only the integral-row integrands are
 // formed (nothing is stored).
 // ---------------------------------------------------------------------------
-// STORES: 0 = values gathered, stored at the end in the compiler's order
-// (FP32 default); 1 = the same with a scheduling fence before the stores
-// (FP64 default); 2 = each value stored as soon as it is formed (fewest
-// registers).
-template <class T, class TP, bool SPLIT = false, bool WRITE = true, class LY = CoefDense<TP>,
-          int STORES = (sizeof(T) == 8 ? 1 : 0)>
+template <class T, class TP, bool SPLIT = false, bool WRITE = true, class LY = CoefDense<TP>>
 __device__ __forceinline__ void coef_stage(const Interval<T, TP>& iv,
                                            const MConst<TP::NB, TP::NJ, TP::NC>& mc,
                                            const BodyConst<T, TP>& c, const T* xs,
@@ -385,12 +380,11 @@ __device__ __forceinline__ void coef_stage(const Interval<T, TP>& iv,
         fa[k] = fv[3 * b + k];
     }
     if constexpr (WRITE) {
-        // STORES = 1 (FP64 by default): all values and addresses are formed
-        // first and stored in one burst, since a register overwritten right
-        // after an LDS store waits until the LDS unit has read it (measured
-        // faster); FP32 keeps the compiler's interleaved order (measured faster
-        // there); STORES = 2 stores at once (throughput kernels).
-        constexpr int NV = STORES < 2 ? 42 + LY::TORSO_COPIES : 1;
+        // FP64: all values and addresses are formed first and stored in one
+        // burst, since a register overwritten right after an LDS store waits
+        // until the LDS unit has read it (measured faster); FP32 keeps the
+        // compiler's interleaved order (measured faster there)
+        constexpr int NV = 43;
         T val[NV];
         T* ptr[NV];
         int e = 0;
@@ -398,14 +392,9 @@ __device__ __forceinline__ void coef_stage(const Interval<T, TP>& iv,
         // one sink slot per lane: stores of many lanes to one LDS address serialize
         T* tr = cf + LY::TRASH + lane;
         auto put = [&](bool ok, int off, T v, int t = 0) {
-            T* const a = ok ? cf + off : tr + t;
-            if constexpr (STORES < 2) {
-                ptr[e] = a;
-                val[e] = v;
-                ++e;
-            } else {
-                *a = v;
-            }
+            ptr[e] = ok ? cf + off : tr + t;
+            val[e] = v;
+            ++e;
         };
         // joint rows of the violation integrand and the joint-force torques
         put(jl, LY::jh(j, 0), s * d0);
@@ -453,16 +442,11 @@ __device__ __forceinline__ void coef_stage(const Interval<T, TP>& iv,
             put(bl, LY::f(NQ + 3 * b + k), fa[k], k);
         }
         const T cth = s * dT * c.ii;
-        put(bl, LY::cth(b, 0), cth);
-        // further copies of the torso entry (compact record: one per leg block)
-#pragma unroll
-        for (int q = 1; q < LY::TORSO_COPIES; ++q) put(lane == 0, LY::cth(0, q), cth, q);
+        put(bl, LY::cth(b), cth);
         put(bl, LY::ctp(b), ctp);
-        if constexpr (STORES < 2) {
-            if constexpr (STORES == 1) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int q = 0; q < NV; ++q) *ptr[q] = val[q];
-        }
+        for (int q = 0; q < NV; ++q) *ptr[q] = val[q];
         (void)e;
     }
     // the lane's body's part of the violation row (summed by the consumers)

@@ -296,15 +296,23 @@ struct StageHold {
     T tau, w, sw, vm, vp, xm, xp;
 };
 
-// What the state wave hands to the coefficient wave, per stage (two slots) and
-// lane: the stage input, its S column, and the rotation; at the end, a flag sum.
-template <class T>
+// What the state wave hands to the coefficient wave, per stage (two slots, in
+// turn; a third for a stage of its own) and lane: the stage input, its rotation
+// and its S column; at the end, a flag sum and the error estimate.
+template <class T, int SLOTS = 2>
 struct PackShared {
+    using Pair = typename PackConst<T>::Pair;
     PackConst<T> lc;
-    T v[2][3][64];                              // velocities
-    typename PackConst<T>::Pair cs[2][64], xy[2][64];   // also read by the children
+    T v[SLOTS][3][64];                  // velocities
+    Pair cs[SLOTS][64], xy[SLOTS][64];  // also read by the children
     T z[2][6][64];
-    T fin[64];
+    T fin[64], err[64];
+    __device__ __forceinline__ void put(int slot, int me, const T (&x)[6], T cb, T sb) {
+        cs[slot][me] = Pair{cb, sb};
+        xy[slot][me] = Pair{x[0], x[1]};
+#pragma unroll
+        for (int q = 0; q < 3; ++q) v[slot][q][me] = x[3 + q];
+    }
 };
 
 // State wave: accelerations f of the stage input xs, derivative kz of the S
@@ -385,10 +393,10 @@ struct PackSums {
 
 // One stage of the coefficient wave (slot: the state wave's): the integrands cc
 // and ct, and with COEF the sums and the stage record (all but CTH).
-template <class T, class TP, bool FLAT, bool COEF>
+template <class T, class TP, bool FLAT, bool COEF, int SLOTS>
 __device__ __forceinline__ void pack_coef(const PackBody<T, TP, FLAT>& c,
                                           const MConst<TP::NB, TP::NJ, TP::NC>& mc,
-                                          const PackShared<T>& sh, int slot, const StageHold<T>& hd,
+                                          const PackShared<T, SLOTS>& sh, int slot, const StageHold<T>& hd,
                                           T& cc, T& ct, PackSums<T, TP, FLAT>& sm,
                                           T* __restrict__ rec, bool write) {
     using R = PackRec<TP, FLAT>;

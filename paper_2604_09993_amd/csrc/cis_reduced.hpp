@@ -552,4 +552,90 @@ __device__ __forceinline__ void red_fill_late(int wave, int waves, const RedDst<
     }
 }
 
+// Single trajectory: items are its intervals; batch: the work list's.
+template <class T>
+struct ItemList {
+    const FwdArgs<T>* descs;   // NULL: one trajectory, `one`
+    const int2* items;
+    const int64_t* rec_off;    // batch: element offset of an item's records
+    T* rec;
+    T* sums;                   // [SUM][n]
+    int n;
+    FwdArgs<T> one;
+    int64_t per;               // one trajectory: elements of an interval's records
+
+    __device__ __forceinline__ int interval(int item) const {
+        return descs ? items[item].y : item;
+    }
+    __device__ __forceinline__ FwdArgs<T> args(int item) const {
+        FwdArgs<T> a = one;
+        if (descs) a = descs[items[item].x];
+        return a;
+    }
+    __device__ __forceinline__ T* records(int item) const {
+        return rec + (descs ? rec_off[item] : (int64_t)item * per);
+    }
+};
+
+// Workgroup of the record launch: closed-form rows, or four intervals of
+// integrate(args, item, not a repeat, largest substep count of the four).
+template <class T, class TP, bool FLAT, class F>
+__device__ __forceinline__ void red_record_block(const ItemList<T>& l, F&& integrate) {
+    using RT = RedTopo<TP, FLAT>;
+    const int u = xcd_slot(blockIdx.x, gridDim.x);
+    const int blk = u / RT::RECU, w = u - blk * RT::RECU, lane = (int)threadIdx.x & 63;
+    if (w >= 16) {
+        const int want = blk * 64 + lane, item = want < l.n ? want : l.n - 1;
+        const FwdArgs<T> a = l.args(item);
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        const int r = 2 * (w - 16) + wave;
+        if (r < TP::NX) red_fill_early<T, TP, FLAT>(r, a, l.interval(item), want == item);
+        return;
+    }
+    const int want = blk * 64 + 4 * w + (lane >> 4);
+    if (blk * 64 + 4 * w >= l.n) return;
+    const int item = want < l.n ? want : l.n - 1;
+    const FwdArgs<T> a = l.args(item);
+    int most = a.K;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int v = __builtin_amdgcn_readlane(a.K, 16 * q);
+        most = v > most ? v : most;
+    }
+    integrate(a, item, want == item, most);
+}
+
+// Workgroup of the tangent launch: four intervals of 64 columns, or the late
+// closed-form entries.  integrate(records, LDS, column, substeps, positions,
+// velocities, ycc, yct).
+template <class T, class TP, bool FLAT, class F>
+__device__ __forceinline__ void red_tangent_block(const ItemList<T>& l, const T* __restrict__ recs,
+                                                  const T* __restrict__ sums, T* lds,
+                                                  F&& integrate) {
+    using RT = RedTopo<TP, FLAT>;
+    using RG = RedGrid<TP, FLAT>;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int u = xcd_slot(blockIdx.x, gridDim.x);
+    const int nblk = (l.n + 63) / 64;
+    if (u >= nblk * RG::UNITS) {
+        const int want = (u - nblk * RG::UNITS) * 64 + lane, item = want < l.n ? want : l.n - 1;
+        red_fill_late<T, TP, FLAT>(wave, RT::IPW, red_dst(l.args(item), l.interval(item)),
+                                   recs + (l.records(item) - l.rec), sums + item, l.n,
+                                   want == item);
+        return;
+    }
+    const int blk = u / RG::UNITS, w = u - blk * RG::UNITS;
+    const int cb = w / RG::GI, first = blk * 64 + (w - cb * RG::GI) * RT::IPW;
+    if (first >= l.n) return;
+    const int item = first + wave < l.n ? first + wave : l.n - 1;
+    const T* rec = recs + (l.records(item) - l.rec);
+    const RedCol col = red_column<TP, FLAT>(cb, lane);
+    T pb[RT::NP], vb[RT::NP], ycc[TP::NC], yct;
+    integrate(rec, lds + wave * RT::GSZ, col, l.args(item).K, pb, vb, ycc, yct);
+    red_integrals<T, TP, FLAT>(col, rec, sums + item, l.n, ycc, yct);
+    red_store<T, TP, FLAT>(lds, cb, pb, vb, ycc, yct, l.n - first < RT::IPW ? l.n - first : RT::IPW,
+                           [&](int e) { return red_dst(l.args(first + e), l.interval(first + e)); });
+}
+
 }  // namespace cis

@@ -10,15 +10,13 @@
 // reported per interval as the largest |e_j| over its steps and all augmented
 // rows.  The stage times tau = (j + c_i) / K feed the FOH controls.
 //
-// Two kernels in the split layout (cis_split.hpp):
-//   k_rkf_rec : per interval two waves, the nominal steps on body lanes
-//               (with the sixth stage for the estimate), the Jacobian
-//               coefficients of the five propagated stages into compact
-//               records, the integral rows, and the dilation column S;
-//   k_rkf_tan : per (interval, block of 64 columns of [Phi_x | B- | B+]) one
-//               wave per leg; each lane carries its column through the five
-//               stages of every step with partial sums of the later stage
-//               inputs (the tableau is not diagonal, unlike classical RK4).
+// Two kernels in the split layout (cis_pack.hpp, cis_reduced.hpp):
+//   k_rkf_rec : four intervals per workgroup of two waves, the nominal steps with
+//               the S column (and the sixth stage for the estimate) and the
+//               coefficients of the five propagated stages;
+//   k_rkf_tan : the coupled columns of [Phi_x | B- | B+], one per lane, with the
+//               stage derivatives of a step kept (the tableau is not diagonal,
+//               unlike classical RK4), and the late closed-form entries.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -30,7 +28,8 @@
 #include "cis_host.hpp"
 #include "cis_launch.hpp"
 #include "cis_model.hpp"
-#include "cis_split.hpp"
+#include "cis_pack.hpp"
+#include "cis_reduced.hpp"
 
 namespace cis {
 
@@ -64,477 +63,433 @@ struct Fehlberg45 {
         return v[i];
     }
     __host__ __device__ static constexpr double e(int i) { return bh(i) - b(i); }
+    // products of the tableau: (A c)_i and (A A c)_i, the responses of a stage to a
+    // force growing with time; (A A)_il and (b A)_l, those of a position to the
+    // velocity derivatives of earlier stages
+    __host__ __device__ static constexpr double ac(int i) {
+        double v = 0;
+        for (int l = 0; l < i; ++l) v += a(i, l) * c(l);
+        return v;
+    }
+    __host__ __device__ static constexpr double aac(int i) {
+        double v = 0;
+        for (int l = 0; l < i; ++l) v += a(i, l) * ac(l);
+        return v;
+    }
+    __host__ __device__ static constexpr double aa(int i, int l) {
+        double v = 0;
+        for (int m = l + 1; m < i; ++m) v += a(i, m) * a(m, l);
+        return v;
+    }
+    __host__ __device__ static constexpr double ba(int l) {
+        double v = 0;
+        for (int m = l + 1; m < R; ++m) v += b(m) * a(m, l);
+        return v;
+    }
 };
 using RKF = Fehlberg45;
 
-template <class T, class TP>
-struct RkfShared {
-    Interval<T, TP> iv;
-    T xring[4][TP::NX];        // stage inputs (record stage t in slot t & 3)
-    T csring[4][TP::NB][2];    // their rotations
-    T fring[4][3 * TP::NB];    // their accelerations
-    T x6[TP::NX];              // sixth-stage input of the current step
-    T cs6[TP::NB][2];
-    T f6[3 * TP::NB];
-    T emax[2];                 // largest estimate: x rows, integral rows
-    T coef[2][CoefRec<TP>::SIZE];
+// What the coefficient wave needs of stage i: c, b, e, A c, A A c.  Its loop runs
+// stage by stage (unrolled over the five, the compiler moves work across them and
+// holds over 500 registers).
+struct RkfStage {
+    double c, b, e, ac, aac;
 };
+constexpr RkfStage rkf_stage(int i) {
+    return {RKF::c(i), RKF::b(i), RKF::e(i), RKF::ac(i), RKF::aac(i)};
+}
+__constant__ const RkfStage RKF_STAGES[6] = {rkf_stage(0), rkf_stage(1), rkf_stage(2),
+                                             rkf_stage(3), rkf_stage(4), rkf_stage(5)};
 
-// h sum_{l <= I} a(I + 1, l) kd[l] (compile-time coefficients; zeros skipped)
+// A tableau coefficient formed where it is used (FP64: in scalar registers; kept
+// in vector registers across the step, 25 of them spill others).
+#define CIS_TAB(V) tableau<T, __builtin_bit_cast(uint64_t, (double)(V))>()
+template <class T, uint64_t BITS>
+__device__ __forceinline__ T tableau() {
+    if constexpr (sizeof(T) == 8) return scalar_const<BITS>();
+    else return (T)__builtin_bit_cast(double, BITS);
+}
+
+// out = base + h sum_{l <= I} a(I + 1, l) kd[l] (zero coefficients skipped)
 template <int I, class T, int NR>
-__device__ __forceinline__ T next_input(const T (&kd)[RKF::R][NR], int r) {
-    T acc = T(0);
+__device__ __forceinline__ void next_input(const T (&kd)[RKF::R][NR], const T (&base)[NR], T h,
+                                           T (&out)[NR]) {
+    T acc[NR];
 #pragma unroll
-    for (int l = 0; l <= I; ++l)
-        if (RKF::a(I + 1, l) != 0.0) acc += T(RKF::a(I + 1, l)) * kd[l][r];
-    return acc;
+    for (int q = 0; q < NR; ++q) acc[q] = T(0);
+    unrolled<I + 1>([&](auto l_c) {
+        constexpr int l = decltype(l_c)::value;
+        if constexpr (RKF::a(I + 1, l) != 0.0) {
+            const T w = CIS_TAB(RKF::a(I + 1, l));
+#pragma unroll
+            for (int q = 0; q < NR; ++q) acc[q] += w * kd[l][q];
+        }
+    });
+#pragma unroll
+    for (int q = 0; q < NR; ++q) out[q] = base[q] + h * acc[q];
 }
 
 // ---------------------------------------------------------------------------
-// k_rkf_rec: interval k by two waves, one workgroup barrier per step (five
-// steps per RKF step):
-//   wave 0 (state, S)    : record stage t at step t; at the fifth stage also
-//                          the sixth (estimate) and the step's end; then the
-//                          S column's record stage t-2 and the copy of that
-//                          record to device memory;
-//   wave 1 (coefficients): record stage t-1 at step t, into coef[(t-1) & 1];
-//                          the integral rows and their estimate.
+// k_rkf_rec: four intervals by two waves, one workgroup barrier per record stage
+// (five per step), the roles of cis_split.hip's record launch: wave 0 the nominal
+// steps and S (at the fifth stage also the sixth, and the step's end), wave 1 the
+// coefficients, sums and integral rows a stage behind, with their estimate.
 // ---------------------------------------------------------------------------
-template <class T, class TP>
-__device__ __forceinline__ void rkf_rec_item(RkfShared<T, TP>& sh, const FwdArgs<T>& a,
-                                             const MConst<TP::NB, TP::NJ, TP::NC>& mc,
-                                             const int k, T* __restrict__ rec, T* __restrict__ err) {
-    constexpr int NB = TP::NB, NX = TP::NX, NXT = TP::NXT, NY = TP::NY, NQ = TP::NQ;
-    constexpr int NC = TP::NC, NJ = TP::NJ;
-    using R = CoefRec<TP>;
-    using SR = SplitRec<TP>;
-    constexpr int NR = RKF::R;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    constexpr int nth = 128;
-    load_interval<T, TP>(sh.iv, a, mc, k, tid, nth);
-    for (int e = tid; e < 2 * R::SIZE; e += nth) (&sh.coef[0][0])[e] = T(0);
+template <class T, class TP, bool FLAT>
+__device__ __forceinline__ void rkf_rec_item(const FwdArgs<T>& a,
+                                             const MConst<TP::NB, TP::NJ, TP::NC>& mc, int k,
+                                             T* __restrict__ rec, T* __restrict__ sums, int64_t n,
+                                             T* __restrict__ err, bool on, PackShared<T, 3>& sh) {
+    constexpr int NQ = TP::NQ, NX = TP::NX, NC = TP::NC, NR = RKF::R;
+    using R = PackRec<TP, FLAT>;
+    const int me = threadIdx.x & 63;
+    PackBody<T, TP, FLAT> c;
+    c.lc = &sh.lc.v[0][me];
+    c.load(a, mc, k, me & 15);   // both waves store the same constants
+    const T s = c.s, Kt = T(a.K), h = T(1) / Kt, sK = s / Kt;
+    T* sr = rec + R::HDR;
     __syncthreads();
-    coefrec_constants<T, TP>(sh.iv, sh.coef[0], tid, nth);
-    coefrec_constants<T, TP>(sh.iv, sh.coef[1], tid, nth);
-    for (int e = tid; e < SR::CRS; e += nth) {
-        T v = T(0);
-        if (e == 0) v = sh.iv.s;
-        else if (e == 1) v = sh.iv.h;
-        else if (e == 2) v = sh.iv.h6;
-        else if (e >= 8 && e < 8 + 4 * NJ) v = sh.iv.kc[(e - 8) >> 2][(e - 8) & 3];
-        rec[e] = v;
-    }
-    const int64_t ldi = a.ldi;
-    const T s = sh.iv.s, h = sh.iv.h, Kt = T(a.K);
-    __syncthreads();
-
-    if (wave == 0) {
-        // ------- state wave (record stage t at step t) and S column (record
-        // stage t-2 at step t, then the copy of that record) -------
-        const BodyConst<T, TP> c = body_const<T, TP>(sh.iv, mc, lane);
-        T xb[6], xs[6], kd[NR][6];
+    if (threadIdx.x < 64) {
+        if (on) pack_header(c, h, rec);
+        T xb[6], xs[6], kd[NR][6], zb[6], zs[6], zd[NR][6], emax = T(0);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            xb[q] = sh.iv.x0[3 * c.b + q];
-            xb[3 + q] = sh.iv.x0[NQ + 3 * c.b + q];
+        for (int q = 0; q < 6; ++q) {
+            xb[q] = a.X[(q < 3 ? 3 * c.b + q : NQ + 3 * c.b + q - 3) * a.ldn + k];
+            xs[q] = xb[q];
+            zb[q] = zs[q] = T(0);
         }
-#pragma unroll
-        for (int q = 0; q < 6; ++q) xs[q] = xb[q];
-        T emax = T(0);
-        constexpr int NCL = SLane<T, TP>::NCL;
-        T zb[6], zs[6], skd[NR][6], ycc[NCL], yct = T(0);
-#pragma unroll
-        for (int q = 0; q < 6; ++q) zb[q] = zs[q] = T(0);
-#pragma unroll
-        for (int l = 0; l < NCL; ++l) ycc[l] = T(0);
-        T* out = rec + SR::CRS;
-        const int nst = NR * a.K, nsteps = nst + 2;
-        for (int j = 0; NR * j < nsteps; ++j) {
-            const T jt = T(j);
-            [&]<int... Is>(std::integer_sequence<int, Is...>) {
-                ([&] {
-                    constexpr int I = Is;
-                    const int t = NR * j + I;
-                    if (t >= nsteps) return;
-                    if (t < nst) {
-                        T fv[3], cb, sb;
-                        body_accel<T, TP>(sh.iv, mc, c, xs, (jt + T(RKF::c(I))) / Kt, fv, cb, sb);
-#pragma unroll
-                        for (int q = 0; q < 6; ++q) kd[I][q] = s * (q < 3 ? xs[3 + q] : fv[q - 3]);
-                        if (lane < NB) {
-#pragma unroll
-                            for (int q = 0; q < 3; ++q) sh.fring[t & 3][3 * c.b + q] = fv[q];
-                            sh.csring[t & 3][c.b][0] = cb;
-                            sh.csring[t & 3][c.b][1] = sb;
-                        }
-                        if constexpr (I < NR - 1) {
-#pragma unroll
-                            for (int q = 0; q < 6; ++q) xs[q] = xb[q] + h * next_input<I>(kd, q);
-                        } else {
-                            // sixth stage (estimate only), then the step's end
-                            T x6[6];
-#pragma unroll
-                            for (int q = 0; q < 6; ++q) x6[q] = xb[q] + h * next_input<I>(kd, q);
-                            T f6[3], c6, s6;
-                            body_accel<T, TP>(sh.iv, mc, c, x6, (jt + T(RKF::c(5))) / Kt, f6, c6,
-                                              s6);
-                            if (lane < NB) {
-#pragma unroll
-                                for (int q = 0; q < 3; ++q) {
-                                    sh.x6[3 * c.b + q] = x6[q];
-                                    sh.x6[NQ + 3 * c.b + q] = x6[3 + q];
-                                    sh.f6[3 * c.b + q] = f6[q];
-                                }
-                                sh.cs6[c.b][0] = c6;
-                                sh.cs6[c.b][1] = s6;
-                            }
-#pragma unroll
-                            for (int q = 0; q < 6; ++q) {
-                                const T k6 = s * (q < 3 ? x6[3 + q] : f6[q - 3]);
-                                T ev = T(RKF::e(5)) * k6, xn = T(0);
-#pragma unroll
-                                for (int l = 0; l < NR; ++l) {
-                                    if (RKF::e(l) != 0.0) ev += T(RKF::e(l)) * kd[l][q];
-                                    if (RKF::b(l) != 0.0) xn += T(RKF::b(l)) * kd[l][q];
-                                }
-                                emax = fmax(emax, fabs(h * ev));
-                                xb[q] += h * xn;
-                                xs[q] = xb[q];
-                            }
-                        }
-                        if (lane < NB) {
-#pragma unroll
-                            for (int q = 0; q < 3; ++q) {
-                                sh.xring[(t + 1) & 3][3 * c.b + q] = xs[q];
-                                sh.xring[(t + 1) & 3][NQ + 3 * c.b + q] = xs[3 + q];
-                            }
-                        }
-                    }
-                    if (t >= 2) {
-                        // the S column's record stage t - 2 (its index within
-                        // the step known at compile time)
-                        constexpr int J = (I + NR - 2) % NR;
-                        const T* cf = sh.coef[(t - 2) & 1];
-                        T kv[3], kcc[NCL], kct;
-                        s_rhs<T, TP, R>(sh.iv, c, zs, cf, lane, kv, kcc, kct);
-#pragma unroll
-                        for (int q = 0; q < 3; ++q) {
-                            skd[J][q] = s * zs[3 + q] + cf[R::f(3 * c.b + q)];
-                            skd[J][3 + q] = kv[q];
-                        }
-                        if constexpr (RKF::b(J) != 0.0) {
-#pragma unroll
-                            for (int l = 0; l < NCL; ++l) ycc[l] += (h * T(RKF::b(J))) * kcc[l];
-                            yct += (h * T(RKF::b(J))) * kct;
-                        }
-                        if constexpr (J < NR - 1) {
-#pragma unroll
-                            for (int q = 0; q < 6; ++q) zs[q] = zb[q] + h * next_input<J>(skd, q);
-                        } else {
-#pragma unroll
-                            for (int q = 0; q < 6; ++q) {
-                                T xn = T(0);
-#pragma unroll
-                                for (int l = 0; l < NR; ++l)
-                                    if (RKF::b(l) != 0.0) xn += T(RKF::b(l)) * skd[l][q];
-                                zb[q] += h * xn;
-                                zs[q] = zb[q];
-                            }
-                        }
-#pragma unroll
-                        for (int e = lane; e < R::GLOBAL; e += 64) out[e] = cf[e];
-                        out += R::GLOBAL;
-                    }
-                    __syncthreads();
-                }(), ...);
-            }(std::make_integer_sequence<int, NR>{});
-        }
-        if (lane < NB) {
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                const int r = q < 3 ? 3 * c.b + q : NQ + 3 * c.b + q - 3;
-                if (a.xprop) a.xprop[r * ldi + k] = xb[q];
-                a.defect[r * ldi + k] = xb[q] - sh.iv.xk1[r];
-            }
-        }
-        T m = T(0);
-#pragma unroll
-        for (int e = 0; e < NB; ++e) m = fmax(m, lane_value(emax, e));
-        if (lane == 0) sh.emax[0] = m;
-        T yt = T(0);
-#pragma unroll
-        for (int e = 0; e < NB; ++e) yt += lane_value(yct, e);
-        if (lane < NB) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                a.S[(int64_t)(3 * c.b + q) * ldi + k] = zb[q];
-                a.S[(int64_t)(NQ + 3 * c.b + q) * ldi + k] = zb[3 + q];
-            }
-            if (c.contact) a.S[(int64_t)(NX + c.i) * ldi + k] = ycc[0];
-            if (lane == 0) a.S[(int64_t)(NX + NC) * ldi + k] = yt;
-        }
-    } else {
-        // ------- coefficient wave: record stage tc at step tc + 1; integral rows -------
-        const BodyConst<T, TP> c = body_const<T, TP>(sh.iv, mc, lane);
-        const int ycc_row = NX + c.i;
-        T ycb = c.contact ? sh.iv.x0[ycc_row] : T(0), ytb = lane == 0 ? sh.iv.x0[NX + NC] : T(0);
-        T emax = T(0);
-        __syncthreads();
         for (int j = 0; j < a.K; ++j) {
             const T jt = T(j);
-            T yac = T(0), yat = T(0), yec = T(0), yet = T(0);
-            [&]<int... Is>(std::integer_sequence<int, Is...>) {
-                ([&] {
-                    constexpr int I = Is;
-                    const int tc = NR * j + I;
-                    T ycc = T(0), yct = T(0);
-                    coef_stage<T, TP, false, true, R, 2>(
-                        sh.iv, mc, c, tc == 0 ? sh.iv.x0 : sh.xring[tc & 3], sh.csring[tc & 3],
-                        sh.fring[tc & 3], (jt + T(RKF::c(I))) / Kt, sh.coef[tc & 1], ycc, yct, lane);
-                    if constexpr (RKF::b(I) != 0.0) {
-                        yac += T(RKF::b(I)) * s * ycc;
-                        yat += T(RKF::b(I)) * s * yct;
-                    }
-                    if constexpr (RKF::e(I) != 0.0) {
-                        yec += T(RKF::e(I)) * s * ycc;
-                        yet += T(RKF::e(I)) * s * yct;
-                    }
-                    if constexpr (I == NR - 1) {
-                        T y6c = T(0), y6t = T(0);
-                        coef_stage<T, TP, false, false>(sh.iv, mc, c, sh.x6, sh.cs6, sh.f6,
-                                                        (jt + T(RKF::c(5))) / Kt, (T*)nullptr,
-                                                        y6c, y6t, lane);
-                        yec += T(RKF::e(5)) * s * y6c;
-                        yet += T(RKF::e(5)) * s * y6t;
-                        ycb += h * yac;
-                        ytb += h * yat;
-                        // estimate: the cross-complementarity rows on their lanes, the
-                        // violation row from the body lanes' parts
-                        T et = T(0);
+            unrolled<NR>([&](auto i_c) {
+                constexpr int I = decltype(i_c)::value;
+                const int slot = (NR * j + I) & 1;
+                T f[3], kz[3], cth, cb, sb;
+                pack_state<T, TP, FLAT>(c, mc, xs, zs, quotient(jt + CIS_TAB(RKF::c(I)), Kt, h), f, kz,
+                                        cth, cb, sb);
+                sh.put(slot, me, xs, cb, sb);
 #pragma unroll
-                        for (int e = 0; e < NB; ++e) et += lane_value(yet, e);
-                        if (c.contact) emax = fmax(emax, fabs(h * yec));
-                        if (lane == 0) emax = fmax(emax, fabs(h * et));
+                for (int q = 0; q < 6; ++q) sh.z[slot][q][me] = zs[q];
+                if (on && c.body) sr[R::CTH + c.b] = cth;
+                sr += R::STAGE;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    kd[I][q] = s * xs[3 + q];
+                    kd[I][3 + q] = s * f[q];
+                    zd[I][q] = s * zs[3 + q] + xs[3 + q];
+                    zd[I][3 + q] = kz[q];
+                }
+                if constexpr (I < NR - 1) {
+                    next_input<I>(kd, xb, h, xs);
+                    next_input<I>(zd, zb, h, zs);
+                } else {
+                    // sixth stage (estimate only), then the step's end
+                    T x6[6], f6[3], kz6[3], cth6, c6, s6;
+                    next_input<I>(kd, xb, h, x6);
+                    pack_state<T, TP, FLAT>(c, mc, x6, zs, quotient(jt + CIS_TAB(RKF::c(5)), Kt, h), f6,
+                                            kz6, cth6, c6, s6);
+                    sh.put(2, me, x6, c6, s6);
+                    T ev[6], xn[6], zn[6];
+                    const T e6 = CIS_TAB(RKF::e(5));
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) {
+                        ev[q] = e6 * (s * (q < 3 ? x6[q < 3 ? 3 + q : 0] : f6[q < 3 ? 0 : q - 3]));
+                        xn[q] = zn[q] = T(0);
                     }
-                    __syncthreads();
-                }(), ...);
-            }(std::make_integer_sequence<int, NR>{});
+                    unrolled<NR>([&](auto l_c) {
+                        constexpr int l = decltype(l_c)::value;
+                        if constexpr (RKF::e(l) != 0.0) {
+                            const T e = CIS_TAB(RKF::e(l));
+#pragma unroll
+                            for (int q = 0; q < 6; ++q) ev[q] += e * kd[l][q];
+                        }
+                        if constexpr (RKF::b(l) != 0.0) {
+                            const T b = CIS_TAB(RKF::b(l));
+#pragma unroll
+                            for (int q = 0; q < 6; ++q) {
+                                xn[q] += b * kd[l][q];
+                                zn[q] += b * zd[l][q];
+                            }
+                        }
+                    });
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) {
+                        emax = fmax(emax, fabs(h * ev[q]));
+                        xs[q] = xb[q] += h * xn[q];
+                        zs[q] = zb[q] += h * zn[q];
+                    }
+                }
+                __syncthreads();
+            });
+        }
+        sh.fin[me] = xb[2] + xb[5];
+        sh.err[me] = emax;
+        // a foot's translation takes 0 x the slope of its contact force on flat
+        // ground: nothing, or a NaN of its angle
+        if (FLAT && c.contact)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                zb[q] += T(0) * zb[2];
+                zb[3 + q] += T(0) * zb[2];
+            }
+        __syncthreads();
+        if (on && c.body)
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+                pack_output(a, k, q < 3 ? 3 * c.b + q : NQ + 3 * c.b + q - 3, xb[q], zb[q]);
+    } else {
+        T ycc = c.contact ? a.X[(NX + c.i) * a.ldn + k] : T(0);
+        T yct = c.torso && c.body ? a.X[(NX + NC) * a.ldn + k] : T(0);
+        T emax = T(0);
+        PackSums<T, TP, FLAT> sm;
+        sm.clear();
+        for (int j = 0; j < a.K; ++j) {
+            const T jt = T(j), t0 = quotient(jt, Kt, h);
+            const T hh = h * h;
+            T vm0, vp0, xm0, xp0;
+            hold_nodes(t0, vm0, vp0, xm0, xp0);
+            T yac = T(0), yat = T(0), yec = T(0), yet = T(0);
+#pragma unroll 1
+            for (int i = 0; i < NR; ++i) {
+                __syncthreads();   // the state wave has left this stage
+                const RkfStage st = RKF_STAGES[i];
+                const T sb = T(st.b), se = T(st.e);
+                // response of a unit mass to the hold weights at the stage input
+                StageHold<T> hd;
+                hd.tau = quotient(jt + T(st.c), Kt, h);
+                hd.w = h * sb;
+                hd.sw = sK * sb;
+                const T h1 = h * T(st.c), h2 = hh * T(st.ac), h3 = hh * (h * T(st.aac));
+                hd.vm = vm0 + (h1 * (T(1) - t0) - h2);
+                hd.vp = vp0 + (h1 * t0 + h2);
+                hd.xm = xm0 + (h1 * vm0 + h2 * (T(1) - t0) - h3);
+                hd.xp = xp0 + (h1 * vp0 + h2 * t0 + h3);
+                T cc, ct;
+                pack_coef<T, TP, FLAT, true>(c, mc, sh, (NR * j + i) & 1, hd, cc, ct, sm, sr, on);
+                sr += R::STAGE;
+                yac += sb * s * cc;
+                yat += sb * s * ct;
+                yec += se * s * cc;
+                yet += se * s * ct;
+            }
+            const T e6 = T(RKF_STAGES[5].e);
+            T c6, t6;
+            pack_coef<T, TP, FLAT, false>(c, mc, sh, 2, StageHold<T>{}, c6, t6, sm, sr, false);
+            yec += e6 * s * c6;
+            yet += e6 * s * t6;
+            ycc += h * yac;
+            yct += h * yat;
+            // estimate: the cross-complementarity rows on their lanes, the
+            // violation row from the body lanes' parts
+            if (c.contact) emax = fmax(emax, fabs(h * yec));
+            emax = fmax(emax, fabs(h * row_sum(yet)));
         }
         __syncthreads();
-        {
-            T acc = T(0);
-#pragma unroll
-            for (int e = 0; e < NB; ++e) acc += lane_value(ytb, e);
-            ytb = acc;
+        const T angles = row_sum(sh.fin[me]);
+        yct = row_sum(yct);
+        const T zct = row_sum(c.body ? sm.zct : T(0));
+        T m = fmax(emax, sh.err[me]);
+        m = fmax(m, row_ror<8>(m));
+        m = fmax(m, row_ror<4>(m));
+        m = fmax(m, row_ror<2>(m));
+        m = fmax(m, row_ror<1>(m));
+        if (on) {
+            pack_sums(c, sm, angles, zct, sums, n);
+            if (c.contact) pack_output(a, k, NX + c.i, ycc, sm.zcc);
+            if (c.torso && c.body) {
+                pack_output(a, k, NX + NC, yct, zct);
+                if (err) err[k] = m;
+            }
         }
-        if (c.contact) {
-            if (a.xprop) a.xprop[ycc_row * ldi + k] = ycb;
-            a.defect[ycc_row * ldi + k] = ycb - sh.iv.xk1[ycc_row];
-        }
-        if (lane == 0) {
-            if (a.xprop) a.xprop[(NX + NC) * ldi + k] = ytb;
-            a.defect[(NX + NC) * ldi + k] = ytb - sh.iv.xk1[NX + NC];
-        }
-        for (int e = lane; e < NXT * NY; e += 64) {
-            const int r = e / NY, cc = NX + e % NY;
-            a.A[((int64_t)r * NXT + cc) * ldi + k] = (r == cc) ? T(1) : T(0);
-        }
-        T m = T(0);
-#pragma unroll
-        for (int e = 0; e < NB; ++e) m = fmax(m, lane_value(emax, e));
-        if (lane == 0) sh.emax[1] = m;
     }
-    __syncthreads();
-    if (err && tid == 0) err[k] = fmax(sh.emax[0], sh.emax[1]);
 }
 
 // ---------------------------------------------------------------------------
-// k_rkf_tan: one Fehlberg stage I of a leg wave.  za = x_j + h sum b_l K_l so
-// far, zs = the stage input, p2..p4 = the partial sums of the inputs of
-// stages 2..4 (each starts at x_j).
+// k_rkf_tan: one step of a column.  Velocity rows keep their stage derivatives
+// k_l; the pose rows follow from them through the products of the tableau (pose
+// rate s v): theta_i = theta + c_i h s w + h^2 s sum (A A)_il k_l.
 // ---------------------------------------------------------------------------
-template <class T, class TP>
-struct RkfLane {
-    static constexpr int NRW = 6 * (TP::D + 1);
-    T za[NRW], zs[NRW], p2[NRW], p3[NRW], p4[NRW];
-    T ycc, yct;
-};
-
-template <int I, class T>
-__device__ __forceinline__ void rkf_combine(T& za, T& zs, T& p2, T& p3, T& p4, T hk) {
-    // hk = h K_I of one row; the input of stage I sits in zs
-    if constexpr (I == 0) {
-        const T base = zs;
-        za = base + T(RKF::b(0)) * hk;
-        p2 = base + T(RKF::a(2, 0)) * hk;
-        p3 = base + T(RKF::a(3, 0)) * hk;
-        p4 = base + T(RKF::a(4, 0)) * hk;
-        zs = base + T(RKF::a(1, 0)) * hk;
-    } else if constexpr (I == 1) {
-        zs = p2 + T(RKF::a(2, 1)) * hk;
-        p3 += T(RKF::a(3, 1)) * hk;
-        p4 += T(RKF::a(4, 1)) * hk;
-    } else if constexpr (I == 2) {
-        zs = p3 + T(RKF::a(3, 2)) * hk;
-        p4 += T(RKF::a(4, 2)) * hk;
-        za += T(RKF::b(2)) * hk;
-    } else if constexpr (I == 3) {
-        zs = p4 + T(RKF::a(4, 3)) * hk;
-        za += T(RKF::b(3)) * hk;
-    } else {
-        za += T(RKF::b(4)) * hk;
-        zs = za;
-    }
-}
-static_assert(Fehlberg45::b(1) == 0.0 && Fehlberg45::b(5) == 0.0,
-              "the tangent stages assume the propagated weights of Fehlberg's pair");
-
-template <class T, class TP, int I, bool FORCE, bool LDSF>
-__device__ __forceinline__ void tangent_rkf_stage(RkfLane<T, TP>& z, const T* __restrict__ cr,
-                                                  const T* __restrict__ lr,
-                                                  const T* __restrict__ rs, T* xch, int leg,
-                                                  int lane, T tau, T wbm, T wbp,
-                                                  const unsigned (&off)[3 * (TP::D + 1)],
-                                                  unsigned offcc, const T* fcur,
-                                                  const T* rs_next, T* fnext) {
-    constexpr int LB = TP::D + 1;
-    const T s = cr[0], h = cr[1];
-    T kv[3 * LB], kcc, kct;
-    tangent_split_rhs<T, TP, FORCE, LDSF>(z.zs, cr, lr, rs, xch, leg, lane, tau, wbm, wbp, off,
-                                          offcc, kv, kcc, kct, fcur, rs_next, fnext);
+template <class T, class TP, bool FLAT>
+__device__ __forceinline__ void rkf_tangent_item(const T* __restrict__ rec, T* lds,
+                                                 const RedCol& col, int K,
+                                                 T (&pb)[RedTopo<TP, FLAT>::NP],
+                                                 T (&vb)[RedTopo<TP, FLAT>::NP], T (&ycc)[TP::NC],
+                                                 T& yct) {
+    using RT = RedTopo<TP, FLAT>;
+    using R = PackRec<TP, FLAT>;
+    using LN = RedLane<T, TP, FLAT>;
+    constexpr int NP = RT::NP, NR = RKF::R;
+    const int lane = threadIdx.x & 63;
+    LN ln;
+    ln.init(rec, lds, col, lane);
+    const T s = rec[0], Kt = uniform(T(K)), h = uniform(T(1) / Kt);
+    const T hs = uniform(s / Kt), hhs = uniform(s / (Kt * Kt));
+    const T* rs = rec + R::HDR;
+    const T* last = rs + (int64_t)(NR * K - 1) * R::STAGE;
+    T ps[NP], vs[NP];
 #pragma unroll
-    for (int r = 0; r < 3 * LB; ++r) {
-        const T hk = h * (s * z.zs[3 * LB + r]);
-        rkf_combine<I>(z.za[r], z.zs[r], z.p2[r], z.p3[r], z.p4[r], hk);
+    for (int p = 0; p < NP; ++p) {
+        pb[p] = p < RT::NU && col.col == p ? T(1) : T(0);
+        vb[p] = p < RT::NU && col.col == RT::NU + p ? T(1) : T(0);
+        ps[p] = pb[p];
+        vs[p] = vb[p];
     }
 #pragma unroll
-    for (int r = 0; r < 3 * LB; ++r) {
-        const int q = 3 * LB + r;
-        rkf_combine<I>(z.za[q], z.zs[q], z.p2[q], z.p3[q], z.p4[q], h * kv[r]);
+    for (int i = 0; i < TP::NC; ++i) ycc[i] = T(0);
+    T kc[R::NVK], cv[2][R::NV], f[2][LN::NFL];
+    T yt[4] = {T(0), T(0), T(0), T(0)};
+    ln.vectors(rec + R::KC, kc);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        ln.vectors(rs + q * R::STAGE, cv[q]);
+        ln.fetch(rs + q * R::STAGE, f[q]);
     }
-    if constexpr (RKF::b(I) != 0.0) {
-        z.ycc += (h * T(RKF::b(I))) * kcc;
-        z.yct += (h * T(RKF::b(I))) * kct;
-    }
-}
-
-template <class T, class TP, bool FORCE, bool LDSF>
-__device__ __forceinline__ void tangent_rkf_loop(RkfLane<T, TP>& z, const T* __restrict__ cr,
-                                                 const T* __restrict__ rec0, T* xch, int leg,
-                                                 int lane, int K, T wbm, T wbp,
-                                                 const unsigned (&off)[3 * (TP::D + 1)],
-                                                 unsigned offcc, T* fbuf) {
-    using R = CoefRec<TP>;
-    constexpr int LEGB = R::LEGB, GL = R::GLOBAL, L = TP::L, FBUF = SplitRec<TP>::FBUF;
-    const T Kt = T(K);
-    const T* rs = rec0;
-    T* xb[2] = {xch, xch + L * 64};
-    T* fb[2] = {fbuf, fbuf + FBUF};
-    int par = 0;   // exchange and forcing buffers of the stage (alternate stage by stage)
-    for (int j = 0; j < K; ++j) {
+    ln.place(f[0]);
+    // steps in pairs: the coefficient slots alternate over an odd number of stages
+    auto step = [&](auto par_c, int j) {
+        constexpr int PAR = decltype(par_c)::value;
         const T jt = T(j);
-        [&]<int... Is>(std::integer_sequence<int, Is...>) {
-            ([&] {
-                constexpr int I = Is;
-                // the interval's last stage copies its own forcing region (never read)
-                const T* rsn = (I == RKF::R - 1 && j + 1 == K) ? rs : rs + GL;
-                tangent_rkf_stage<T, TP, I, FORCE, LDSF>(z, cr, rs + leg * LEGB, rs, xb[par], leg,
-                                                         lane, (jt + T(RKF::c(I))) / Kt, wbm,
-                                                         wbp, off, offcc, fb[par], rsn,
-                                                         fb[par ^ 1]);
-                rs += GL;
-                par ^= 1;
-            }(), ...);
-        }(std::make_integer_sequence<int, RKF::R>{});
-    }
-}
-
-template <class T, class TP>
-__device__ __forceinline__ void rkf_tangent_item(const FwdArgs<T>& a, const T* __restrict__ rec,
-                                                 const int k, const int cb, T* xch, T* fbuf) {
-    constexpr int LB = TP::D + 1;
-    using SR = SplitRec<TP>;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int leg = __builtin_amdgcn_readfirstlane(tid >> 6);
-    T wbm, wbp;
-    RkfLane<T, TP> z;
-    const TanCol<TP> tc = tangent_column<T, TP>(cb, leg, lane, wbm, wbp, z.zs);
+        T kd[NR - 1][NP];
+        unrolled<NR>([&](auto i_c) {
+            constexpr int I = decltype(i_c)::value, SL = (PAR + I) & 1;
+            T k[NP];
+            red_rates<T, TP, FLAT>(ln, kc, cv[SL], uniform(quotient(jt + T(RKF::c(I)), Kt, h)), ps,
+                                   vs, k, ycc, yt, f[SL ^ 1]);
+            const T* ahead = rs + 2 * R::STAGE;
+            ahead = ahead < last ? ahead : last;
+            ln.vectors(ahead, cv[SL]);
+            ln.fetch(ahead, f[SL]);
+            // weights of the next stage input (I + 1), or of the step
+            if constexpr (I < NR - 1) {
+                const T hc = uniform(T(RKF::c(I + 1)) * hs);
 #pragma unroll
-    for (int r = 0; r < 6 * LB; ++r) z.za[r] = z.zs[r];
-    z.ycc = T(0);
-    z.yct = T(0);
-    const T* cr = rec;
-    const T* rec0 = rec + SR::CRS;
-    if constexpr (TP::L > 1) {
-        // every block stages the records (in blocks without B-/B+ columns
-        // only to bring the leg blocks into the L2 cache a stage early)
-        stage_store<T, TP>(fbuf, stage_load<T, TP>(rec0, leg, lane), leg, lane);
+                for (int p = 0; p < NP; ++p) {
+                    kd[I][p] = k[p];
+                    T v = T(0), x = hc * vb[p];
+#pragma unroll
+                    for (int l = 0; l <= I; ++l) {
+                        v += uniform(h * T(RKF::a(I + 1, l))) * kd[l][p];
+                        if (l < I) x += uniform(hhs * T(RKF::aa(I + 1, l))) * kd[l][p];
+                    }
+                    ps[p] = pb[p] + x;
+                    vs[p] = vb[p] + v;
+                }
+            }
+            if constexpr (I == NR - 2) {
+                // the step's end but for the last derivative, which the pose does
+                // not see (the kept derivatives are not needed beyond)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    T v = T(0), x = hs * vb[p];
+#pragma unroll
+                    for (int l = 0; l < NR - 1; ++l) {
+                        if (RKF::b(l) != 0.0) v += uniform(h * T(RKF::b(l))) * kd[l][p];
+                        if (RKF::ba(l) != 0.0) x += uniform(hhs * T(RKF::ba(l))) * kd[l][p];
+                    }
+                    kd[0][p] = v;
+                    pb[p] += x;
+                }
+            }
+            if constexpr (I == NR - 1) {
+                const T w = uniform(h * T(RKF::b(NR - 1)));
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    vs[p] = vb[p] += kd[0][p] + w * k[p];
+                    ps[p] = pb[p];
+                }
+            }
+            rs += R::STAGE;
+            if constexpr (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    static_assert(RKF::b(1) == 0.0 && RKF::b(5) == 0.0 && RKF::ba(NR - 1) == 0.0,
+                  "the last derivative enters the velocity only");
+    for (int j = 0; j < K; j += 2) {
+        step(std::integral_constant<int, 0>{}, j);
+        if (j + 1 < K) step(std::integral_constant<int, 1>{}, j + 1);
     }
-    if ((cb + 1) * 64 <= TP::NX) {
-        tangent_rkf_loop<T, TP, false, (TP::L > 1)>(z, cr, rec0, xch, leg, lane, a.K, wbm, wbp,
-                                                    tc.off, tc.offcc, fbuf);
-    } else if constexpr (TP::L > 1) {
-        // forcing from the stage records staged in LDS (stage 0's record
-        // stored above, ordered before its reads by stage 0's barrier)
-        tangent_rkf_loop<T, TP, true, true>(z, cr, rec0, xch, leg, lane, a.K, wbm, wbp, tc.off,
-                                            tc.offcc, fbuf);
-    } else {
-        tangent_rkf_loop<T, TP, true, false>(z, cr, rec0, xch, leg, lane, a.K, wbm, wbp, tc.off,
-                                             tc.offcc, fbuf);
-    }
-    tangent_store<T, TP>(a, k, leg, lane, tc, z.za, z.ycc, z.yct, xch);
+    yct = (yt[0] + yt[1]) + (yt[2] + yt[3]);
 }
 
-// FP64 at one wave per SIMD: two would spill the stage derivatives to scratch.
-template <class T, class TP>
+// quad13, 3,201 intervals, K = 20: 220 us at two waves per SIMD (108 bytes of
+// scratch per lane), 280 us at one; one interval per workgroup 1,130 us.
+template <class T, class TP, bool FLAT>
 __global__ void __launch_bounds__(128)
-    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 1 : 2)))
-    k_rkf_rec(FwdArgs<T> a, MConst<TP::NB, TP::NJ, TP::NC> mc, T* __restrict__ rec,
-              T* __restrict__ err) {
-    __shared__ RkfShared<T, TP> sh;
-    const int k = xcd_slot(blockIdx.x, gridDim.x);
-    rkf_rec_item<T, TP>(sh, a, mc, k, rec + (int64_t)k * SplitRec<TP>::per_interval(a.K, RKF::R),
-                        err);
+    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3)))
+    k_rkf_rec(ItemList<T> l, MConst<TP::NB, TP::NJ, TP::NC> mc, T* __restrict__ err) {
+    __shared__ PackShared<T, 3> sh;
+    red_record_block<T, TP, FLAT>(l, [&](const FwdArgs<T>& a, int item, bool on, int) {
+        rkf_rec_item<T, TP, FLAT>(a, mc, l.interval(item), l.records(item), l.sums + item, l.n,
+                                  err, on, sh);
+    });
 }
 
-template <class T, class TP, int WAVES>
-__global__ void __launch_bounds__(64 * TP::L) __attribute__((amdgpu_waves_per_eu(WAVES)))
-    k_rkf_tan(FwdArgs<T> a, const T* __restrict__ rec) {
-    __shared__ T xch[2 * TP::L * 64];
-    __shared__ T fbuf[2 * SplitRec<TP>::FBUF];
-    int item, cb;
-    unit_item(xcd_slot(blockIdx.x, gridDim.x), a.N, SplitRec<TP>::NBLK, item, cb);
-    rkf_tangent_item<T, TP>(a, rec + (int64_t)item * SplitRec<TP>::per_interval(a.K, RKF::R),
-                            item, cb, xch, fbuf);
+// Eight values per pair and lane at the fourth stage: FP64 takes one wave per SIMD
+// (346 registers for quad13).  3,201 intervals, K = 20: 610 us (two waves per SIMD
+// spill 270 bytes per lane and take 1,060 us; one wave per leg and every row and
+// column of Z took 4,180 us).
+template <class T, class TP, bool FLAT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 1 : 2)))
+    k_rkf_tan(ItemList<T> l, const T* __restrict__ recs, const T* __restrict__ sums) {
+    __shared__ T lds[RedTopo<TP, FLAT>::LDS];
+    red_tangent_block<T, TP, FLAT>(
+        l, recs, sums, lds,
+        [](const T* rec, T* g, const RedCol& col, int K, auto& pb, auto& vb, auto& ycc, T& yct) {
+            rkf_tangent_item<T, TP, FLAT>(rec, g, col, K, pb, vb, ycc, yct);
+        });
 }
 
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
 template <int L, int D>
-static int64_t rkf_elems_t(int K) {
-    if constexpr (L >= 1 && D >= 1) return SplitRec<Topo<L, D>>::per_interval(K, RKF::R);
+static int64_t rkf_elems_t(const cis_model* m, int K) {
+    if constexpr (L >= 1 && D >= 1)
+        return m->A == 0.0 ? PackRec<Topo<L, D>, true>::per_interval(K, RKF::R)
+                           : PackRec<Topo<L, D>, false>::per_interval(K, RKF::R);
     else return -1;
 }
 
 static int64_t rkf_elems_per_interval(const cis_model* m, int K) {
 #define CIS_RKF_SZ(LL, DD) \
-    if (m->L == LL && m->D == DD) return rkf_elems_t<LL, DD>(K);
+    if (m->L == LL && m->D == DD) return rkf_elems_t<LL, DD>(m, K);
     CIS_TOPOLOGIES(CIS_RKF_SZ)
 #undef CIS_RKF_SZ
     return -1;
+}
+
+template <class T, class TP, bool FLAT>
+static cis_status rkf_launches(const cis_model* m, ItemList<T>& l, T* err, hipStream_t stream) {
+    l.per = PackRec<TP, FLAT>::records(l.one.K, RKF::R);
+    l.sums = l.rec + (int64_t)l.n * l.per;
+    KLaunch ka, kb;
+    ka.arg(l);
+    ka.arg(make_const<TP::NB, TP::NJ, TP::NC>(m));
+    ka.arg(err);
+    ka.func = (const void*)&k_rkf_rec<T, TP, FLAT>;
+    ka.grid = dim3(RedGrid<TP, FLAT>::rec_blocks(l.n));
+    ka.block = dim3(128);
+    hipError_t st = ka.launch(stream);
+    if (st != hipSuccess) return fail(CIS_ERR_HIP, "k_rkf_rec launch: %s", hipGetErrorString(st));
+    kb.arg(l);
+    kb.arg((const T*)l.rec);
+    kb.arg((const T*)l.sums);
+    kb.func = (const void*)&k_rkf_tan<T, TP, FLAT>;
+    kb.grid = dim3(RedGrid<TP, FLAT>::blocks(l.n));
+    kb.block = dim3(64 * RedTopo<TP, FLAT>::IPW);
+    st = kb.launch(stream);
+    if (st != hipSuccess) return fail(CIS_ERR_HIP, "k_rkf_tan launch: %s", hipGetErrorString(st));
+    return CIS_OK;
 }
 
 template <class T, int L, int D>
 static cis_status launch_rkf_t(const cis_model* m, const cis_shape* sh, const void* X,
                                const void* U, const void* s, const void* prm, void* A, void* Bm,
                                void* Bp, void* S, void* defect, void* xprop, void* err, void* ws,
-                               int waves, hipStream_t stream) {
+                               hipStream_t stream) {
     if constexpr (L >= 1 && D >= 1) {
-        using TP = Topo<L, D>;
-        auto mc = make_const<TP::NB, TP::NJ, TP::NC>(m);
-        FwdArgs<T> a;
-        std::memset(&a, 0, sizeof(a));
+        ItemList<T> l;
+        std::memset(&l, 0, sizeof(l));
+        FwdArgs<T>& a = l.one;
         a.X = (const T*)X;
         a.U = (const T*)U;
         a.s = (const T*)s;
@@ -550,20 +505,10 @@ static cis_status launch_rkf_t(const cis_model* m, const cis_shape* sh, const vo
         a.N = sh->N;
         a.K = sh->substeps;
         a.C = 1;
-        T* rec = (T*)ws;
-        T* e = (T*)err;
-        void* args_a[] = {&a, &mc, &rec, &e};
-        hipError_t st = hipLaunchKernel((const void*)&k_rkf_rec<T, TP>, dim3(sh->N), dim3(128),
-                                        args_a, 0, stream);
-        if (st != hipSuccess) return fail(CIS_ERR_HIP, "k_rkf_rec launch: %s", hipGetErrorString(st));
-        const T* crec = rec;
-        void* args_b[] = {&a, &crec};
-        st = hipLaunchKernel(waves == 2 ? (const void*)&k_rkf_tan<T, TP, 2>
-                                        : (const void*)&k_rkf_tan<T, TP, 1>,
-                             dim3(sh->N * SplitRec<TP>::NBLK), dim3(64 * TP::L), args_b, 0,
-                             stream);
-        if (st != hipSuccess) return fail(CIS_ERR_HIP, "k_rkf_tan launch: %s", hipGetErrorString(st));
-        return CIS_OK;
+        l.n = sh->N;
+        l.rec = (T*)ws;
+        return m->A == 0.0 ? rkf_launches<T, Topo<L, D>, true>(m, l, (T*)err, stream)
+                           : rkf_launches<T, Topo<L, D>, false>(m, l, (T*)err, stream);
     } else {
         return fail(CIS_ERR_UNSUPPORTED, "the RKF form needs legs with links");
     }
@@ -617,9 +562,9 @@ static cis_status discretize_rkf_impl(const cis_model* model, const cis_shape* s
     if (model->L == LL && model->D == DD)                                                      \
         return shape->dtype == CIS_F64                                                         \
                    ? launch_rkf_t<double, LL, DD>(model, shape, X, U, s, params, A, Bm, Bp, S, \
-                                                  defect, xprop, err, ws, waves, hs)           \
+                                                  defect, xprop, err, ws, hs)           \
                    : launch_rkf_t<float, LL, DD>(model, shape, X, U, s, params, A, Bm, Bp, S,  \
-                                                 defect, xprop, err, ws, waves, hs);
+                                                 defect, xprop, err, ws, hs);
     CIS_TOPOLOGIES(CIS_DISPATCH_RKF)
 #undef CIS_DISPATCH_RKF
     return fail(CIS_ERR_UNSUPPORTED, "cis_discretize_rkf: topology has no compiled kernel");

@@ -66,11 +66,7 @@ __device__ __forceinline__ void coefrec_item(const FwdArgs<T>& a,
                 T f[3], kz[3], cth, cb, sb;
                 pack_state<T, TP, FLAT>(c, mc, xs, zs, quotient(jt, Kt, h), f, kz, cth, cb, sb);
                 constexpr int sl = ST & 1;
-                using Pair = typename PackConst<T>::Pair;
-                sh.cs[sl][me] = Pair{cb, sb};
-                sh.xy[sl][me] = Pair{xs[0], xs[1]};
-#pragma unroll
-                for (int q = 0; q < 3; ++q) sh.v[sl][q][me] = xs[3 + q];
+                sh.put(sl, me, xs, cb, sb);
 #pragma unroll
                 for (int q = 0; q < 6; ++q) sh.z[sl][q][me] = zs[q];
                 if (on && c.body) sr[R::CTH + c.b] = cth;
@@ -286,59 +282,15 @@ __device__ __forceinline__ void tangent_item(const T* __restrict__ rec, T* lds,
     yct = (yt[0] + yt[1]) + (yt[2] + yt[3]);
 }
 
-// Single trajectory: items are its intervals; batch: the work list's.
-template <class T>
-struct ItemList {
-    const FwdArgs<T>* descs;   // NULL: one trajectory, `one`
-    const int2* items;
-    const int64_t* rec_off;    // batch: element offset of an item's records
-    T* rec;
-    T* sums;                   // [SUM][n]
-    int n;
-    FwdArgs<T> one;
-    int64_t per;               // one trajectory: elements of an interval's records
-
-    __device__ __forceinline__ int interval(int item) const {
-        return descs ? items[item].y : item;
-    }
-    __device__ __forceinline__ FwdArgs<T> args(int item) const {
-        FwdArgs<T> a = one;
-        if (descs) a = descs[items[item].x];
-        return a;
-    }
-    __device__ __forceinline__ T* records(int item) const {
-        return rec + (descs ? rec_off[item] : (int64_t)item * per);
-    }
-};
-
 template <class T, class TP, bool FLAT>
 __global__ void __launch_bounds__(128)
     __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3)))
     k_coefrec(ItemList<T> l, MConst<TP::NB, TP::NJ, TP::NC> mc) {
     __shared__ PackShared<T> sh;
-    using RT = RedTopo<TP, FLAT>;
-    const int u = xcd_slot(blockIdx.x, gridDim.x);
-    const int blk = u / RT::RECU, w = u - blk * RT::RECU, lane = (int)threadIdx.x & 63;
-    if (w >= 16) {
-        const int want = blk * 64 + lane, item = want < l.n ? want : l.n - 1;
-        const FwdArgs<T> a = l.args(item);
-        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-        const int r = 2 * (w - 16) + wave;
-        if (r < TP::NX) red_fill_early<T, TP, FLAT>(r, a, l.interval(item), want == item);
-        return;
-    }
-    const int want = blk * 64 + 4 * w + (lane >> 4);
-    if (blk * 64 + 4 * w >= l.n) return;
-    const int item = want < l.n ? want : l.n - 1;
-    const FwdArgs<T> a = l.args(item);
-    int most = a.K;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int v = __builtin_amdgcn_readlane(a.K, 16 * q);
-        most = v > most ? v : most;
-    }
-    coefrec_item<T, TP, FLAT>(a, mc, l.interval(item), l.records(item), l.sums + item, l.n,
-                              want == item, most, sh);
+    red_record_block<T, TP, FLAT>(l, [&](const FwdArgs<T>& a, int item, bool on, int most) {
+        coefrec_item<T, TP, FLAT>(a, mc, l.interval(item), l.records(item), l.sums + item, l.n, on,
+                                  most, sh);
+    });
 }
 
 // Registers: six values per pair and lane, so FP64 holds two waves per SIMD up to
@@ -350,31 +302,12 @@ __global__ void __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu((RedTopo<TP, FLAT>::NP > 14 ? 1 : 2) +
                                        (sizeof(T) == 4 ? 1 : 0))))
     k_tangent(ItemList<T> l, const T* __restrict__ recs, const T* __restrict__ sums) {
-    using RT = RedTopo<TP, FLAT>;
-    using RG = RedGrid<TP, FLAT>;
-    __shared__ T lds[RT::LDS];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int u = xcd_slot(blockIdx.x, gridDim.x);
-    const int nblk = (l.n + 63) / 64;
-    if (u >= nblk * RG::UNITS) {
-        const int want = (u - nblk * RG::UNITS) * 64 + lane, item = want < l.n ? want : l.n - 1;
-        red_fill_late<T, TP, FLAT>(wave, RT::IPW, red_dst(l.args(item), l.interval(item)),
-                                   recs + (l.records(item) - l.rec), sums + item, l.n,
-                                   want == item);
-        return;
-    }
-    const int blk = u / RG::UNITS, w = u - blk * RG::UNITS;
-    const int cb = w / RG::GI, first = blk * 64 + (w - cb * RG::GI) * RT::IPW;
-    if (first >= l.n) return;
-    const int item = first + wave < l.n ? first + wave : l.n - 1;
-    const T* rec = recs + (l.records(item) - l.rec);
-    const RedCol col = red_column<TP, FLAT>(cb, lane);
-    T pb[RT::NP], vb[RT::NP], ycc[TP::NC], yct;
-    tangent_item<T, TP, FLAT>(rec, lds + wave * RT::GSZ, col, l.args(item).K, pb, vb, ycc, yct);
-    red_integrals<T, TP, FLAT>(col, rec, sums + item, l.n, ycc, yct);
-    red_store<T, TP, FLAT>(lds, cb, pb, vb, ycc, yct, l.n - first < RT::IPW ? l.n - first : RT::IPW,
-                           [&](int e) { return red_dst(l.args(first + e), l.interval(first + e)); });
+    __shared__ T lds[RedTopo<TP, FLAT>::LDS];
+    red_tangent_block<T, TP, FLAT>(
+        l, recs, sums, lds,
+        [](const T* rec, T* g, const RedCol& col, int K, auto& pb, auto& vb, auto& ycc, T& yct) {
+            tangent_item<T, TP, FLAT>(rec, g, col, K, pb, vb, ycc, yct);
+        });
 }
 
 // ---------------------------------------------------------------------------

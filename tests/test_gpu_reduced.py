@@ -60,6 +60,25 @@ def test_tile_edges(legs, depth, terrain, dtype):
         _check(model, d, K, out, dtype)
 
 
+@pytest.mark.parametrize("terrain", ["flat", "sinusoid"])
+@pytest.mark.parametrize("legs,depth", [(1, 1), (2, 2), (2, 3), (4, 3)])
+def test_rkf_tile_edges(legs, depth, terrain):
+    """Odd and even step counts (the coefficient slots alternate over five stages)."""
+    from paper_2604_09993_amd import api
+    for N, K in ((1, 1), (4, 2), (5, 3), (65, 1)):
+        print(f"[gpu] reduced rkf {legs}x{depth} {terrain} N={N} K={K}", flush=True)
+        model, d = _case(legs, depth, terrain, N)
+        cm, X, U, s, p = _dev(model, d, torch.float64)
+        out = api.discretize_rkf(cm, X, U, s, p, K)
+        torch.cuda.synchronize()
+        got = {k: v.cpu().numpy() for k, v in api.as_interval_major(out).items()}
+        ref = oracle.discretize_rkf(model, d["X"], d["U"], d["s"], d["p"], K)
+        errs = compare_outputs(got, ref)
+        bad = {k: e for k, e in errs.items() if not e <= TOL64}
+        assert not bad, bad
+        assert np.all(np.abs(got["err"] - ref["err"]) <= 1e-9 * np.abs(ref["err"]) + 1e-13)
+
+
 @pytest.mark.parametrize("legs,depth,terrain", [(1, 1, "flat"), (2, 2, "sinusoid"), (4, 3, "flat")])
 def test_batch_mixes_substep_counts_in_a_workgroup(legs, depth, terrain):
     from paper_2604_09993_amd import api
