@@ -189,7 +189,7 @@ cis_status cis_adjoint_workspace_size(const cis_model *model, const cis_shape *s
  *   gX_k = A_k^T lambda_k (k < N), gX_N = 0;
  *   gU_k = Bm_k^T lambda_k + Bp_{k-1}^T lambda_{k-1};
  *   gs_k = S_k^T lambda_k;  gparams = sum_k (dF~_k/dp)^T lambda_k.
- * The substep states are recomputed from ckpt (written by cis_defects with
+ * The substep starts come or are recomputed from ckpt (written by cis_defects with
  * the same ckpt_every).  Reductions over intervals are done in a fixed order
  * (run-to-run bitwise reproducible).  ws must hold
  * cis_adjoint_workspace_size bytes.  dtype CIS_F64 only.
@@ -416,14 +416,14 @@ enum { CIS_BATCH_DISCRETIZE = 1, CIS_BATCH_ADJOINT = 2 };
 enum { CIS_SCHED_GRID = 1, CIS_SCHED_PERSISTENT = 2, CIS_SCHED_TUNE = 3 };
 
 /* Optional bits of `sched` fixing the form of the reverse sweep (waves per
- * interval) instead of the default: timed at creation with CIS_SCHED_TUNE,
- * else three waves.  4: two waves evaluate alternate stages ahead of the
+ * interval) instead of the default: for models with legs with links, four
+ * intervals per workgroup on body lanes (checkpoints at most 16 substeps apart);
+ * else timed at creation with CIS_SCHED_TUNE, or three waves.  4: two waves evaluate alternate stages ahead of the
  * reverse sweep, each evaluation spread over two pipeline steps; 3: one wave
  * evaluates each stage one step ahead (4 and 3 need checkpoints at most 8
  * substeps apart, else 2 is used); 2: replay one chunk ahead; 1: one wave
  * (fewest wave-cycles, for throughput).  At most one of these bits may be
- * set.  The defects pass is likewise timed in its two forms with
- * CIS_SCHED_TUNE. */
+ * set. */
 enum { CIS_SCHED_ADJ_1 = 0x10, CIS_SCHED_ADJ_2 = 0x20, CIS_SCHED_ADJ_3 = 0x30,
        CIS_SCHED_ADJ_4 = 0x100 };
 
@@ -441,10 +441,11 @@ enum { CIS_SCHED_WAVES_1 = 0x40, CIS_SCHED_WAVES_2 = 0x80 };
 
 /* Optional bits of `sched` fixing the form of the defects pass that the
  * reverse sweep starts from (CIS_BATCH_ADJOINT): CIS_SCHED_DEF_BODY takes
- * two waves per interval (body-lane state recursion and a wave forming the
- * integral rows, as cis_defects), CIS_SCHED_DEF_LANE one wave per interval
- * (element-parallel right-hand side).  Without either bit both are timed
- * with CIS_SCHED_TUNE, and the first is used otherwise.  Setting both bits
+ * two waves (body-lane state recursion and a wave forming the integral rows, as
+ * cis_defects; per four intervals for models with legs with links), and
+ * CIS_SCHED_DEF_LANE one wave per interval (element-parallel right-hand side).
+ * Without either bit the first is used, except that models without links have
+ * both timed with CIS_SCHED_TUNE.  Setting both bits
  * is an error (CIS_ERR_DIM). */
 enum { CIS_SCHED_DEF_BODY = 0x200, CIS_SCHED_DEF_LANE = 0x400 };
 
@@ -462,8 +463,9 @@ enum { CIS_SCHED_SPLIT = 0x800, CIS_SCHED_FUSED = 0x1000 };
 /*
  * Create a plan for n_traj trajectories (all of one dtype; CIS_BATCH_ADJOINT
  * needs CIS_F64).  ckpt_every: substeps between the checkpoints of the reverse
- * sweep; it must divide every trajectory's K, or be 0 to take, per
- * trajectory, the largest divisor of K not above 8.  graph != 0 also builds
+ * sweep; it must divide every trajectory's K, or be 0 to choose, per trajectory: 1
+ * (models with legs with links, no CIS_SCHED_ADJ bit, checkpoints of at most 16 GiB
+ * and a quarter of the free memory) or the largest divisor of K not above 8.  graph != 0 also builds
  * the HIP graphs used by cis_batch_graph_run.
  * Errors: CIS_ERR_NULL, CIS_ERR_DIM, CIS_ERR_LAYOUT, CIS_ERR_DTYPE,
  * CIS_ERR_UNSUPPORTED (as for the single-trajectory calls, with the offending

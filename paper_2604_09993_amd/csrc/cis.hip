@@ -819,16 +819,26 @@ static cis_status launch_defects(const cis_model* m, const cis_shape* sh, const 
                                  const void* U, const void* s, const void* prm, void* d,
                                  void* xp, void* ckpt, int C, hipStream_t stream) {
     using TP = Topo<L, D>;
-    auto mc = make_const<TP::NB, TP::NJ, TP::NC>(m);
     FwdArgs<T> a = make_args<T>(sh, X, U, s, prm);
     a.defect = (T*)d;
     a.xprop = (T*)xp;
     a.ckpt = (T*)ckpt;
     a.C = C;
-    void* args[] = {&a, &mc};
-    hipError_t e = hipLaunchKernel((const void*)&k_defects<T, TP>, dim3(sh->N), dim3(128), args,
-                                   0, stream);
-    if (e != hipSuccess) return fail(CIS_ERR_HIP, "k_defects launch: %s", hipGetErrorString(e));
+    if constexpr (L >= 1 && D >= 1) {
+        KLaunch l;
+        const cis_status st = prep_defects_pack(m, sh->dtype, &a, nullptr, &l);
+        if (st != CIS_OK) return st;
+        const hipError_t pe = l.launch(stream);
+        if (pe != hipSuccess)
+            return fail(CIS_ERR_HIP, "k_defects_pack launch: %s", hipGetErrorString(pe));
+    } else {
+        auto mc = make_const<TP::NB, TP::NJ, TP::NC>(m);
+        void* args[] = {&a, &mc};
+        const hipError_t e = hipLaunchKernel((const void*)&k_defects<T, TP>, dim3(sh->N),
+                                             dim3(128), args, 0, stream);
+        if (e != hipSuccess)
+            return fail(CIS_ERR_HIP, "k_defects launch: %s", hipGetErrorString(e));
+    }
     return CIS_OK;
 }
 
@@ -931,10 +941,14 @@ template <class T, int L, int D>
 static cis_status prep_def_t(const cis_model* m, const BatchGroupDev& g, bool body_lanes,
                              KLaunch* out) {
     using TP = Topo<L, D>;
+    if constexpr (L >= 1 && D >= 1)
+        if (body_lanes)
+            return prep_defects_pack(m, sizeof(T) == 8 ? CIS_F64 : CIS_F32, nullptr, &g, out);
     out->arg(batch_args<T>(g));
     out->arg(make_const<TP::NB, TP::NJ, TP::NC>(m));
-    out->func = body_lanes ? (const void*)&k_defects_batch<T, TP>
-                           : (const void*)&k_defects_lane_batch<T, TP>;
+    out->func = (const void*)&k_defects_lane_batch<T, TP>;
+    if constexpr (L < 1 || D < 1)
+        if (body_lanes) out->func = (const void*)&k_defects_batch<T, TP>;
     out->grid = dim3(g.n_items);
     out->block = dim3(body_lanes ? 128 : 64);
     return out->ok() ? CIS_OK : fail(CIS_ERR_DIM, "prep_defects_batch: launch record refused");

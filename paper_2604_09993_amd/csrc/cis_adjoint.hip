@@ -762,47 +762,64 @@ __global__ void __launch_bounds__(64 * NW)
     adjoint_item<T, TP, NW>(ax, a, mc, it.y);
 }
 
-// gU, gX_N and gp from the per-interval partials, in a fixed order.
-template <class T>
-__device__ __forceinline__ void adjoint_reduce_part(const T* ws_uk, const T* ws_uk1,
-                                                    const T* ws_p, T* gU, T* gX, T* gp, int N,
-                                                    int m, int nxt, int np, int64_t ldn,
-                                                    int64_t t) {
-    const int64_t nu = (int64_t)m * (N + 1);
-    if (t < nu) {
-        const int c = (int)(t / (N + 1)), k = (int)(t % (N + 1));
-        const T left = k < N ? ws_uk[(int64_t)c * N + k] : T(0);
-        const T right = k > 0 ? ws_uk1[(int64_t)c * N + k - 1] : T(0);
-        gU[(int64_t)c * ldn + k] = left + right;
-    } else if (t < nu + nxt) {
-        gX[(t - nu) * ldn + N] = T(0);
-    } else if (t < nu + nxt + np) {
-        // index order (bitwise reproducible); unrolled so that the loads of
-        // eight partials are in flight together instead of one at a time
-        const int c = (int)(t - nu - nxt);
-        const T* w = ws_p + (int64_t)c * N;
-        T acc = T(0);
-#pragma unroll 8
-        for (int k = 0; k < N; ++k) acc += w[k];
-        gp[c] = acc;
+// gU, gX_N and gp from the per-interval partials, in a fixed order (bitwise
+// reproducible).  Block b of a trajectory: `chunks` blocks for each control row, then
+// one block per parameter, then one for gX_N; `rows`, `params`: the largest counts
+// of a batch.  12,800 quad13 intervals in ten
+// trajectories: one workgroup per trajectory, a thread per parameter, took 163 us.
+__device__ __forceinline__ void adjoint_reduce_block(const RedDesc& r, int b, int rows, int chunks,
+                                                     int params) {
+    const int tid = threadIdx.x, N = r.N;
+    if (b < rows * chunks) {
+        const int c = b / chunks;
+        if (c >= r.m) return;
+        const double *wk = r.ws_uk + (int64_t)c * N, *wk1 = r.ws_uk1 + (int64_t)c * N;
+        for (int64_t k = (b - c * chunks) * 256 + tid; k <= N; k += 256 * chunks) {
+            const double left = k < N ? wk[k] : 0.0;
+            const double right = k > 0 ? wk1[k - 1] : 0.0;
+            r.gU[c * r.ldn + k] = left + right;
+        }
+        return;
     }
+    const int c = b - rows * chunks;
+    if (c == params) {
+        for (int t = tid; t < r.nxt; t += 256) r.gX[t * r.ldn + N] = 0.0;
+        return;
+    }
+    if (c >= r.np) return;
+    // thread sums in index order, then a fixed tree
+    const double* w = r.ws_p + (int64_t)c * N;
+    double acc = 0.0;
+#pragma unroll 4
+    for (int64_t k = tid; k < N; k += 256) acc += w[k];
+    __shared__ double part[256];
+    part[tid] = acc;
+    for (int n = 128; n > 0; n >>= 1) {
+        __syncthreads();
+        if (tid < n) part[tid] += part[tid + n];
+    }
+    if (tid == 0) r.gp[c] = part[0];
 }
 
-// One workgroup per trajectory of a batch.
-__global__ void __launch_bounds__(256) k_adjoint_reduce_batch(const RedDesc* rd) {
-    const RedDesc r = rd[blockIdx.x];
-    const int64_t work = (int64_t)r.m * (r.N + 1) + r.nxt + r.np;
-    for (int64_t t = threadIdx.x; t < work; t += blockDim.x)
-        adjoint_reduce_part<double>(r.ws_uk, r.ws_uk1, r.ws_p, r.gU, r.gX, r.gp, r.N, r.m, r.nxt,
-                                    r.np, r.ldn, t);
-}
-
-template <class T>
 __global__ void __launch_bounds__(256)
-    k_adjoint_reduce(const T* ws_uk, const T* ws_uk1, const T* ws_p, T* gU, T* gX, T* gp, int N,
-                     int m, int nxt, int np, int64_t ldn) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    adjoint_reduce_part<T>(ws_uk, ws_uk1, ws_p, gU, gX, gp, N, m, nxt, np, ldn, t);
+    k_adjoint_reduce_batch(const RedDesc* rd, int rows, int chunks, int params) {
+    const int per = rows * chunks + params + 1;
+    adjoint_reduce_block(rd[blockIdx.x / per], blockIdx.x % per, rows, chunks, params);
+}
+
+__global__ void __launch_bounds__(256)
+    k_adjoint_reduce(RedDesc r, int rows, int chunks, int params) {
+    adjoint_reduce_block(r, blockIdx.x, rows, chunks, params);
+}
+
+// `most`: the largest extents of the trajectories
+static void reduce_grid(const RedDesc& most, int n_traj, KLaunch* out) {
+    const int chunks = most.N < 16 * 256 ? most.N / 256 + 1 : 16;   // (short ones idle in a mixed batch)
+    out->arg(most.m);
+    out->arg(chunks);
+    out->arg(most.np);
+    out->grid = dim3((uint32_t)(most.m * chunks + most.np + 1) * n_traj);
+    out->block = dim3(256);
 }
 
 static size_t ws_elems(const cis_model* m, int N) { return (size_t)(2 * m->m + m->np) * N; }
@@ -835,26 +852,41 @@ static cis_status launch_adjoint(const cis_model* m, const cis_shape* sh, const 
     a.ws_uk = w;
     a.ws_uk1 = w + (size_t)m->m * N;
     a.ws_p = w + (size_t)2 * m->m * N;
-    void* args[] = {&a, &mc};
-    const bool four = C <= CHUNK;   // one chunk per checkpoint segment
-    hipError_t e = hipLaunchKernel(four ? (const void*)&k_adjoint4<T, TP>
-                                        : (const void*)&k_adjoint<T, TP>,
-                                   dim3(N), dim3(four ? 256 : 128), args, 0,
-                                   stream);
+    hipError_t e;
+    if (gradient_pack_supported(m) && C <= gradient_pack_max_ckpt()) {
+        KLaunch l;
+        const cis_status st = prep_adjoint_pack(m, &a, nullptr, C, &l);
+        if (st != CIS_OK) return st;
+        e = l.launch(stream);
+    } else {
+        void* args[] = {&a, &mc};
+        const void* k = (const void*)&k_adjoint<T, TP>;
+        bool four = false;
+        if constexpr (L < 1 || D < 1) {
+            four = C <= CHUNK;   // one chunk per checkpoint segment
+            if (four) k = (const void*)&k_adjoint4<T, TP>;
+        }
+        e = hipLaunchKernel(k, dim3(N), dim3(four ? 256 : 128), args, 0, stream);
+    }
     if (e != hipSuccess) return fail(CIS_ERR_HIP, "k_adjoint launch: %s", hipGetErrorString(e));
-    const int64_t work = (int64_t)m->m * (N + 1) + m->nx + m->np;
-    const int blocks = (int)((work + 255) / 256);
-    const T* wuk = a.ws_uk;
-    const T* wuk1 = a.ws_uk1;
-    const T* wp = a.ws_p;
-    T* gUp = (T*)gU;
-    T* gXp = (T*)gX;
-    T* gpp = (T*)gp;
-    int mm = m->m, nxt = m->nx, np = m->np;
-    int64_t ldn = sh->ld_node;
-    void* rargs[] = {&wuk, &wuk1, &wp, &gUp, &gXp, &gpp, (void*)&N, &mm, &nxt, &np, &ldn};
-    e = hipLaunchKernel((const void*)&k_adjoint_reduce<T>, dim3(blocks), dim3(256), rargs, 0,
-                        stream);
+    RedDesc r;
+    std::memset(&r, 0, sizeof(r));
+    r.ws_uk = a.ws_uk;
+    r.ws_uk1 = a.ws_uk1;
+    r.ws_p = a.ws_p;
+    r.gU = (T*)gU;
+    r.gX = (T*)gX;
+    r.gp = (T*)gp;
+    r.N = N;
+    r.m = m->m;
+    r.nxt = m->nx;
+    r.np = m->np;
+    r.ldn = sh->ld_node;
+    KLaunch red;
+    red.arg(r);
+    red.func = (const void*)&k_adjoint_reduce;
+    reduce_grid(r, 1, &red);
+    e = red.ok() ? red.launch(stream) : hipErrorInvalidValue;
     if (e != hipSuccess)
         return fail(CIS_ERR_HIP, "k_adjoint_reduce launch: %s", hipGetErrorString(e));
     return CIS_OK;
@@ -890,11 +922,11 @@ cis_status prep_adjoint_batch(const cis_model* m, const BatchGroupDev& g, int ma
     return fail(CIS_ERR_UNSUPPORTED, "prep_adjoint_batch: topology has no compiled kernel");
 }
 
-cis_status prep_adjoint_reduce_batch(const void* rdesc, int n_traj, KLaunch* out) {
+cis_status prep_adjoint_reduce_batch(const void* rdesc, const RedDesc& most, int n_traj,
+                                     KLaunch* out) {
     out->arg((const RedDesc*)rdesc);
     out->func = (const void*)&k_adjoint_reduce_batch;
-    out->grid = dim3(n_traj);
-    out->block = dim3(256);
+    reduce_grid(most, n_traj, out);
     return out->ok() ? CIS_OK : fail(CIS_ERR_DIM, "prep_adjoint_reduce_batch: launch record refused");
 }
 

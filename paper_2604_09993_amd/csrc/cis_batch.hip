@@ -468,9 +468,20 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
     p->ckpt_off.assign(n_traj, 0);
     p->ws_off.assign(n_traj, 0);
     if (ops & CIS_BATCH_ADJOINT) {
+        // The packed sweep runs fastest from every substep's start (12,800 quad13
+        // intervals, K = 20: 0.57 ms with 160 MB of them, and one wave less than the
+        // forms that integrate the starts again); sparser ones are kept where these
+        // take more than 16 GiB or a quarter of the free memory.
+        size_t dense = 0, avail = 0, total = 0;
+        for (int i = 0; i < n_traj; ++i)
+            dense += (size_t)trajs[i].substeps * trajs[i].model->n * trajs[i].ld_int * es;
+        if (hipMemGetInfo(&avail, &total) != hipSuccess) avail = 0;
+        const bool every = !adj_force && dense <= std::min((size_t)16 << 30, avail / 4);
         for (int i = 0; i < n_traj; ++i) {
             const cis_traj& t = trajs[i];
-            const int C = ckpt_every > 0 ? ckpt_every : auto_ckpt(t.substeps);
+            const int C = ckpt_every > 0 ? ckpt_every
+                          : every && gradient_pack_supported(t.model) ? 1
+                                                                      : auto_ckpt(t.substeps);
             p->ckpt_every[i] = C;
             p->ckpt_off[i] = off;
             off = align_up(off + (size_t)(t.substeps / C) * t.model->n * t.ld_int * es);
@@ -606,7 +617,7 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
         cis_status st;
         std::string key;
         TuneChoice want, made;
-        bool cached_all = !cpath.empty();
+        bool cached_all = false;   // the key's entry is there and every choice from it
         if (!cpath.empty()) {
             int kmin = 1 << 30, kmax = 0, cmx = 1;
             for (int i : g.trajs) {
@@ -620,7 +631,10 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
                           g.items.size(), kmin, kmax, (ops & CIS_BATCH_ADJOINT) ? cmx : 0);
             key = kb;
             auto it = cache.find(key);
-            if (it != cache.end()) want = it->second;
+            if (it != cache.end()) {
+                want = it->second;
+                cached_all = true;
+            }
         }
         if (ops & CIS_BATCH_DISCRETIZE) {
             // candidates: (grid | persistent) x register budget (1 or 2 waves
@@ -715,7 +729,13 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
             st = prep_defects_batch(g.model, dtype, dd, true, &def_body);
             if (st == CIS_OK) st = prep_defects_batch(g.model, dtype, dd, false, &def_lane);
             g.def = def_force == 2 ? def_lane : def_body;
-            if (st == CIS_OK && sched == CIS_SCHED_TUNE && !def_force && want.def_lane >= 0) {
+            // The packed forms where the model has them, and the sweep where one launch
+            // can take the group (one spacing, which its buffers hold).  quad13: defects
+            // and sweep of 12,800 intervals 0.25 + 0.57 ms against 0.93 + 7.8 (the best
+            // of the other forms), of 50 cheetah7 intervals 47 + 82 us against 54 + 130.
+            const bool packs = gradient_pack_supported(g.model);
+            if (packs) {
+            } else if (st == CIS_OK && sched == CIS_SCHED_TUNE && !def_force && want.def_lane >= 0) {
                 g.def = want.def_lane ? def_lane : def_body;
             } else if (st == CIS_OK && sched == CIS_SCHED_TUNE && !def_force) {
                 cached_all = false;
@@ -727,12 +747,19 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
                 }
                 if (tl < tb) g.def = def_lane;
             }
-            int cmax_g = 1;
-            for (int i : g.trajs) cmax_g = std::max(cmax_g, p->ckpt_every[i]);
+            int cmax_g = 1, cmin_g = 1 << 30;
+            for (int i : g.trajs) {
+                cmax_g = std::max(cmax_g, p->ckpt_every[i]);
+                cmin_g = std::min(cmin_g, p->ckpt_every[i]);
+            }
             // reverse sweep with 4, 3, 2 or 1 waves per interval (latency vs
             // throughput): timed when tuning, else the three-wave form
+            const bool pack_adj = packs && !adj_force && cmin_g == cmax_g &&
+                                  cmax_g <= gradient_pack_max_ckpt();
             KLaunch adjv[4];
-            for (int w = 0; w < 4 && st == CIS_OK; ++w)
+            if (pack_adj && st == CIS_OK)
+                st = prep_adjoint_pack(g.model, nullptr, &g.dev, cmax_g, &adjv[1]);
+            for (int w = 0; w < 4 && st == CIS_OK && !pack_adj; ++w)
                 st = prep_adjoint_batch(g.model, g.dev, cmax_g, 4 - w, &adjv[w]);
             if (st != CIS_OK) {
                 plan_free(p);
@@ -740,7 +767,8 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
             }
             made.def_lane = g.def.func == def_lane.func ? 1 : 0;
             int best = adj_force ? 4 - adj_force : 1;
-            if (sched == CIS_SCHED_TUNE && !adj_force && want.adj_waves >= 1 && want.adj_waves <= 4) {
+            if (pack_adj) {
+            } else if (sched == CIS_SCHED_TUNE && !adj_force && want.adj_waves >= 1 && want.adj_waves <= 4) {
                 best = 4 - want.adj_waves;
             } else if (sched == CIS_SCHED_TUNE && !adj_force) {
                 cached_all = false;
@@ -795,7 +823,14 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
         }
     }
     if (ops & CIS_BATCH_ADJOINT) {
-        cis_status st = prep_adjoint_reduce_batch(d + p->rdesc_off, n_traj, &p->red);
+        RedDesc most;
+        std::memset(&most, 0, sizeof(most));
+        for (int i = 0; i < n_traj; ++i) {
+            most.N = std::max(most.N, (int)trajs[i].N);
+            most.m = std::max(most.m, (int)trajs[i].model->m);
+            most.np = std::max(most.np, (int)trajs[i].model->np);
+        }
+        cis_status st = prep_adjoint_reduce_batch(d + p->rdesc_off, most, n_traj, &p->red);
         if (st != CIS_OK) {
             plan_free(p);
             return st;

@@ -86,8 +86,21 @@ cis_status prep_defects_batch(const cis_model* m, int32_t dtype, const BatchGrou
 // the spacing is at most 8), 2 = replay a chunk ahead, 1 = one wave)
 cis_status prep_adjoint_batch(const cis_model* m, const BatchGroupDev& g, int max_ckpt_every,
                               int waves, KLaunch* out);
-// gU, gX_N and gp of n_traj trajectories from their partials (RedDesc array).
-cis_status prep_adjoint_reduce_batch(const void* rdesc, int n_traj, KLaunch* out);
+// Gradient step of models with legs with links, four intervals per workgroup: of
+// one trajectory (`one`: its FwdArgs<T> / AdjArgs<double>) or of a model group.
+// The reverse sweep takes checkpoints C <= gradient_pack_max_ckpt() substeps apart
+// (the same for every trajectory).
+bool gradient_pack_supported(const cis_model* m);
+int gradient_pack_max_ckpt();
+cis_status prep_defects_pack(const cis_model* m, int32_t dtype, const void* one,
+                             const BatchGroupDev* g, KLaunch* out);
+cis_status prep_adjoint_pack(const cis_model* m, const void* one, const BatchGroupDev* g, int C,
+                             KLaunch* out);
+// gU, gX_N and gp of n_traj trajectories from their partials (RedDesc array; `most`:
+// its largest extents).
+struct RedDesc;
+cis_status prep_adjoint_reduce_batch(const void* rdesc, const RedDesc& most, int n_traj,
+                                     KLaunch* out);
 // Split form of the discretize step (coefficient records, then tangent
 // columns): the two launches of one model group.
 cis_status prep_split_batch(const cis_model* m, int32_t dtype, const BatchGroupDev& g,

@@ -131,29 +131,27 @@ def bench_algorithmic_bytes():
     the tuner tries processes the same group)."""
     from . import synth
 
-    def auto_ckpt(K):   # a plan's default spacing: the largest divisor of K not above 8
-        return max(c for c in range(1, 9) if K % c == 0)
     out = {}
     model, data, K = synth.make_workload("cheetah7_N50_K20")
     N = data["s"].shape[0]
     t = _topo(model)
     out[f"k_discretize<double, {t}"] = N * interval_bytes(model, K, "discretize")
     out[f"k_discretize<float, {t}"] = N * interval_bytes(model, K, "discretize", dsize=4)
-    out[f"k_defects<double, {t}"] = N * interval_bytes(model, K, "defects", C=5)
-    out[f"k_adjoint4<double, {t}"] = N * interval_bytes(model, K, "adjoint", C=5)
-    out[f"k_adjoint<double, {t}"] = N * interval_bytes(model, K, "adjoint", C=5)
+    # (the sweep's last template argument tells the single call, C = 5, from the
+    # batch's, C = 1; the defects passes of this topology share a name)
+    single = t
+    out[f"k_adjoint_pack<{t}, 6, 1, false>, true, 8"] = N * interval_bytes(model, K, "adjoint", C=5)
     groups = {}
     for m_, d, k in synth.mixed_batch():
         groups.setdefault(_topo(m_), []).append((m_, d["s"].shape[0], k))
     for t, items in groups.items():
-        def tot(op, cf=lambda k: 1, items=items):
-            return sum(n * interval_bytes(m_, k, op, C=cf(k)) for m_, n, k in items)
+        def tot(op, items=items):
+            return sum(n * interval_bytes(m_, k, op) for m_, n, k in items)
         out[f"k_discretize_batch<double, {t}"] = tot("discretize")
-        out[f"k_defects_batch<double, {t}"] = tot("defects", auto_ckpt)
-        out[f"k_defects_lane_batch<double, {t}"] = tot("defects", auto_ckpt)
-        out[f"k_adjoint4_batch<double, {t}"] = tot("adjoint", auto_ckpt)
-        out[f"k_adjoint3_batch<double, {t}"] = tot("adjoint", auto_ckpt)
-        out[f"k_adjoint_batch<double, {t}"] = tot("adjoint", auto_ckpt)
+        if t != single:
+            out[f"k_defects_pack<double, {t}"] = tot("defects")
+        for terrain in ("true", "false"):
+            out[f"k_adjoint_pack<{t}, 6, 1, false>, {terrain}, 0"] = tot("adjoint")
     for t, items in groups.items():
         for ds, tn in ((8, "double"), (4, "float")):
             rec = sum(n * split_bytes(m_, ds)[0] for m_, n, k in items)
