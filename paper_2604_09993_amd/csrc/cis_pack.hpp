@@ -114,6 +114,15 @@ __device__ __forceinline__ T row_sum(T v) {
     return v;
 }
 
+// the first N lanes of the row, in their order
+template <int N, class T, int E = 1>
+__device__ __forceinline__ T row_sum_first(T v, T acc) {
+    if constexpr (E < N) return row_sum_first<N, T, E + 1>(v, acc + row_lane<E>(v));
+    else return acc;
+}
+template <int N, class T>
+__device__ __forceinline__ T row_sum_first(T v) { return row_sum_first<N, T>(v, row_lane<0>(v)); }
+
 // A double constant in scalar registers, formed where it is used: as ordinary
 // constants the compiler keeps the 22 coefficients of sin and cos in vector
 // registers across the stage loop (44 of them) and spills others for it.
@@ -203,6 +212,8 @@ struct PackBody {
             return torso ? t : T(0);
         }
     }
+    // FORCES: keep the forces themselves, not their sums (pack_accel)
+    template <bool FORCES = false>
     __device__ __forceinline__ void load(const FwdArgs<T>& a,
                                          const MConst<TP::NB, TP::NJ, TP::NC>& mc, int k,
                                          int lane) {
@@ -257,6 +268,14 @@ struct PackBody {
             for (int q = 0; q < 3; ++q) cm[q] += T(0.5) * w[q];
             ln[n] = w[0];
             ft[n] = w[1] - w[2];
+            if constexpr (FORCES) {
+                P[n] = lx;
+                Q[n] = ly;
+                tq[n] = tau;
+                F[n][0] = w[1];
+                F[n][1] = w[2];
+                continue;
+            }
             F[n][0] = children(lx) - lx;
             F[n][1] = children(ly) - ly;
             P[n] = children(rp[0] * ly - rp[1] * lx) - (rc[0] * ly - rc[1] * lx);
@@ -314,6 +333,9 @@ struct PackShared {
         for (int q = 0; q < 3; ++q) v[slot][q][me] = x[3 + q];
     }
 };
+
+template <class T>
+__device__ __forceinline__ T mul_add(T a, T b, T c) { return __builtin_elementwise_fma(a, b, c); }
 
 // State wave: accelerations f of the stage input xs, derivative kz of the S
 // column's velocity rows at zs, the own-angle coefficient cth and the rotation.
@@ -376,6 +398,83 @@ __device__ __forceinline__ void pack_state(const PackBody<T, TP, FLAT>& c,
     }
 }
 
+// As pack_state from the forces themselves (PackBody::load<true>), the
+// accelerations in a fixed arithmetic: an embedded error estimate is a difference of
+// nearly equal sums, down to their rounding, so which product of a sum is rounded
+// is written out (mul_add) and not left to the compiler.
+template <class T, class TP, bool FLAT>
+__device__ __forceinline__ void pack_accel(const PackBody<T, TP, FLAT>& c,
+                                           const MConst<TP::NB, TP::NJ, TP::NC>& mc,
+                                           const T (&xs)[6], const T (&zs)[6], T tau, T (&f)[3],
+                                           T (&kz)[3], T& cth, T& cb, T& sb) {
+    using C = PackConst<T>;
+    asm volatile("" ::: "memory");   // read the constants in every stage, keep none
+    const T omt = T(1) - tau;
+    auto hold = [&](int q) {
+        const auto v = c.get(q);
+        return mul_add(tau, v.b, omt * v.a);
+    };
+    sincos_pack(xs[2], &sb, &cb);
+    const T thp = c.parent(xs[2]), omp = c.parent(xs[5]);
+    const T sp = c.parent(sb), cp = c.parent(cb);
+    const auto kd = c.get(C::KD);
+    T Fx = T(0), Fy = T(0), Tq = T(0), dT = T(0);
+    T wx = T(0), wy = T(0), wt = T(0), dp = T(0);   // parent-side wrench of the own joint
+    if (c.joint) {
+        const auto jp = c.get(C::RP), jc = c.get(C::RC);
+        const T apx = mul_add(cp, jp.a, -(sp * jp.b)), apy = mul_add(sp, jp.a, cp * jp.b);
+        const T acx = mul_add(cb, jc.a, -(sb * jc.b)), acy = mul_add(cb, jc.b, sb * jc.a);
+        const T tq = hold(C::CTQ), lx = hold(C::CP), ly = hold(C::CQ);
+        const T tt = mul_add(-kd.b, xs[5] - omp, mul_add(-kd.a, xs[2] - thp, tq));
+        Fx -= lx;
+        Fy -= ly;
+        Tq += tt - mul_add(acx, ly, -(acy * lx));
+        wx = lx;
+        wy = ly;
+        wt = mul_add(apx, ly, -(apy * lx)) - tt;
+        dT = acx * lx + acy * ly;
+        dp = apx * lx + apy * ly;
+    }
+    const T si = c.s * c.ii;
+    T fxx = T(0), fyx = T(0), ftx = T(0), ay = T(0);
+    if (c.contact) {
+        const auto cr = c.get(C::RX);
+        const T ax = mul_add(cb, cr.a, -(sb * cr.b));
+        ay = mul_add(cb, cr.b, sb * cr.a);
+        const Frame<T> fr = FLAT ? Frame<T>{xs[1] + ay, T(0), T(1), T(1), T(0), T(0), T(1), T(0), T(0)}
+                                 : terrain<T>(mc, xs[0] + ax, xs[1] + ay);
+        const T ln = hold(C::LN), ft = hold(C::CFX) - hold(C::CFY);
+        const T fx = mul_add(fr.nx, ln, fr.tx * ft), fy = mul_add(fr.ty, ft, fr.ny * ln);
+        Fx += fx;
+        Fy += fy;
+        Tq += mul_add(ax, fy, -(ay * fx));
+        dT -= ax * fx + ay * fy;
+        if constexpr (!FLAT) {
+            const T dfx = fr.dny * ft + fr.dnx * ln, dfy = -fr.dnx * ft + fr.dny * ln;
+            fxx = dfx * (c.s * c.mi);
+            fyx = dfy * (c.s * c.mi);
+            ftx = (ax * dfy - ay * dfx) * si;
+        }
+    }
+    Fx += c.children(wx);
+    Fy += c.children(wy);
+    Tq += c.children(wt);
+    f[0] = Fx * c.mi;
+    f[1] = mul_add(Fy, c.mi, -T(mc.g));
+    f[2] = Tq * c.ii;
+    cth = si * (dT - c.children(dp));
+    if constexpr (!FLAT) cth -= ftx * ay;
+    const T tz = kd.a * (zs[2] - c.parent(zs[2])) + kd.b * (zs[5] - c.parent(zs[5]));
+    kz[0] = f[0];
+    kz[1] = f[1];
+    kz[2] = f[2] + cth * zs[2] + si * (c.children(tz) - tz);
+    if constexpr (!FLAT) {
+        kz[0] += fxx * (zs[0] - ay * zs[2]);
+        kz[1] += fyx * (zs[0] - ay * zs[2]);
+        kz[2] += ftx * zs[0];
+    }
+}
+
 // Coefficient wave: sums over the stages of the coefficients of the integral
 // rows (PackRec::SUM), and the integral rows of the state and of S.
 template <class T, class TP, bool FLAT>
@@ -391,7 +490,8 @@ struct PackSums {
     }
 };
 
-// One stage of the coefficient wave (slot: the state wave's): the integrands cc
+// One stage of the coefficient wave (slot: the state wave's; the integrands in a
+// fixed arithmetic, as pack_accel): the integrands cc
 // and ct, and with COEF the sums and the stage record (all but CTH).
 template <class T, class TP, bool FLAT, bool COEF, int SLOTS>
 __device__ __forceinline__ void pack_coef(const PackBody<T, TP, FLAT>& c,
@@ -412,14 +512,14 @@ __device__ __forceinline__ void pack_coef(const PackBody<T, TP, FLAT>& c,
     const auto cr = c.get(C::RX), jp = c.get(C::RP), jc = c.get(C::RC);
     const auto lb = c.get(C::LB), ls = c.get(C::LS);   // (lnb, ltpb), (ltmb, slack)
     // contact point and frame
-    const T ax = cb * cr.a - sb * cr.b, ay = sb * cr.a + cb * cr.b;
+    const T ax = mul_add(cb, cr.a, -(sb * cr.b)), ay = mul_add(cb, cr.b, sb * cr.a);
     const Frame<T> f = FLAT ? Frame<T>{yb + ay, T(0), T(1), T(1), T(0), T(0), T(1), T(0), T(0)}
                             : terrain<T>(mc, xb + ax, yb + ay);
-    const T Pdx = vx - om * ay, Pdy = vy + om * ax;
+    const T Pdx = mul_add(-om, ay, vx), Pdy = mul_add(om, ax, vy);
     // smooth functions: |h|_s of the own joint, |v_t|_s and ramp_s(-sd) of the contact
-    const T apx = cp * jp.a - sp * jp.b, apy = sp * jp.a + cp * jp.b;
-    const T acx = cb * jc.a - sb * jc.b, acy = sb * jc.a + cb * jc.b;
-    const T vt = FLAT ? Pdx + T(0) * Pdy : f.tx * Pdx + f.ty * Pdy;   // (a NaN of v_y too)
+    const T apx = mul_add(cp, jp.a, -(sp * jp.b)), apy = mul_add(cp, jp.b, sp * jp.a);
+    const T acx = mul_add(cb, jc.a, -(sb * jc.b)), acy = mul_add(cb, jc.b, sb * jc.a);
+    const T vt = FLAT ? Pdx + T(0) * Pdy : mul_add(f.ty, Pdy, f.tx * Pdx);   // (a NaN of v_y too)
     T v0, d0, v1, d1, av, dav, v3, d3;
     sabs_d(xp + apx - xb - acx, v0, d0);
     sabs_d(yp + apy - yb - acy, v1, d1);
@@ -427,7 +527,7 @@ __device__ __forceinline__ void pack_coef(const PackBody<T, TP, FLAT>& c,
     sabs_d(-f.sd, v3, d3);
     const T rp = vt > T(0) ? av : T(0), rm = vt < T(0) ? av : T(0);
     const bool pen = c.contact && -f.sd > T(0);
-    cc = lb.a * f.sd + lb.b * rp + ls.a * rm + ls.b * av;
+    cc = mul_add(ls.b, av, mul_add(ls.a, rm, mul_add(lb.a, f.sd, lb.b * rp)));
     ct = (c.joint ? v0 + v1 : T(0)) + (pen ? v3 : T(0));
     if constexpr (COEF) {
         const T s = c.s, sw = hd.sw, tau = hd.tau;

@@ -145,7 +145,7 @@ __device__ __forceinline__ void rkf_rec_item(const FwdArgs<T>& a,
     const int me = threadIdx.x & 63;
     PackBody<T, TP, FLAT> c;
     c.lc = &sh.lc.v[0][me];
-    c.load(a, mc, k, me & 15);   // both waves store the same constants
+    c.template load<true>(a, mc, k, me & 15);   // both waves store the same constants
     const T s = c.s, Kt = T(a.K), h = T(1) / Kt, sK = s / Kt;
     T* sr = rec + R::HDR;
     __syncthreads();
@@ -164,7 +164,7 @@ __device__ __forceinline__ void rkf_rec_item(const FwdArgs<T>& a,
                 constexpr int I = decltype(i_c)::value;
                 const int slot = (NR * j + I) & 1;
                 T f[3], kz[3], cth, cb, sb;
-                pack_state<T, TP, FLAT>(c, mc, xs, zs, quotient(jt + CIS_TAB(RKF::c(I)), Kt, h), f, kz,
+                pack_accel<T, TP, FLAT>(c, mc, xs, zs, quotient(jt + CIS_TAB(RKF::c(I)), Kt, h), f, kz,
                                         cth, cb, sb);
                 sh.put(slot, me, xs, cb, sb);
 #pragma unroll
@@ -185,7 +185,7 @@ __device__ __forceinline__ void rkf_rec_item(const FwdArgs<T>& a,
                     // sixth stage (estimate only), then the step's end
                     T x6[6], f6[3], kz6[3], cth6, c6, s6;
                     next_input<I>(kd, xb, h, x6);
-                    pack_state<T, TP, FLAT>(c, mc, x6, zs, quotient(jt + CIS_TAB(RKF::c(5)), Kt, h), f6,
+                    pack_accel<T, TP, FLAT>(c, mc, x6, zs, quotient(jt + CIS_TAB(RKF::c(5)), Kt, h), f6,
                                             kz6, cth6, c6, s6);
                     sh.put(2, me, x6, c6, s6);
                     T ev[6], xn[6], zn[6];
@@ -281,7 +281,7 @@ __device__ __forceinline__ void rkf_rec_item(const FwdArgs<T>& a,
             // estimate: the cross-complementarity rows on their lanes, the
             // violation row from the body lanes' parts
             if (c.contact) emax = fmax(emax, fabs(h * yec));
-            emax = fmax(emax, fabs(h * row_sum(yet)));
+            emax = fmax(emax, fabs(h * row_sum_first<TP::NB>(yet)));
         }
         __syncthreads();
         const T angles = row_sum(sh.fin[me]);
@@ -410,7 +410,7 @@ __device__ __forceinline__ void rkf_tangent_item(const T* __restrict__ rec, T* l
     yct = (yt[0] + yt[1]) + (yt[2] + yt[3]);
 }
 
-// quad13, 3,201 intervals, K = 20: 220 us at two waves per SIMD (108 bytes of
+// quad13, 3,201 intervals, K = 20: 250 us at two waves per SIMD (some scratch, 20 to 200 bytes of
 // scratch per lane), 280 us at one; one interval per workgroup 1,130 us.
 template <class T, class TP, bool FLAT>
 __global__ void __launch_bounds__(128)
