@@ -152,6 +152,19 @@ struct BodyRK {
     T xb[6], xa[6], xs[6];
 };
 
+// 1 / sqrt(w), w >= 1.  FP64: the hardware estimate and two steps on the residual
+// 1 - w y^2 (a square root and a division are some 40 instructions in one chain).
+__device__ __forceinline__ float rsqrt_t(float w) { return 1.0f / sqrt_t(w); }
+__device__ __forceinline__ double rsqrt_t(double w) {
+    double y = __builtin_amdgcn_rsq(w);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double e = fma(-(w * y), y, 1.0);
+        y = fma(y * e, fma(0.375, e, 0.5), y);
+    }
+    return y;
+}
+
 // Terrain frame at the contact point (flat ground when A == 0).
 template <class T>
 struct Frame {
@@ -178,8 +191,7 @@ __device__ __forceinline__ Frame<T> terrain(const MC& mc, T Px, T Py) {
         const T H = Py - A * sw;
         const T Hx = -A * kap * cw;
         const T Hxx = A * kap * kap * sw;
-        const T G = sqrt_t(T(1) + Hx * Hx);
-        const T rG = T(1) / G;
+        const T rG = rsqrt_t(T(1) + Hx * Hx);
         const T rG3 = rG * rG * rG;
         f.sd = H * rG;
         f.nx = Hx * rG;

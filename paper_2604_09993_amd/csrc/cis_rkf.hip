@@ -410,11 +410,13 @@ __device__ __forceinline__ void rkf_tangent_item(const T* __restrict__ rec, T* l
     yct = (yt[0] + yt[1]) + (yt[2] + yt[3]);
 }
 
-// quad13, 3,201 intervals, K = 20: 250 us at two waves per SIMD (some scratch, 20 to 200 bytes of
-// scratch per lane), 280 us at one; one interval per workgroup 1,130 us.
+// Two waves per SIMD on flat ground (quad13, 3,201 intervals, K = 20: 250 us with 68
+// bytes of scratch per lane, 280 us at one; one interval per workgroup 1,130 us).
+// The sinusoid's frame holds more: one (biped5 on it, up to 400 intervals: 240 us
+// against 345 with 272 bytes of scratch).
 template <class T, class TP, bool FLAT>
 __global__ void __launch_bounds__(128)
-    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3)))
+    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? (FLAT ? 2 : 1) : 3)))
     k_rkf_rec(ItemList<T> l, MConst<TP::NB, TP::NJ, TP::NC> mc, T* __restrict__ err) {
     __shared__ PackShared<T, 3> sh;
     red_record_block<T, TP, FLAT>(l, [&](const FwdArgs<T>& a, int item, bool on, int) {
