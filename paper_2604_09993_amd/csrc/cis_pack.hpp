@@ -181,43 +181,13 @@ struct PackConst {
     Pair v[N][64];
 };
 
-// Body lane of one of the wave's four intervals: lane & 15 is the body.
-template <class T, class TP, bool FLAT>
-struct PackBody {
+// Body lane of one of the wave's four intervals (lane & 15 is the body) and its
+// place in the tree.
+template <class T, class TP>
+struct PackTree {
     int b, p, j, i;
     bool body, joint, contact, pt, torso, inner;   // inner: its child is the next lane
-    T mi, ii, s, mu, ipar;   // ipar: 1/I of the parent
-    // LDS, pairs: hold values at the two nodes of the joint force on the body, of
-    // the moment terms P = sum r x lambda, Q = sum r . lambda in body axes (signed
-    // by side; with the contact force on flat ground) and of the joint torque;
-    // joint anchors, contact point, stiffness and damping; contact force (n, t) at
-    // the nodes and its hold means (n, t+), (t-, friction slack)
-    typename PackConst<T>::Pair* lc;
-    __device__ __forceinline__ typename PackConst<T>::Pair get(int q) const { return lc[64 * q]; }
-
-    __device__ __forceinline__ T parent(T v) const {
-        const T t = row_lane<0>(v);
-        const T q = prev_lane(v);
-        return pt ? t : q;
-    }
-    // sum over the children of a value held by the child lanes
-    __device__ __forceinline__ T children(T v) const {
-        constexpr int D = TP::D;
-        const T t = row_sum_of<TP::L, 1, 1 + (TP::L > 1) * D, 1 + (TP::L > 2) * 2 * D,
-                               1 + (TP::L > 3) * 3 * D>(v);
-        if constexpr (TP::D > 1) {
-            const T q = next_lane(v);
-            return torso ? t : (inner ? q : T(0));
-        } else {
-            return torso ? t : T(0);
-        }
-    }
-    // FORCES: keep the forces themselves, not their sums (pack_accel)
-    template <bool FORCES = false>
-    __device__ __forceinline__ void load(const FwdArgs<T>& a,
-                                         const MConst<TP::NB, TP::NJ, TP::NC>& mc, int k,
-                                         int lane) {
-        constexpr int NJ = TP::NJ;
+    __device__ __forceinline__ void place(int lane) {
         body = lane < TP::NB;
         b = body ? lane : 0;
         joint = b >= 1;
@@ -228,6 +198,61 @@ struct PackBody {
         p = pt ? 0 : j;
         torso = b == 0;
         inner = joint && !contact;
+    }
+    __device__ __forceinline__ T parent(T v) const {
+        const T t = row_lane<0>(v);
+        const T q = prev_lane(v);
+        return pt ? t : q;
+    }
+    // sum over the legs of a value held by their first links
+    static __device__ __forceinline__ T legs(T v) {
+        constexpr int D = TP::D;
+        return row_sum_of<TP::L, 1, 1 + (TP::L > 1) * D, 1 + (TP::L > 2) * 2 * D,
+                          1 + (TP::L > 3) * 3 * D>(v);
+    }
+    // sum over the children of a value held by the child lanes
+    __device__ __forceinline__ T children(T v) const {
+        const T t = legs(v);
+        if constexpr (TP::D > 1) {
+            const T q = next_lane(v);
+            return torso ? t : (inner ? q : T(0));
+        } else {
+            return torso ? t : T(0);
+        }
+    }
+};
+
+template <class T, class TP, bool FLAT>
+struct PackBody : PackTree<T, TP> {
+    using Tree = PackTree<T, TP>;
+    using Tree::b;
+    using Tree::p;
+    using Tree::j;
+    using Tree::i;
+    using Tree::body;
+    using Tree::joint;
+    using Tree::contact;
+    using Tree::pt;
+    using Tree::torso;
+    using Tree::inner;
+    using Tree::parent;
+    using Tree::children;
+    T mi, ii, s, mu, ipar;   // ipar: 1/I of the parent
+    // LDS, pairs: hold values at the two nodes of the joint force on the body, of
+    // the moment terms P = sum r x lambda, Q = sum r . lambda in body axes (signed
+    // by side; with the contact force on flat ground) and of the joint torque;
+    // joint anchors, contact point, stiffness and damping; contact force (n, t) at
+    // the nodes and its hold means (n, t+), (t-, friction slack)
+    typename PackConst<T>::Pair* lc;
+    __device__ __forceinline__ typename PackConst<T>::Pair get(int q) const { return lc[64 * q]; }
+
+    // FORCES: keep the forces themselves, not their sums (pack_accel)
+    template <bool FORCES = false>
+    __device__ __forceinline__ void load(const FwdArgs<T>& a,
+                                         const MConst<TP::NB, TP::NJ, TP::NC>& mc, int k,
+                                         int lane) {
+        constexpr int NJ = TP::NJ;
+        Tree::place(lane);
         const int64_t ld = a.ldn;
         s = a.s[k];
         mu = a.prm[0];

@@ -7,24 +7,26 @@
 // Classical RK4 with K substeps and the variational equations through the same
 // stages (Sec. IV-B, Sec. VI), FP64.
 //
-// With M v' = W + J^T R phi + grad h^T lambda and grad h v' + c = 0
-// (c_j = -w_p^2 a_p + w_c^2 a_c), the joint forces solve A lambda =
-// -(grad h M^-1 (W + J^T R phi) + c), A = grad h M^-1 grad h^T.  For a
-// direction z of the state (or of the controls) the acceleration moves by
-//     dv' = M^-1 u - Wm b,   Wm = M^-1 grad h^T A^-1,
-//     u = dF + dgrad_h^T lambda,   b = grad h M^-1 u + dgrad_h v' + dc,
-// where u and b are local: u on the bodies z touches and their joint
-// neighbours, b on the joints at those bodies.  Two kernels:
-//   k_paper_rec : one wave per interval; the nominal RK4 on body lanes, and
-//                 per stage the values, A and its Gauss-Jordan elimination in
-//                 registers (one lane per column of [A | grad h M^-1 | r]),
-//                 which leave Wm and lambda; a stage record to device memory;
-//   k_paper_tan : per (interval, block of 64 columns of [Phi_x | B- | B+ | S])
-//                 one wave per leg, a lane holding its column on the torso and
-//                 leg rows; per stage u on those rows (the torso's hip terms
-//                 of the other legs through LDS), b on the leg's joints (all
-//                 joints through LDS), then dv' with the record's Wm rows read
-//                 by scalar loads.
+// The joint forces are eliminated leg by leg instead of through A = grad h M^-1 grad
+// h^T: the joint rows grad h v' + c = 0 give every link's translation from the
+// torso's acceleration a0 = (v'_0, w'_0) and the angular accelerations of its leg,
+//     v'_l = v'_0 + w'_0 E a_p1 + sum_{i<=l} (gamma_i + w'_i E r_li),
+//     r_li = a_p,i+1 - a_c,i (i < l),  r_ll = -a_c,l,  E a = (-a_y, a_x),
+//     gamma_i = -w_p^2 a_p + w_c^2 a_c,
+// and virtual work along the w'_i leaves, per leg, H w' = f - H0 a0 (H symmetric, as
+// many rows as the leg has links) and a 3 x 3 system of the torso,
+//     w' = H^-1 f - G a0,  G = H^-1 H0,  (M0 + sum_legs (M_leg - H0^T G)) a0 = ... .
+// A direction of the state or of the controls moves v' by the same elimination
+// with perturbed forces u = dF + dgrad_h^T lambda and joint terms d = dgrad_h v' +
+// dc in the place of F and gamma.  Two kernels:
+//   k_paper_rec : four intervals per wave on rows of 16 body lanes; the nominal RK4,
+//                 and per stage and leg the coefficients of u, d, H^-1, G and the
+//                 torso's inverse to device memory;
+//   k_paper_tan : per (interval, block of 64 columns of [Phi_x | B- | B+ | S]) one
+//                 wave per leg, a lane holding its column on the torso and leg
+//                 rows; the stage's coefficients as vectors of 16 that enter the
+//                 FMAs as DPP broadcasts; one exchange of three values between
+//                 the legs per stage (the torso's system).
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -35,6 +37,8 @@
 #include "cis_host.hpp"
 #include "cis_launch.hpp"
 #include "cis_model.hpp"
+#include "cis_pack.hpp"
+#include "cis_reduced.hpp"
 
 namespace cis {
 
@@ -45,49 +49,37 @@ struct PTopo {
     static constexpr int NQ = 3 * NB, N6 = 6 * NB;
     static constexpr int NY = 4 * NC + 1, NX = N6 + NY;   // augmented state
     static constexpr int M = NJ + 3 * NC, P = NB + 2;
-    static constexpr int NJ2 = 2 * NJ, LB = D + 1;
+    static constexpr int LB = D + 1;
     static constexpr int NCOL = N6 + 2 * M + 1;            // [Phi_x | B- | B+ | S]
     static constexpr int NBLK = (NCOL + 63) / 64;
-    static_assert(NJ2 + NQ + 1 <= 64, "one lane per column of the augmented system");
+    static_assert(NB <= 16, "the bodies fit one DPP row");
     __host__ __device__ static constexpr int parent(int j) { return (j % D == 0) ? 0 : j; }
     __host__ __device__ static constexpr int cbody(int i) { return D * (i + 1); }
 };
 
-// Layout of an interval's record area (doubles):
-//   header [HDR]: s, h, h/6, 0 x5, then 1/m, 1/m, 1/I per body, then (k_j, d_j)
-//   stage t < 4 K at HDR + t * STAGE:
-//     WM   [NQ][NJ2]  Wm = M^-1 grad h^T A^-1
-//     BODY [NB][6]    v (stage input), v'
-//     JNT  [NJ][6]    a_p, a_c (world), lambda
-//     CON  [NC][CN]   contact terms (offsets C_*)
-//     CT   [8]        violation integrand value
+// Layout of an interval's record area (doubles): header [HDR]: s, h, 0 x6, the masses,
+// then (k_j, d_j); stage t < 4 K, leg l at HDR + (t L + l) LEG, as vectors of 16:
+//   joint of link l at JN (l - 1): arms a_p, a_c, then d by th_p, th_c, w_p, w_c (x, y
+//   each), a_p . lambda, a_c . lambda
+//   HI: H^-1 (lower triangle); G [D][3]; SI: the torso's inverse (upper triangle)
+//   CO: the contact: force and torque by its x and theta, by the controls phi_t and
+//   phi_n, d lambda_c by x, theta, w, d violation by x, y, theta, and the controls'
+//   integrand partials
+//   SF: forcing of S: v and v' of the torso and the links, the integrands
 template <class TP>
 struct PRec {
-    static constexpr int CN = 32;
-    static constexpr int HDR = (8 + TP::NQ + 2 * TP::NJ + 7) / 8 * 8;
-    static constexpr int WM = 0;
-    static constexpr int BODY = WM + TP::NQ * TP::NJ2;
-    static constexpr int JNT = BODY + 6 * TP::NB;
-    static constexpr int CON = JNT + 6 * TP::NJ;
-    static constexpr int CT = CON + CN * TP::NC;
-    static constexpr int STAGE = (CT + 8 + 7) / 8 * 8;
+    static constexpr int D = TP::D;
+    static constexpr int HDR = (8 + TP::NB + 2 * TP::NJ + 7) / 8 * 8;
+    static constexpr int JN = 14, HI = JN * D, G = HI + D * (D + 1) / 2, SI = G + 3 * D;
+    static constexpr int CO = SI + 6;
+    enum { FXX = CO, FXT, FYX, FYT, TQX, TQT, CTX, CNX, CTY, CNY, CTT, CTN, LX, LT, LW, SX, SY, ST,
+           LCT, LCG, RCN, RCT, VN, VT, VG, SF };
+    static constexpr int YF = SF + 6 * (D + 1), NSC = YF + 5, NV = (NSC + 15) / 16;
+    static constexpr int LEG = 16 * NV, STAGE = TP::L * LEG;
+    __host__ __device__ static constexpr int hi(int i, int k) {   // i >= k
+        return HI + i * (i + 1) / 2 + k;
+    }
     static constexpr int64_t per_interval(int K) { return HDR + (int64_t)4 * K * STAGE; }
-};
-// contact slots: arm a, tangent t, normal n, dt/dPx, dn/dPx, grad sd, force F,
-// contact-point velocity J v, integrands (phi_n, lambda_c, gamma, rho_c), and
-// the control partials of the integrands
-enum {
-    P_AX = 0, P_AY, P_TX, P_TY, P_NX, P_NY, P_DTX, P_DTY, P_DNX, P_DNY, P_GSX, P_GSY, P_FX, P_FY,
-    P_JVX, P_JVY, P_OPN, P_OLC, P_OGM, P_ORC,
-    P_LCT,   // d lambda_c / d phi_t = gamma / (phi_t^2 + 1)^(3/2)
-    P_LCG,   // d lambda_c / d gamma = phi_t / sqrt(phi_t^2 + 1)
-    P_RCN,   // d rho_c / d phi_n
-    P_RCT,   // d rho_c / d phi_t
-    P_CCN,   // d ramp_s(-phi_n) / d phi_n
-    P_CCG,   // d ramp_s(-gamma) / d gamma
-    P_CCR,   // d ramp_s(-rho_c) / d rho_c
-    P_CCS,   // d ramp_s(-sd) / d sd
-    P_PT, P_PN
 };
 
 struct PaperArgs {
@@ -106,334 +98,419 @@ struct PaperArgs {
     int N, K;
 };
 
-__device__ __forceinline__ double pbcast(double v, int src) {
-    const int2 w = __builtin_bit_cast(int2, v);
-    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(w.x, src),
-                                                __builtin_amdgcn_readlane(w.y, src)));
-}
 __device__ __forceinline__ void plds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
-// |a|_s = sqrt(a^2+1) - 1 and its slope; ramp_s and its slope
-__device__ __forceinline__ double psabs(double a) { return a * a / (sqrt(a * a + 1.0) + 1.0); }
-__device__ __forceinline__ double pdsabs(double a) { return a / sqrt(a * a + 1.0); }
-__device__ __forceinline__ double psramp(double a) { return a > 0.0 ? psabs(a) : 0.0; }
-__device__ __forceinline__ double pdsramp(double a) { return a > 0.0 ? pdsabs(a) : 0.0; }
-
 template <class TP>
 struct PShared {
-    double x0[TP::NX], xk1[TP::NX];
-    double uk[TP::M], uk1[TP::M];
-    double prm[TP::P];
-    double minv[TP::NQ];
-    double xs[TP::N6];                 // stage input (q, v)
-    double cs[TP::NB][2];
-    double arm[TP::NJ][4];
-    double tt[TP::NJ];                 // joint torque + spring-damper torque
-    double cw[TP::NC][3];              // contact wrench on the contact body
-    double W[TP::NQ];                  // generalized force
-    double cv[TP::NJ2];                // velocity-product term c
-    double lam[TP::NJ2];
-    double vd[TP::NQ];                 // v'
-    double om[TP::NY];                 // Omega at the stage
+    enum { RX, RY, SX, SY, HD, F, AX, AY, N };   // a link's part of its leg's system
+    double g[N][64];
 };
 
+// a <- a^-1 (symmetric positive definite, without pivoting)
+template <int N>
+__device__ __forceinline__ void spd_inverse(double (&a)[N][N]) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const double p = 1.0 / a[k][k];
+        a[k][k] = p;
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            if (j != k) a[k][j] *= p;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if (i == k) continue;
+            const double t = a[i][k];
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+                if (j != k) a[i][j] = fma(-t, a[k][j], a[i][j]);
+            a[i][k] = -t * p;
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
-// k_paper_rec: interval k, one wave.
+// k_paper_rec: four intervals, one wave, lane & 15 the body.  Sums along a leg run
+// by lane shifts (links of a leg are consecutive lanes); every lane then forms its
+// leg's system from the links' parts in LDS, and the torso's from the legs' sums.
+// Bound by the serial chain of a stage (two sines, nine root estimates, six divisions,
+// eight shift sums), 3.4 us of it.  1,603 quad13 intervals, K = 20: 270 us; one interval
+// per wave with a 24 x 24 Gauss-Jordan elimination took 1,650 us.
 // ---------------------------------------------------------------------------
 template <class TP>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1)))
     k_paper_rec(PaperArgs a, MConst<TP::NB, TP::NJ, TP::NC> mc) {
-    constexpr int NB = TP::NB, NJ = TP::NJ, NC = TP::NC, NQ = TP::NQ, N6 = TP::N6;
-    constexpr int NX = TP::NX, NY = TP::NY, M = TP::M, NJ2 = TP::NJ2;
+    constexpr int NJ = TP::NJ, NC = TP::NC, NQ = TP::NQ, N6 = TP::N6;
+    constexpr int NX = TP::NX, NY = TP::NY, D = TP::D;
     using R = PRec<TP>;
-    __shared__ PShared<TP> sh;
-    const int lane = threadIdx.x;
-    const int k = xcd_slot(blockIdx.x, gridDim.x);
+    using SH = PShared<TP>;
+    __shared__ SH sh;
+    const int me = threadIdx.x;
+    const int want = 4 * xcd_slot(blockIdx.x, gridDim.x) + (me >> 4);
+    const bool on = want < a.N;   // spare rows repeat the last interval
+    const int k = on ? want : a.N - 1;
     const int64_t ldn = a.ldn, ldi = a.ldi;
     double* rec = a.rec + (int64_t)k * R::per_interval(a.K);
-    for (int e = lane; e < NX; e += 64) {
-        sh.x0[e] = a.X[e * ldn + k];
-        sh.xk1[e] = a.X[e * ldn + k + 1];
-    }
-    for (int e = lane; e < M; e += 64) {
-        sh.uk[e] = a.U[e * ldn + k];
-        sh.uk1[e] = a.U[e * ldn + k + 1];
-    }
-    if (lane < TP::P) sh.prm[lane] = a.prm[lane];
-    plds_sync();
-    if (lane < NB) {
-        const double m = sh.prm[2 + lane];
-        sh.minv[3 * lane] = 1.0 / m;
-        sh.minv[3 * lane + 1] = 1.0 / m;
-        sh.minv[3 * lane + 2] = 1.0 / (m * mc.ipm[lane]);
-    }
-    plds_sync();
-    const double s = a.s[k], h = 1.0 / double(a.K), mu = sh.prm[0];
-    // header
-    for (int e = lane; e < R::HDR; e += 64) {
-        double v = 0.0;
-        if (e == 0) v = s;
-        else if (e == 1) v = h;
-        else if (e == 2) v = h / 6.0;
-        else if (e >= 8 && e < 8 + NQ) v = sh.minv[e - 8];
-        else if (e >= 8 + NQ && e < 8 + NQ + 2 * NJ) {
-            const int j = (e - 8 - NQ) >> 1;
-            v = ((e - 8 - NQ) & 1) ? mc.ds[j] : mc.ks[j];
+    PackTree<double, TP> c;
+    c.place(me & 15);
+    const bool body = on && c.body;
+    const int leg = c.joint ? c.j / D : 0, lk = c.joint ? c.j % D : 0;
+    const bool first = c.joint && lk == 0;
+    const int leg0 = (me & 48) + 1 + leg * D;   // lane of the leg's first link
+    const double s = a.s[k], h = 1.0 / double(a.K), mu = a.prm[0];
+    const double m = a.prm[2 + c.b], I = m * mc.ipm[c.b];
+    double rp[2] = {0.0, 0.0}, rc[2] = {0.0, 0.0}, ks = 0.0, ds = 0.0, cr[2] = {0.0, 0.0};
+    double tq[2] = {0.0, 0.0}, cu[3][2];
+    if (c.joint) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            rp[e] = mc.rp[c.j][e];
+            rc[e] = mc.rc[c.j][e];
+            tq[e] = a.U[c.j * ldn + k + e];
         }
-        rec[e] = v;
-    }
-    // nominal RK4 on body lanes: rows (q_b, v_b); integral rows on lanes < NY
-    const int bl = lane < NB ? lane : 0;
-    double xb[6], xa[6], xsl[6];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        xb[q] = sh.x0[3 * bl + q];
-        xb[3 + q] = sh.x0[NQ + 3 * bl + q];
+        ks = mc.ks[c.j];
+        ds = mc.ds[c.j];
     }
 #pragma unroll
-    for (int q = 0; q < 6; ++q) xsl[q] = xb[q];
-    double yb = lane < NY ? sh.x0[N6 + lane] : 0.0, ya = 0.0;
-    for (int t = 0; t < 4 * a.K; ++t) {
-        const int st = t & 3, j = t >> 2;
-        const double tau = (double(j) + (st == 0 ? 0.0 : (st == 3 ? 1.0 : 0.5))) * h;
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+            cu[q][e] = c.contact ? a.U[(NJ + 3 * c.i + q) * ldn + k + e] : 0.0;
+    if (c.contact) {
+        cr[0] = mc.cr[c.i][0];
+        cr[1] = mc.cr[c.i][1];
+    }
+    // sums over a leg: up to and with the own link from the torso, and from the tip
+    auto from_torso = [&](double v) {
+        double t = v;
+#pragma unroll
+        for (int e = 1; e < D; ++e) {
+            const double q = prev_lane(t);
+            t = first ? v : v + q;
+        }
+        return t;
+    };
+    auto beyond = [&](double v) {   // without the own link
+        double t = 0.0;
+#pragma unroll
+        for (int e = 1; e < D; ++e) {
+            const double q = next_lane(t + v);
+            t = c.inner ? q : 0.0;
+        }
+        return t;
+    };
+    const double msub = beyond(m), mleg = msub + m;   // mleg: on first links
+    const double m0 = row_lane<0>(m), I0 = row_lane<0>(I);
+    if (body) {
+        if (c.torso) {
+            rec[0] = s;
+            rec[1] = h;
+        }
+        rec[8 + c.b] = m;
+        if (c.joint) {
+            rec[8 + TP::NB + 2 * c.j] = ks;
+            rec[8 + TP::NB + 2 * c.j + 1] = ds;
+        }
+    }
+    auto row = [&](int q) { return q < 3 ? 3 * c.b + q : NQ + 3 * c.b + q - 3; };
+    double xb[6], xa[6], xs[6], yb[4], ya[4], vb = 0.0, va = 0.0;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) xs[q] = xb[q] = a.X[row(q) * ldn + k];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) yb[q] = c.contact ? a.X[(N6 + 4 * c.i + q) * ldn + k] : 0.0;
+    vb = a.X[(N6 + 4 * NC) * ldn + k];
+    double* sr = rec + R::HDR;
+    for (int t = 0; t < 4 * a.K; ++t, sr += R::STAGE) {
+        const int st = t & 3;
+        const double tau = (double(t >> 2) + (st == 0 ? 0.0 : (st == 3 ? 1.0 : 0.5))) * h;
         const double omt = 1.0 - tau;
-        double* sr = rec + R::HDR + (int64_t)t * R::STAGE;
-        // ---- stage input and rotations ----
-        if (lane < NB) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                sh.xs[3 * lane + q] = xsl[q];
-                sh.xs[NQ + 3 * lane + q] = xsl[3 + q];
-            }
-            double sn, cn;
-            sincos_t(xsl[2], &sn, &cn);
-            sh.cs[lane][0] = cn;
-            sh.cs[lane][1] = sn;
-        }
-        plds_sync();
-        const double* qs = sh.xs;
-        const double* vs = sh.xs + NQ;
-        // ---- joint arms, torques, velocity products; contact terms ----
-        if (lane < NJ) {
-            const int p = TP::parent(lane), c = lane + 1;
-            const double cp = sh.cs[p][0], sp = sh.cs[p][1], cc = sh.cs[c][0], sc = sh.cs[c][1];
-            const double apx = cp * mc.rp[lane][0] - sp * mc.rp[lane][1];
-            const double apy = sp * mc.rp[lane][0] + cp * mc.rp[lane][1];
-            const double acx = cc * mc.rc[lane][0] - sc * mc.rc[lane][1];
-            const double acy = sc * mc.rc[lane][0] + cc * mc.rc[lane][1];
-            sh.arm[lane][0] = apx;
-            sh.arm[lane][1] = apy;
-            sh.arm[lane][2] = acx;
-            sh.arm[lane][3] = acy;
-            const double tq = omt * sh.uk[lane] + tau * sh.uk1[lane];
-            sh.tt[lane] = tq - mc.ks[lane] * (qs[3 * c + 2] - qs[3 * p + 2]) -
-                          mc.ds[lane] * (vs[3 * c + 2] - vs[3 * p + 2]);
-            const double wp = vs[3 * p + 2], wc = vs[3 * c + 2];
-            sh.cv[2 * lane] = -wp * wp * apx + wc * wc * acx;
-            sh.cv[2 * lane + 1] = -wp * wp * apy + wc * wc * acy;
-        }
-        double ctcs_part = 0.0;
-        if (lane >= 32 && lane < 32 + NC) {
-            const int i = lane - 32, b = TP::cbody(i);
-            const double cb = sh.cs[b][0], sb = sh.cs[b][1];
-            const double ax = cb * mc.cr[i][0] - sb * mc.cr[i][1];
-            const double ay = sb * mc.cr[i][0] + cb * mc.cr[i][1];
-            const double Px = qs[3 * b] + ax, Py = qs[3 * b + 1] + ay;
+        double* lr = sr + leg * R::LEG;
+        auto put = [&](int q, double v) { lr[q] = v; };
+        const double om = xs[5], omp = c.parent(om);
+        double cb, sb;
+        sincos_pack(xs[2], &sb, &cb);
+        const double cp = c.parent(cb), sp = c.parent(sb);
+        // joint: arms, torque, velocity products (zero without one)
+        const double apx = cp * rp[0] - sp * rp[1], apy = sp * rp[0] + cp * rp[1];
+        const double acx = cb * rc[0] - sb * rc[1], acy = sb * rc[0] + cb * rc[1];
+        const double thp = c.parent(xs[2]);
+        const double tt = c.joint ? (omt * tq[0] + tau * tq[1]) - ks * (xs[2] - thp) - ds * (om - omp)
+                                  : 0.0;
+        const double wp2 = omp * omp, wc2 = om * om;
+        const double gx = c.joint ? wc2 * acx - wp2 * apx : 0.0;
+        const double gy = c.joint ? wc2 * acy - wp2 * apy : 0.0;
+        double Fx = 0.0, Fy = -m * mc.g, T = tt - c.children(tt);
+        double io[4] = {0.0, 0.0, 0.0, 0.0}, viol = 0.0;
+        if (c.contact) {
+            const double ax = cb * cr[0] - sb * cr[1], ay = sb * cr[0] + cb * cr[1];
+            const double Px = xs[0] + ax, Py = xs[1] + ay;
             // terrain frame (Sec. II; sd = H / ||grad H||, Sec. VI-B) and its x-derivative
             double sw, cw;
-            sincos_t(mc.kappa * Px, &sw, &cw);
+            sincos_pack(mc.kappa * Px, &sw, &cw);
             const double H = Py - mc.A * sw;
             const double Hx = -mc.A * mc.kappa * cw;
             const double Hxx = mc.A * mc.kappa * mc.kappa * sw;
-            const double G = sqrt(1.0 + Hx * Hx), rG = 1.0 / G, rG3 = rG * rG * rG;
+            const double rG = rsqrt_t(1.0 + Hx * Hx), rG3 = rG * rG * rG;
             const double sd = H * rG;
             const double nx = Hx * rG, ny = rG;
             const double dnx = Hxx * rG3, dny = -Hx * Hxx * rG3;
             const double tx = ny, ty = -nx, dtx = dny, dty = -dnx;
             const double gsx = Hx * rG - H * Hx * Hxx * rG3, gsy = rG;
-            const int u0 = NJ + 3 * i;
-            const double pt = omt * sh.uk[u0] + tau * sh.uk1[u0];
-            const double pn = omt * sh.uk[u0 + 1] + tau * sh.uk1[u0 + 1];
-            const double gm = omt * sh.uk[u0 + 2] + tau * sh.uk1[u0 + 2];
-            const double Fx = tx * pt + nx * pn, Fy = ty * pt + ny * pn;
-            sh.cw[i][0] = Fx;
-            sh.cw[i][1] = Fy;
-            sh.cw[i][2] = ax * Fy - ay * Fx;
-            const double om = vs[3 * b + 2];
-            const double jvx = vs[3 * b] - om * ay, jvy = vs[3 * b + 1] + om * ax;
-            const double r1 = sqrt(pt * pt + 1.0);
-            const double lc = tx * jvx + ty * jvy + gm * pt / r1;
-            const double rc = psabs(mu * pn) - psabs(pt);
-            sh.om[4 * i] = pn;
-            sh.om[4 * i + 1] = lc;
-            sh.om[4 * i + 2] = gm;
-            sh.om[4 * i + 3] = rc;
-            ctcs_part = psramp(-pn) + psramp(-sd) + psramp(-gm) + psramp(-rc);
-            double* cr = sr + R::CON + R::CN * i;
-            const double vals[R::CN] = {ax, ay, tx, ty, nx, ny, dtx, dty, dnx, dny, gsx, gsy, Fx, Fy,
-                                        jvx, jvy, pn, lc, gm, rc,
-                                        gm / (r1 * r1 * r1), pt / r1, mu * pdsabs(mu * pn),
-                                        -pdsabs(pt), -pdsramp(-pn), -pdsramp(-gm), -pdsramp(-rc),
-                                        -pdsramp(-sd), pt, pn, 0.0, 0.0};
+            const double pt = omt * cu[0][0] + tau * cu[0][1];
+            const double pn = omt * cu[1][0] + tau * cu[1][1];
+            const double gm = omt * cu[2][0] + tau * cu[2][1];
+            const double cfx = tx * pt + nx * pn, cfy = ty * pt + ny * pn;
+            Fx += cfx;
+            Fy += cfy;
+            T += ax * cfy - ay * cfx;
+            const double jvx = xs[3] - om * ay, jvy = xs[4] + om * ax;
+            // smooth functions and slopes (a ramp is its |.|_s, or zero)
+            double vn, dn, vt, dt, v1, d1, v2, d2, v3, d3, v4, d4;
+            sabs_d(mu * pn, vn, dn);
+            sabs_d(pt, vt, dt);
+            const double y1 = rsqrt_t(pt * pt + 1.0);
+            const double lc = tx * jvx + ty * jvy + gm * dt;
+            const double rr = vn - vt;
+            sabs_d(-pn, v1, d1);
+            sabs_d(-sd, v2, d2);
+            sabs_d(-gm, v3, d3);
+            sabs_d(-rr, v4, d4);
+            auto ramp = [](double arg, double v) { return arg > 0.0 ? v : 0.0; };
+            io[0] = pn;
+            io[1] = lc;
+            io[2] = gm;
+            io[3] = rr;
+            viol = ramp(-pn, v1) + ramp(-sd, v2) + ramp(-gm, v3) + ramp(-rr, v4);
+            if (body) {
+                const double fxx = dtx * pt + dnx * pn, fyx = dty * pt + dny * pn;
+                const double tqx = ax * fyx - ay * fxx;
+                put(R::FXX, fxx);
+                put(R::FXT, -fxx * ay);
+                put(R::FYX, fyx);
+                put(R::FYT, -fyx * ay);
+                put(R::TQX, tqx);
+                put(R::TQT, -(ax * cfx + ay * cfy) - tqx * ay);
+                put(R::CTX, tx);
+                put(R::CNX, nx);
+                put(R::CTY, ty);
+                put(R::CNY, ny);
+                put(R::CTT, ax * ty - ay * tx);
+                put(R::CTN, ax * ny - ay * nx);
+                const double lx = dtx * jvx + dty * jvy;
+                put(R::LX, lx);
+                put(R::LT, -lx * ay - om * (tx * ax + ty * ay));
+                put(R::LW, ty * ax - tx * ay);
+                const double ccs = -ramp(-sd, d2);
+                put(R::SX, ccs * gsx);
+                put(R::SY, ccs * gsy);
+                put(R::ST, ccs * (gsy * ax - gsx * ay));
+                const double rcn = mu * dn, rct = -dt, ccr = -ramp(-rr, d4);
+                put(R::LCT, gm * (y1 * y1 * y1));
+                put(R::LCG, dt);
+                put(R::RCN, rcn);
+                put(R::RCT, rct);
+                put(R::VN, ccr * rcn - ramp(-pn, d1));
+                put(R::VT, ccr * rct);
+                put(R::VG, -ramp(-gm, d3));
 #pragma unroll
-            for (int q = 0; q < R::CN; ++q) cr[q] = vals[q];
+                for (int q = 0; q < 4; ++q) put(R::YF + q, io[q]);
+            }
         }
+        viol = row_sum(c.body ? viol : 0.0);
+        // the leg's system
+        const double Gx = from_torso(gx), Gy = from_torso(gy);
+        const double Px = Fx - m * Gx, Py = Fy - m * Gy;
+        const double Qx = beyond(Px), Qy = beyond(Py);
+        const double nax = next_lane(apx), nay = next_lane(apy);
+        const double rx = c.inner ? nax - acx : 0.0, ry = c.inner ? nay - acy : 0.0;
         {
-            double acc = 0.0;
+            const double v[SH::N] = {rx, ry, msub * rx - m * acx, msub * ry - m * acy,
+                                     I + m * (acx * acx + acy * acy) + msub * (rx * rx + ry * ry),
+                                     T + (acy * Px - acx * Py) + (rx * Qy - ry * Qx), apx, apy};
 #pragma unroll
-            for (int i = 0; i < NC; ++i) acc += pbcast(ctcs_part, 32 + i);
-            if (lane == 0) sh.om[4 * NC] = acc;
+            for (int q = 0; q < SH::N; ++q) sh.g[q][me] = v[q];
         }
         plds_sync();
-        // ---- generalized force W ----
-        if (lane < NQ) {
-            const int b = lane / 3, q = lane - 3 * b;
-            double w = q == 1 ? -sh.prm[2 + b] * mc.g : 0.0;
-            if (q == 2) {
+        double Hi[D][D], H0[D][3], Gm[D][3], y[D];
+        const double a1x = sh.g[SH::AX][leg0], a1y = sh.g[SH::AY][leg0];
 #pragma unroll
-                for (int jj = 0; jj < NJ; ++jj) {
-                    if (TP::parent(jj) == b) w -= sh.tt[jj];
-                    if (jj + 1 == b) w += sh.tt[jj];
+        for (int i = 0; i < D; ++i) {
+            const double qx = sh.g[SH::RX][leg0 + i], qy = sh.g[SH::RY][leg0 + i];
+            const double ex = sh.g[SH::SX][leg0 + i], ey = sh.g[SH::SY][leg0 + i];
+            Hi[i][i] = sh.g[SH::HD][leg0 + i];
+            y[i] = sh.g[SH::F][leg0 + i];
+            H0[i][0] = -ey;
+            H0[i][1] = ex;
+            H0[i][2] = ex * a1x + ey * a1y;
+#pragma unroll
+            for (int l = i + 1; l < D; ++l)
+                Hi[i][l] = Hi[l][i] = qx * sh.g[SH::SX][leg0 + l] + qy * sh.g[SH::SY][leg0 + l];
+        }
+        plds_sync();
+        spd_inverse<D>(Hi);
+        double f[D];
+#pragma unroll
+        for (int i = 0; i < D; ++i) f[i] = y[i];
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            double t0 = 0.0, g0 = 0.0, g1 = 0.0, g2 = 0.0;
+#pragma unroll
+            for (int l = 0; l < D; ++l) {
+                t0 += Hi[i][l] * f[l];
+                g0 += Hi[i][l] * H0[l][0];
+                g1 += Hi[i][l] * H0[l][1];
+                g2 += Hi[i][l] * H0[l][2];
+            }
+            y[i] = t0;
+            Gm[i][0] = g0;
+            Gm[i][1] = g1;
+            Gm[i][2] = g2;
+        }
+        // the torso's system: first links hold their leg's part
+        double S[3][3], r0[3];
+        {
+            const double tx1 = Px + Qx, ty1 = Py + Qy;
+            double p[6] = {mleg, 0.0, -mleg * a1y, mleg, mleg * a1x, mleg * (a1x * a1x + a1y * a1y)};
+            double q[3] = {tx1, ty1, a1x * ty1 - a1y * tx1};
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                p[0] -= H0[i][0] * Gm[i][0];
+                p[1] -= H0[i][0] * Gm[i][1];
+                p[2] -= H0[i][0] * Gm[i][2];
+                p[3] -= H0[i][1] * Gm[i][1];
+                p[4] -= H0[i][1] * Gm[i][2];
+                p[5] -= H0[i][2] * Gm[i][2];
+#pragma unroll
+                for (int e = 0; e < 3; ++e) q[e] -= H0[i][e] * y[i];
+            }
+#pragma unroll
+            for (int e = 0; e < 6; ++e) p[e] = c.legs(p[e]);
+#pragma unroll
+            for (int e = 0; e < 3; ++e) r0[e] = c.legs(q[e]);
+            S[0][0] = p[0] + m0;
+            S[0][1] = S[1][0] = p[1];
+            S[0][2] = S[2][0] = p[2];
+            S[1][1] = p[3] + m0;
+            S[1][2] = S[2][1] = p[4];
+            S[2][2] = p[5] + I0;
+            r0[0] += row_lane<0>(Fx);
+            r0[1] += row_lane<0>(Fy);
+            r0[2] += row_lane<0>(T);
+        }
+        spd_inverse<3>(S);
+        double a0[3];
+#pragma unroll
+        for (int e = 0; e < 3; ++e) a0[e] = S[e][0] * r0[0] + S[e][1] * r0[1] + S[e][2] * r0[2];
+        // accelerations of the own body
+        double w = a0[2];
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            const double wi = y[i] - (Gm[i][0] * a0[0] + Gm[i][1] * a0[1] + Gm[i][2] * a0[2]);
+            if (c.joint && lk == i) w = wi;
+        }
+        const double ex = from_torso(c.joint ? -ry * w : 0.0), ey = from_torso(c.joint ? rx * w : 0.0);
+        double vx = a0[0], vy = a0[1];
+        if (c.joint) {   // (ex, ey without the own link)
+            vx += -a0[2] * a1y + Gx + (ex + ry * w) + acy * w;
+            vy += a0[2] * a1x + Gy + (ey - rx * w) - acx * w;
+        }
+        // joint forces
+        const double qx = Fx - m * vx, qy = Fy - m * vy;
+        const double lx = qx + beyond(qx), ly = qy + beyond(qy);
+        // ---- stage record ----
+        const double wpar = c.parent(w);   // (every lane takes part in a lane shift)
+        if (body) {
+            if (c.joint) {
+                const double jr[R::JN] = {apx, apy, acx, acy,
+                                          wp2 * apy - wpar * apx, -wp2 * apx - wpar * apy,
+                                          w * acx - wc2 * acy, w * acy + wc2 * acx,
+                                          -2.0 * omp * apx, -2.0 * omp * apy, 2.0 * om * acx,
+                                          2.0 * om * acy, apx * lx + apy * ly, acx * lx + acy * ly};
+#pragma unroll
+                for (int q = 0; q < R::JN; ++q) put(R::JN * lk + q, jr[q]);
+                const double sf[6] = {xs[3], xs[4], om, vx, vy, w};
+#pragma unroll
+                for (int q = 0; q < 6; ++q) put(R::SF + 6 * (lk + 1) + q, sf[q]);
+            } else {
+                const double sf[6] = {xs[3], xs[4], om, vx, vy, w};
+#pragma unroll
+                for (int l = 0; l < TP::L; ++l) {
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) sr[l * R::LEG + R::SF + q] = sf[q];
+                    sr[l * R::LEG + R::YF + 4] = l == 0 ? viol : 0.0;
                 }
             }
+            if (first) {
 #pragma unroll
-            for (int i = 0; i < NC; ++i)
-                if (TP::cbody(i) == b) w += sh.cw[i][q];
-            sh.W[lane] = w;
-        }
-        plds_sync();
-        // ---- Gauss-Jordan on [A | grad h M^-1 | r], r = -(grad h M^-1 W + c) ----
-        {
-            double y[NQ];
-            const int jl = (lane < NJ2 ? lane : 0) >> 1, cl = lane & 1;
-            const int pl = TP::parent(jl), chl = jl + 1;
-            const double eap = cl == 0 ? -sh.arm[jl][1] : sh.arm[jl][0];
-            const double eac = cl == 0 ? -sh.arm[jl][3] : sh.arm[jl][2];
+                for (int i = 0; i < D; ++i) {
 #pragma unroll
-            for (int r = 0; r < NQ; ++r) {
-                const int b = r / 3, q = r % 3;
-                double row = 0.0;
-                if (b == pl) row += q == cl ? 1.0 : (q == 2 ? eap : 0.0);
-                if (b == chl) row -= q == cl ? 1.0 : (q == 2 ? eac : 0.0);
-                const double mi = sh.minv[r];
-                y[r] = lane < NJ2 ? mi * row
-                     : lane < NJ2 + NQ ? (lane - NJ2 == r ? mi : 0.0)
-                                       : mi * sh.W[r];
-            }
-            double col[NJ2];
+                    for (int l = 0; l <= i; ++l) put(R::hi(i, l), Hi[i][l]);
 #pragma unroll
-            for (int i = 0; i < NJ2; ++i) {
-                const int jj = i >> 1, c = i & 1, p = TP::parent(jj), ch = jj + 1;
-                const double ep = c == 0 ? -sh.arm[jj][1] : sh.arm[jj][0];
-                const double ec = c == 0 ? -sh.arm[jj][3] : sh.arm[jj][2];
-                col[i] = (y[3 * p + c] + y[3 * p + 2] * ep) - (y[3 * ch + c] + y[3 * ch + 2] * ec);
-                if (lane == NJ2 + NQ) col[i] = -(col[i] + sh.cv[i]);
-            }
+                    for (int e = 0; e < 3; ++e) put(R::G + 3 * i + e, Gm[i][e]);
+                }
+                const double si[6] = {S[0][0], S[0][1], S[0][2], S[1][1], S[1][2], S[2][2]};
 #pragma unroll
-            for (int kk = 0; kk < NJ2; ++kk) {
-                double piv[NJ2];
-#pragma unroll
-                for (int i = 0; i < NJ2; ++i) piv[i] = pbcast(col[i], kk);
-                const double tv = col[kk] / piv[kk];
-#pragma unroll
-                for (int i = 0; i < NJ2; ++i) col[i] = i == kk ? tv : fma(-piv[i], tv, col[i]);
-            }
-            // Wm[r][c] = (A^-1 grad h M^-1)[c][r]
-            if (lane >= NJ2 && lane < NJ2 + NQ) {
-                double* wr = sr + R::WM + (lane - NJ2) * NJ2;
-#pragma unroll
-                for (int i = 0; i < NJ2; ++i) wr[i] = col[i];
-            }
-            if (lane == NJ2 + NQ) {
-#pragma unroll
-                for (int i = 0; i < NJ2; ++i) sh.lam[i] = col[i];
+                for (int e = 0; e < 6; ++e) put(R::SI + e, si[e]);
             }
         }
-        plds_sync();
-        // ---- v' = M^-1 (W + grad h^T lambda) ----
-        if (lane < NQ) {
-            const int b = lane / 3, q = lane - 3 * b;
-            double jt = 0.0;
-#pragma unroll
-            for (int jj = 0; jj < NJ; ++jj) {
-                const int p = TP::parent(jj), ch = jj + 1;
-                const double lx = sh.lam[2 * jj], ly = sh.lam[2 * jj + 1];
-                const double tp = sh.arm[jj][0] * ly - sh.arm[jj][1] * lx;
-                const double tc = sh.arm[jj][2] * ly - sh.arm[jj][3] * lx;
-                if (b == p) jt += q == 0 ? lx : (q == 1 ? ly : tp);
-                if (b == ch) jt -= q == 0 ? lx : (q == 1 ? ly : tc);
-            }
-            sh.vd[lane] = sh.minv[lane] * (sh.W[lane] + jt);
-        }
-        plds_sync();
-        // ---- rest of the stage record ----
-        if (lane < NB) {
-            double* br = sr + R::BODY + 6 * lane;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                br[q] = vs[3 * lane + q];
-                br[3 + q] = sh.vd[3 * lane + q];
-            }
-        }
-        if (lane < NJ) {
-            double* jr = sr + R::JNT + 6 * lane;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) jr[q] = sh.arm[lane][q];
-            jr[4] = sh.lam[2 * lane];
-            jr[5] = sh.lam[2 * lane + 1];
-        }
-        if (lane == 0) sr[R::CT] = sh.om[4 * NC];
         // ---- RK4 of the nominal ----
-        {
-            const double wk = (st == 0 || st == 3) ? 1.0 : 2.0;
-            const double an = (st == 2) ? h : 0.5 * h;
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                const double kk = s * (q < 3 ? xsl[3 + q] : sh.vd[3 * bl + q - 3]);
-                xa[q] = st == 0 ? kk : xa[q] + wk * kk;
-                if (st < 3) xsl[q] = xb[q] + an * kk;
-            }
-            const double ky = lane < NY ? s * sh.om[lane] : 0.0;
-            ya = st == 0 ? ky : ya + wk * ky;
-            if (st == 3) {
-#pragma unroll
-                for (int q = 0; q < 6; ++q) {
-                    xb[q] += (h / 6.0) * xa[q];
-                    xsl[q] = xb[q];
-                }
-                yb += (h / 6.0) * ya;
-            }
-        }
-        plds_sync();
-    }
-    // ---- outputs of the nominal ----
-    if (lane < NB) {
+        const double wk = (st == 0 || st == 3) ? 1.0 : 2.0;
+        const double an = (st == 2) ? h : 0.5 * h;
+        const double vd[3] = {vx, vy, w};
 #pragma unroll
         for (int q = 0; q < 6; ++q) {
-            const int r = q < 3 ? 3 * lane + q : NQ + 3 * lane + q - 3;
-            if (a.xprop) a.xprop[r * ldi + k] = xb[q];
-            a.defect[r * ldi + k] = xb[q] - sh.xk1[r];
+            const double kk = s * (q < 3 ? xs[3 + q] : vd[q - 3]);
+            xa[q] = st == 0 ? kk : xa[q] + wk * kk;
+        }
+        if (st < 3) {
+            const double v0 = xs[3], v1 = xs[4], v2 = xs[5];
+            xs[0] = xb[0] + an * (s * v0);
+            xs[1] = xb[1] + an * (s * v1);
+            xs[2] = xb[2] + an * (s * v2);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) xs[3 + q] = xb[3 + q] + an * (s * vd[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ya[q] = st == 0 ? s * io[q] : ya[q] + wk * (s * io[q]);
+        va = st == 0 ? s * viol : va + wk * (s * viol);
+        if (st == 3) {
+#pragma unroll
+            for (int q = 0; q < 6; ++q) xs[q] = xb[q] += (h / 6.0) * xa[q];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) yb[q] += (h / 6.0) * ya[q];
+            vb += (h / 6.0) * va;
         }
     }
-    if (lane < NY) {
-        if (a.xprop) a.xprop[(N6 + lane) * ldi + k] = yb;
-        a.defect[(N6 + lane) * ldi + k] = yb - sh.xk1[N6 + lane];
+    // ---- outputs of the nominal ----
+    auto out = [&](int r, double v) {
+        if (a.xprop) a.xprop[r * ldi + k] = v;
+        a.defect[r * ldi + k] = v - a.X[r * ldn + k + 1];
+    };
+    if (body) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) out(row(q), xb[q]);
+        if (c.contact)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) out(N6 + 4 * c.i + q, yb[q]);
+        if (c.torso) out(N6 + 4 * NC, vb);
     }
     // A[:, n:] = [0; I]: the integral states feed back into nothing
-    for (int e = lane; e < NX * NY; e += 64) {
-        const int r = e / NY, cc = N6 + e % NY;
-        a.A[((int64_t)r * NX + cc) * ldi + k] = (r == cc) ? 1.0 : 0.0;
-    }
+    if (on)
+        for (int e = me & 15; e < NX * NY; e += 16) {
+            const int r = e / NY, cc = N6 + e % NY;
+            a.A[((int64_t)r * NX + cc) * ldi + k] = (r == cc) ? 1.0 : 0.0;
+        }
 }
 
 // ---------------------------------------------------------------------------
 // k_paper_tan: columns [64 cb, 64 cb + 64) of interval k, wave `leg`.  Local
-// body lb = 0 is the torso, lb = 1..D the links of the leg; rows zs[3 lb + q]
-// (pose) and zs[3 LB + 3 lb + q] (velocity); the leg's contact rows y[0..3]
-// and its share of the violation row y[4].
+// body 0 is the torso, 1..D the links of the leg; rows zs[3 lb + q] (pose) and
+// zs[3 LB + 3 lb + q] (velocity); the leg's contact rows y[0..3] and its share of
+// the violation row y[4].  Bound by FP64 issue (280 instructions of a stage, 150 of
+// them with a coefficient).  1,603 quad13 intervals, K = 20: 1.00 ms; the product with
+// the dense M^-1 grad h^T A^-1 of every stage, read by scalar loads, took 5.6 ms.
 // ---------------------------------------------------------------------------
 template <class TP>
 struct PLane {
@@ -442,202 +519,179 @@ struct PLane {
     double yc[5];
 };
 
-// Threads of a tangent workgroup and the elements of a stage record each of
-// them loads one stage ahead (into the LDS area `sink`, never read: the loads
-// bring the record, which the leg waves then read with scalar loads, into the
-// L2 cache before it is needed).
+// a += coefficient IDX of the stage's vectors times x; b += coefficient IDY times z
+template <int IDX, int NV>
+__device__ __forceinline__ void pfma(double& a, const double (&v)[NV], double x) {
+    fma_row<IDX & 15>(a, v[IDX >> 4], x);
+}
+template <int IDX, int IDY, int NV>
+__device__ __forceinline__ void pfma2(double& a, double& b, const double (&v)[NV], double x,
+                                      double z) {
+    fma_row2<IDX & 15, IDY & 15>(a, b, v[IDX >> 4], v[IDY >> 4], x, z);
+}
+
+// What a tangent lane is: hold weights, and its control's selection on this leg.
 template <class TP>
-struct PWarm {
-    static constexpr int NT = 64 * TP::L;
-    static constexpr int PW = (PRec<TP>::STAGE + NT - 1) / NT;
+struct PColumn {
+    double wbm, wbp, fsel;
+    bool tq[TP::D], ct, cn, cg;
 };
 
-template <class TP>
-__device__ __forceinline__ void paper_tangent_stage(PLane<TP>& z, const double* __restrict__ hd,
-                                                    const double* __restrict__ sr, double* xch,
-                                                    int leg, int lane, int st, double tau,
-                                                    double wbm, double wbp, int ctrl,
-                                                    double fsel,
-                                                    const double* __restrict__ sr_next,
-                                                    double* sink) {
-    constexpr int D = TP::D, L = TP::L, LB = TP::LB, NJ = TP::NJ, NJ2 = TP::NJ2, NQ = TP::NQ;
+template <class TP, int ST>
+__device__ __forceinline__ void paper_tangent_stage(PLane<TP>& z, const PColumn<TP>& col,
+                                                    const double (&v)[PRec<TP>::NV],
+                                                    const double (&mass)[TP::D],
+                                                    const double (&kd)[2 * TP::D], double s,
+                                                    double h, double tau, double* xch, int leg,
+                                                    int lane) {
+    constexpr int D = TP::D, L = TP::L, LB = TP::LB;
     using R = PRec<TP>;
-    constexpr int NT = PWarm<TP>::NT, PW = PWarm<TP>::PW;
-    double warm[PW];
-#pragma unroll
-    for (int e = 0; e < PW; ++e) {
-        const int c = e * NT + leg * 64 + lane;
-        warm[e] = sr_next[c < R::STAGE ? c : R::STAGE - 1];
-    }
-    const double s = hd[0], h = hd[1], h6 = hd[2];
-    const double* minv = hd + 8;
-    const double* kd = hd + 8 + NQ;
-    auto gb = [&](int lb) { return lb == 0 ? 0 : 1 + leg * D + lb - 1; };
 #define ZQ(lb, q) z.zs[3 * (lb) + (q)]
 #define ZV(lb, q) z.zs[3 * LB + 3 * (lb) + (q)]
-    const double* bo = sr + R::BODY;
-    const double* jn = sr + R::JNT;
-    const double* co = sr + R::CON + R::CN * leg;
     // FOH weight of a B- / B+ column (0 for the other columns)
-    const double w = wbm * (1.0 - tau) + wbp * tau;
-    // ---- u = dF + dgrad_h^T lambda (+ control forcing) on the local bodies ----
-    double u[3 * LB];
+    const double w = col.wbm * (1.0 - tau) + col.wbp * tau;
+    const double wt = col.ct ? w : 0.0, wn = col.cn ? w : 0.0, wg = col.cg ? w : 0.0;
+    // ---- u: torques of the bodies, force at the tip; d: joint terms, summed from
+    // the torso (dx, dy: link by link) ----
+    double ut[LB], dx[D], dy[D];
 #pragma unroll
-    for (int r = 0; r < 3 * LB; ++r) u[r] = 0.0;
-    // spring-damper and torque of the leg's joints: dtt = -k dth_rel - d dw_rel
-    double hip = 0.0;
-#pragma unroll
-    for (int lb = 1; lb <= D; ++lb) {
-        const int j = leg * D + lb - 1;
-        double dtt = -kd[2 * j] * (ZQ(lb, 2) - ZQ(lb - 1, 2)) - kd[2 * j + 1] * (ZV(lb, 2) - ZV(lb - 1, 2));
-        if (ctrl == j) dtt += w;   // joint torque column
-        if (lb == 1) hip = -dtt;   // torso share, summed over the legs below
-        else u[3 * (lb - 1) + 2] -= dtt;
-        u[3 * lb + 2] += dtt;
-        // dgrad_h^T lambda on the theta rows: parent -dth_p (a_p . lam), child +dth_c (a_c . lam)
-        const double* jj = jn + 6 * j;
-        if (lb >= 2) u[3 * (lb - 1) + 2] -= ZQ(lb - 1, 2) * (jj[0] * jj[4] + jj[1] * jj[5]);
-        else hip -= ZQ(0, 2) * (jj[0] * jj[4] + jj[1] * jj[5]);
-        u[3 * lb + 2] += ZQ(lb, 2) * (jj[2] * jj[4] + jj[3] * jj[5]);
-    }
-    // contact at the leg tip: dF = (dt/dPx phi_t + dn/dPx phi_n) dPx, torque a x F
+    for (int lb = 0; lb < LB; ++lb) ut[lb] = 0.0;
+    unrolled<D>([&](auto l_c) {
+        constexpr int l = decltype(l_c)::value, J = R::JN * l;
+        double t = -kd[2 * l] * (ZQ(l + 1, 2) - ZQ(l, 2)) - kd[2 * l + 1] * (ZV(l + 1, 2) - ZV(l, 2));
+        t += col.tq[l] ? w : 0.0;
+        ut[l] -= t;
+        ut[l + 1] += t;
+        pfma2<J + 12, J + 13>(ut[l], ut[l + 1], v, -ZQ(l, 2), ZQ(l + 1, 2));
+        dx[l] = dy[l] = 0.0;
+        pfma2<J + 4, J + 5>(dx[l], dy[l], v, ZQ(l, 2), ZQ(l, 2));
+        pfma2<J + 6, J + 7>(dx[l], dy[l], v, ZQ(l + 1, 2), ZQ(l + 1, 2));
+        pfma2<J + 8, J + 9>(dx[l], dy[l], v, ZV(l, 2), ZV(l, 2));
+        pfma2<J + 10, J + 11>(dx[l], dy[l], v, ZV(l + 1, 2), ZV(l + 1, 2));
+    });
+    double fx = 0.0, fy = 0.0;
+    pfma2<R::FXX, R::FYX>(fx, fy, v, ZQ(D, 0), ZQ(D, 0));
+    pfma2<R::FXT, R::FYT>(fx, fy, v, ZQ(D, 2), ZQ(D, 2));
+    pfma2<R::CTX, R::CTY>(fx, fy, v, wt, wt);
+    pfma2<R::CNX, R::CNY>(fx, fy, v, wn, wn);
+    pfma<R::TQX>(ut[D], v, ZQ(D, 0));
+    pfma<R::TQT>(ut[D], v, ZQ(D, 2));
+    pfma<R::CTT>(ut[D], v, wt);
+    pfma<R::CTN>(ut[D], v, wn);
+    // ---- generalized forces f of the leg, and its part of the torso's system ----
+    double f[D], px = 0.0, py = 0.0;   // (px, py): sum of u - m Gamma beyond a link
     {
-        constexpr int lb = D;
-        const double dPx = ZQ(lb, 0) - co[P_AY] * ZQ(lb, 2);
-        const double dFx = (co[P_DTX] * co[P_PT] + co[P_DNX] * co[P_PN]) * dPx;
-        const double dFy = (co[P_DTY] * co[P_PT] + co[P_DNY] * co[P_PN]) * dPx;
-        u[3 * lb] += dFx;
-        u[3 * lb + 1] += dFy;
-        u[3 * lb + 2] += -(co[P_AX] * co[P_FX] + co[P_AY] * co[P_FY]) * ZQ(lb, 2) +
-                         (co[P_AX] * dFy - co[P_AY] * dFx);
-        // contact force columns of this leg's contact
-        const int i0 = NJ + 3 * leg;
-        const double wt = ctrl == i0 ? w : 0.0, wn = ctrl == i0 + 1 ? w : 0.0;
-        const double fx = co[P_TX] * wt + co[P_NX] * wn, fy = co[P_TY] * wt + co[P_NY] * wn;
-        u[3 * lb] += fx;
-        u[3 * lb + 1] += fy;
-        u[3 * lb + 2] += co[P_AX] * fy - co[P_AY] * fx;
-    }
-    // ---- exchange 1: the torso's hip terms of every leg ----
-    if constexpr (L > 1) {
-        xch[leg * 64 + lane] = hip;
-        __syncthreads();
-        double acc = 0.0;
+        double Gx[D], Gy[D];
 #pragma unroll
-        for (int l = 0; l < L; ++l) acc += xch[l * 64 + lane];
-        u[2] += acc;
-    } else {
-        u[2] += hip;
-    }
-#pragma unroll
-    for (int e = 0; e < PW; ++e) sink[e * NT + leg * 64 + lane] = warm[e];
-    // ---- b on the leg's joints: grad h M^-1 u + dgrad_h v' + dc ----
-    double y[3 * LB];
-#pragma unroll
-    for (int lb = 0; lb < LB; ++lb)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) y[3 * lb + q] = minv[3 * gb(lb) + q] * u[3 * lb + q];
-    double bl[2 * D];
-#pragma unroll
-    for (int lb = 1; lb <= D; ++lb) {
-        const int j = leg * D + lb - 1;
-        const double* jj = jn + 6 * j;
-        const double apx = jj[0], apy = jj[1], acx = jj[2], acy = jj[3];
-        const int pb = lb - 1, cb = lb;
-        const double wp = bo[6 * gb(pb) + 2], wc = bo[6 * gb(cb) + 2];
-        const double ap_dd = bo[6 * gb(pb) + 5], ac_dd = bo[6 * gb(cb) + 5];
-        const double thp = ZQ(pb, 2), thc = ZQ(cb, 2), dwp = ZV(pb, 2), dwc = ZV(cb, 2);
-        // grad h M^-1 u (E a = (-a_y, a_x))
-        double bx = (y[3 * pb] - y[3 * pb + 2] * apy) - (y[3 * cb] - y[3 * cb + 2] * acy);
-        double by = (y[3 * pb + 1] + y[3 * pb + 2] * apx) - (y[3 * cb + 1] + y[3 * cb + 2] * acx);
-        // dgrad_h v': -dth_p w'_p a_p + dth_c w'_c a_c
-        bx += -thp * ap_dd * apx + thc * ac_dd * acx;
-        by += -thp * ap_dd * apy + thc * ac_dd * acy;
-        // dc: -2 w_p dw_p a_p - w_p^2 dth_p E a_p + 2 w_c dw_c a_c + w_c^2 dth_c E a_c
-        bx += -2.0 * wp * dwp * apx + wp * wp * thp * apy + 2.0 * wc * dwc * acx - wc * wc * thc * acy;
-        by += -2.0 * wp * dwp * apy - wp * wp * thp * apx + 2.0 * wc * dwc * acy + wc * wc * thc * acx;
-        bl[2 * (lb - 1)] = bx;
-        bl[2 * (lb - 1) + 1] = by;
-    }
-    // ---- exchange 2: b of every joint ----
-    double* xb2 = xch + L * 64;
-    if constexpr (L > 1) {
-#pragma unroll
-        for (int e = 0; e < 2 * D; ++e) xb2[(leg * 2 * D + e) * 64 + lane] = bl[e];
-        __syncthreads();
-    }
-    // ---- dv' = M^-1 u - Wm b on the local rows ----
-    double kv[3 * LB];
-#pragma unroll
-    for (int lb = 0; lb < LB; ++lb)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const double* wr = sr + R::WM + (3 * gb(lb) + q) * NJ2;
-            double acc = y[3 * lb + q];
-#pragma unroll
-            for (int e = 0; e < NJ2; ++e) {
-                double be;
-                if constexpr (L > 1) be = xb2[e * 64 + lane];
-                else be = bl[e];
-                acc = fma(-wr[e], be, acc);
+        for (int l = 0; l < D; ++l) {
+            Gx[l] = l ? Gx[l > 0 ? l - 1 : 0] + dx[l] : dx[l];
+            Gy[l] = l ? Gy[l > 0 ? l - 1 : 0] + dy[l] : dy[l];
+        }
+        unrolled<D>([&](auto e_c) {
+            constexpr int l = D - 1 - decltype(e_c)::value, J = R::JN * l;
+            double t = ut[l + 1];
+            if constexpr (l < D - 1) {   // E a_p of the next joint on the links beyond
+                pfma<J + R::JN>(t, v, py);
+                pfma<J + R::JN + 1>(t, v, -px);
             }
-            kv[3 * lb + q] = s * acc + fsel * bo[6 * gb(lb) + 3 + q];
+            const double fl = l == D - 1 ? 1.0 : 0.0;
+            px += fma(-mass[l], Gx[l], fl * fx);
+            py += fma(-mass[l], Gy[l], fl * fy);
+            pfma<J + 3>(t, v, px);
+            pfma<J + 2>(t, v, -py);
+            f[l] = t;
+        });
+    }
+    double r0[3] = {px, py, ut[0]};
+    pfma<0>(r0[2], v, py);
+    pfma<1>(r0[2], v, -px);
+    unrolled<D>([&](auto l_c) {
+        constexpr int l = decltype(l_c)::value;
+        const double n = -f[l];
+        pfma2<R::G + 3 * l, R::G + 3 * l + 1>(r0[0], r0[1], v, n, n);
+        pfma<R::G + 3 * l + 2>(r0[2], v, n);
+    });
+    // ---- exchange: the legs' parts ----
+    if constexpr (L > 1) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e) xch[(leg * 3 + e) * 64 + lane] = r0[e];
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            double acc = 0.0;
+#pragma unroll
+            for (int l = 0; l < L; ++l) acc += xch[(l * 3 + e) * 64 + lane];
+            r0[e] = acc;
         }
+    }
+    double a0[3] = {0.0, 0.0, 0.0}, kv[3 * LB];
+    pfma2<R::SI, R::SI + 1>(a0[0], a0[1], v, r0[0], r0[0]);
+    pfma2<R::SI + 2, R::SI + 1>(a0[2], a0[0], v, r0[0], r0[1]);
+    pfma2<R::SI + 3, R::SI + 4>(a0[1], a0[2], v, r0[1], r0[1]);
+    pfma2<R::SI + 2, R::SI + 4>(a0[0], a0[1], v, r0[2], r0[2]);
+    pfma<R::SI + 5>(a0[2], v, r0[2]);
+    // ---- angular accelerations of the leg, then the links' translations ----
+    kv[0] = a0[0];
+    kv[1] = a0[1];
+    kv[2] = a0[2];
+    const double n0[3] = {-a0[0], -a0[1], -a0[2]};
+    unrolled<D>([&](auto l_c) {
+        constexpr int l = decltype(l_c)::value;
+        double t = 0.0, q = 0.0;
+        pfma2<R::G + 3 * l, R::G + 3 * l + 1>(t, q, v, n0[0], n0[1]);
+        pfma<R::G + 3 * l + 2>(t, v, n0[2]);
+        unrolled<D>([&](auto i_c) {
+            constexpr int i = decltype(i_c)::value;
+            pfma<(i > l ? R::hi(i, l) : R::hi(l, i))>(q, v, f[i]);
+        });
+        kv[3 * (l + 1) + 2] = t + q;
+    });
+    double ax = a0[0], ay = a0[1];
+    unrolled<D>([&](auto l_c) {
+        constexpr int l = decltype(l_c)::value, J = R::JN * l;
+        const double wp = kv[3 * l + 2], wc = kv[3 * l + 5];
+        ax += dx[l];
+        ay += dy[l];
+        pfma2<J + 1, J>(ax, ay, v, -wp, wp);
+        pfma2<J + 3, J + 2>(ax, ay, v, wc, -wc);
+        kv[3 * l + 3] = ax;
+        kv[3 * l + 4] = ay;
+    });
     // ---- the leg's integral rows and its share of the violation row ----
-    double ky[5];
-    {
-        constexpr int lb = D;
-        const double dPx = ZQ(lb, 0) - co[P_AY] * ZQ(lb, 2);
-        const double dPy = ZQ(lb, 1) + co[P_AX] * ZQ(lb, 2);
-        // d(J v) = dv_b + dw E a - w dth a
-        const double wb = bo[6 * gb(lb) + 2];
-        const double djx = ZV(lb, 0) - ZV(lb, 2) * co[P_AY] - wb * ZQ(lb, 2) * co[P_AX];
-        const double djy = ZV(lb, 1) + ZV(lb, 2) * co[P_AX] - wb * ZQ(lb, 2) * co[P_AY];
-        double dlc = (co[P_DTX] * co[P_JVX] + co[P_DTY] * co[P_JVY]) * dPx +
-                     co[P_TX] * djx + co[P_TY] * djy;
-        double dct = co[P_CCS] * (co[P_GSX] * dPx + co[P_GSY] * dPy);
-        double dpn = 0.0, dgm = 0.0, drc = 0.0;
-        const int i0 = NJ + 3 * leg;
-        const double wt = ctrl == i0 ? w : 0.0, wn = ctrl == i0 + 1 ? w : 0.0;
-        const double wg = ctrl == i0 + 2 ? w : 0.0;
-        dpn += wn;
-        dgm += wg;
-        dlc += co[P_LCT] * wt + co[P_LCG] * wg;
-        drc += co[P_RCN] * wn + co[P_RCT] * wt;
-        dct += co[P_CCN] * wn + co[P_CCG] * wg + co[P_CCR] * (co[P_RCN] * wn + co[P_RCT] * wt);
-        ky[0] = s * dpn + fsel * co[P_OPN];
-        ky[1] = s * dlc + fsel * co[P_OLC];
-        ky[2] = s * dgm + fsel * co[P_OGM];
-        ky[3] = s * drc + fsel * co[P_ORC];
-        ky[4] = s * dct + (leg == 0 ? fsel * sr[R::CT] : 0.0);
-    }
+    double ky[5] = {wn, 0.0, wg, 0.0, 0.0};
+    pfma2<R::LX, R::SX>(ky[1], ky[4], v, ZQ(D, 0), ZQ(D, 0));
+    pfma2<R::LT, R::SY>(ky[1], ky[4], v, ZQ(D, 2), ZQ(D, 1));
+    pfma2<R::CTX, R::ST>(ky[1], ky[4], v, ZV(D, 0), ZQ(D, 2));
+    pfma2<R::CTY, R::VN>(ky[1], ky[4], v, ZV(D, 1), wn);
+    pfma2<R::LW, R::VT>(ky[1], ky[4], v, ZV(D, 2), wt);
+    pfma2<R::LCT, R::VG>(ky[1], ky[4], v, wt, wg);
+    pfma2<R::LCG, R::RCN>(ky[1], ky[3], v, wg, wn);
+    pfma<R::RCT>(ky[3], v, wt);
+#pragma unroll
+    for (int q = 0; q < 5; ++q) ky[q] *= s;
+    unrolled<5>([&](auto q_c) {
+        constexpr int q = decltype(q_c)::value;
+        pfma<R::YF + q>(ky[q], v, col.fsel);
+    });
     // ---- classical RK4 combination ----
-    const double wk = (st == 0 || st == 3) ? 1.0 : 2.0;
-    const double an = (st == 2) ? h : 0.5 * h;
-#pragma unroll
-    for (int lb = 0; lb < LB; ++lb)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int r = 3 * lb + q;
-            const double kq = s * z.zs[3 * LB + r] + fsel * bo[6 * gb(lb) + q];
-            z.za[r] = st == 0 ? kq : z.za[r] + wk * kq;
-            if (st < 3) z.zs[r] = z.zb[r] + an * kq;
+    constexpr double wk = (ST == 0 || ST == 3) ? 1.0 : 2.0;
+    const double an = ST == 2 ? h : 0.5 * h, h6 = h / 6.0;
+    unrolled<3 * LB>([&](auto r_c) {
+        constexpr int r = decltype(r_c)::value, lb = r / 3, q = r % 3;
+        double kq = s * z.zs[3 * LB + r], ka = s * kv[r];
+        pfma2<R::SF + 6 * lb + q, R::SF + 6 * lb + 3 + q>(kq, ka, v, col.fsel, col.fsel);
+        z.za[r] = ST == 0 ? kq : z.za[r] + wk * kq;
+        z.za[3 * LB + r] = ST == 0 ? ka : z.za[3 * LB + r] + wk * ka;
+        if constexpr (ST < 3) {
+            z.zs[r] = z.zb[r] + an * kq;
+            z.zs[3 * LB + r] = z.zb[3 * LB + r] + an * ka;
+        } else {
+            z.zs[r] = z.zb[r] += h6 * z.za[r];
+            z.zs[3 * LB + r] = z.zb[3 * LB + r] += h6 * z.za[3 * LB + r];
         }
-#pragma unroll
-    for (int r = 0; r < 3 * LB; ++r) {
-        z.za[3 * LB + r] = st == 0 ? kv[r] : z.za[3 * LB + r] + wk * kv[r];
-        if (st < 3) z.zs[3 * LB + r] = z.zb[3 * LB + r] + an * kv[r];
-    }
+    });
 #pragma unroll
     for (int q = 0; q < 5; ++q) z.yc[q] += (h6 * wk) * ky[q];
-    if (st == 3) {
-#pragma unroll
-        for (int r = 0; r < 6 * LB; ++r) {
-            z.zb[r] += h6 * z.za[r];
-            z.zs[r] = z.zb[r];
-        }
-    }
-    if constexpr (L > 1) __syncthreads();   // the exchange areas are reused next stage
 #undef ZQ
 #undef ZV
 }
@@ -646,10 +700,9 @@ template <class TP>
 __global__ void __launch_bounds__(64 * TP::L) __attribute__((amdgpu_waves_per_eu(2)))
     k_paper_tan(PaperArgs a) {
     constexpr int N6 = TP::N6, NQ = TP::NQ, M = TP::M, D = TP::D, L = TP::L, LB = TP::LB;
-    constexpr int NX = TP::NX, NC = TP::NC;
+    constexpr int NX = TP::NX, NC = TP::NC, NJ = TP::NJ;
     using R = PRec<TP>;
-    __shared__ double xch[(TP::L + 2 * TP::NJ) * 64];
-    __shared__ double sink[PWarm<TP>::PW * PWarm<TP>::NT];
+    __shared__ double xch[2][3 * L * 64];   // in turn, one barrier per stage
     int k, cb;
     unit_item(xcd_slot(blockIdx.x, gridDim.x), a.N, TP::NBLK, k, cb);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -657,11 +710,17 @@ __global__ void __launch_bounds__(64 * TP::L) __attribute__((amdgpu_waves_per_eu
     const int col = cb * 64 + lane;
     const bool active = col < TP::NCOL;
     auto gb = [&](int lb) { return lb == 0 ? 0 : 1 + leg * D + lb - 1; };
-    double wbm = 0.0, wbp = 0.0, fsel = 0.0;
+    PColumn<TP> pc;
+    pc.wbm = pc.wbp = pc.fsel = 0.0;
     int ctrl = -1;
-    if (col >= N6 && col < N6 + M) { wbm = 1.0; ctrl = col - N6; }
-    else if (col >= N6 + M && col < N6 + 2 * M) { wbp = 1.0; ctrl = col - N6 - M; }
-    else if (col == N6 + 2 * M) fsel = 1.0;
+    if (col >= N6 && col < N6 + M) { pc.wbm = 1.0; ctrl = col - N6; }
+    else if (col >= N6 + M && col < N6 + 2 * M) { pc.wbp = 1.0; ctrl = col - N6 - M; }
+    else if (col == N6 + 2 * M) pc.fsel = 1.0;
+#pragma unroll
+    for (int l = 0; l < D; ++l) pc.tq[l] = ctrl == leg * D + l;
+    pc.ct = ctrl == NJ + 3 * leg;
+    pc.cn = ctrl == NJ + 3 * leg + 1;
+    pc.cg = ctrl == NJ + 3 * leg + 2;
     PLane<TP> z;
 #pragma unroll
     for (int lb = 0; lb < LB; ++lb)
@@ -679,25 +738,47 @@ __global__ void __launch_bounds__(64 * TP::L) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
     for (int q = 0; q < 5; ++q) z.yc[q] = 0.0;
     const double* hd = a.rec + (int64_t)k * R::per_interval(a.K);
-    const double h = 1.0 / double(a.K);
-    for (int t = 0; t < 4 * a.K; ++t) {
-        const int st = t & 3, j = t >> 2;
-        const double tau = (double(j) + (st == 0 ? 0.0 : (st == 3 ? 1.0 : 0.5))) * h;
-        const double* sr = hd + R::HDR + (int64_t)t * R::STAGE;
-        paper_tangent_stage<TP>(z, hd, sr, xch, leg, lane, st, tau, wbm, wbp, ctrl, fsel,
-                                t + 1 < 4 * a.K ? sr + R::STAGE : sr, sink);
+    const double h = uniform(1.0 / double(a.K)), s = hd[0];
+    double mass[D], kd[2 * D];
+#pragma unroll
+    for (int l = 0; l < D; ++l) {
+        mass[l] = hd[8 + gb(l + 1)];
+        kd[2 * l] = hd[8 + TP::NB + 2 * (leg * D + l)];
+        kd[2 * l + 1] = hd[8 + TP::NB + 2 * (leg * D + l) + 1];
     }
-    // the warm-up copies are never read; a read on a path that never runs
-    // (K >= 1 is checked on the host) keeps their stores
-    if (a.K <= 0) xch[tid] = sink[tid];
+    // the stage's coefficients, element lane & 15 of each vector; a stage ahead
+    const double* at = hd + R::HDR + leg * R::LEG + (lane & 15);
+    const double* last = at + (int64_t)(4 * a.K - 1) * R::STAGE;
+    double v[2][R::NV];
+    auto load = [&](double (&to)[R::NV]) {
+#pragma unroll
+        for (int q = 0; q < R::NV; ++q) to[q] = at[16 * q];
+        at = at < last ? at + R::STAGE : last;
+    };
+    load(v[0]);
+    for (int j = 0; j < a.K; ++j) {
+        auto stage = [&](auto st_c) {
+            constexpr int ST = decltype(st_c)::value;
+            load(v[(ST + 1) & 1]);
+            const double tau =
+                uniform((double(j) + (ST == 0 ? 0.0 : (ST == 3 ? 1.0 : 0.5))) * h);
+            paper_tangent_stage<TP, ST>(z, pc, v[ST & 1], mass, kd, s, h, tau, xch[ST & 1], leg,
+                                        lane);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        stage(std::integral_constant<int, 0>{});
+        stage(std::integral_constant<int, 1>{});
+        stage(std::integral_constant<int, 2>{});
+        stage(std::integral_constant<int, 3>{});
+    }
     // violation row: the legs' shares in leg order
     double yct = z.yc[4];
     if constexpr (L > 1) {
-        xch[leg * 64 + lane] = yct;
+        xch[0][leg * 64 + lane] = yct;   // (last read before the last stage's barrier)
         __syncthreads();
         yct = 0.0;
 #pragma unroll
-        for (int l = 0; l < L; ++l) yct += xch[l * 64 + lane];
+        for (int l = 0; l < L; ++l) yct += xch[0][l * 64 + lane];
     }
     if (!active) return;
     const int64_t ldi = a.ldi;
@@ -727,7 +808,7 @@ static cis_status launch_paper_t(const cis_model* m, const PaperArgs& a, hipStre
     if constexpr (L >= 1 && D >= 1) {
         using TP = PTopo<L, D>;
         const auto mc = make_const<TP::NB, TP::NJ, TP::NC>(m);
-        hipLaunchKernelGGL(k_paper_rec<TP>, dim3(a.N), dim3(64), 0, stream, a, mc);
+        hipLaunchKernelGGL(k_paper_rec<TP>, dim3((a.N + 3) / 4), dim3(64), 0, stream, a, mc);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(CIS_ERR_HIP, "k_paper_rec launch: %s", hipGetErrorString(e));
         hipLaunchKernelGGL(k_paper_tan<TP>, dim3(a.N * TP::NBLK), dim3(64 * TP::L), 0, stream, a);
