@@ -220,6 +220,13 @@ cis_status cis_discretize_adjoint_noalloc(const cis_model *model, const cis_shap
                                           int32_t ckpt_every, const void *seed, void *gX,
                                           void *gU, void *gs, void *gparams, void *stream);
 
+/* Which form of the discretize step is the faster one for this shape on the
+ * current device, by measured rule: *split = 1 for cis_discretize_split, 0 for
+ * cis_discretize (also where the first is not offered, or shape->layout names a
+ * layout of the second). */
+cis_status cis_discretize_prefers_split(const cis_model *model, const cis_shape *shape,
+                                        int32_t *split);
+
 /* Bytes of device workspace cis_discretize_split needs for this shape (the
  * model must have legs with links, else CIS_ERR_UNSUPPORTED). */
 cis_status cis_split_workspace_size(const cis_model *model, const cis_shape *shape,

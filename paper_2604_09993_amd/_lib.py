@@ -54,6 +54,7 @@ EXPORTS = [
     "cis_adjoint_workspace_size", "cis_discretize_adjoint", "cis_batch_plan_create",
     "cis_batch_run", "cis_batch_graph_run", "cis_batch_plan_info", "cis_batch_plan_destroy",
     "cis_blocked_workspace_size", "cis_discretize_blocked", "cis_discretize_adjoint_noalloc",
+    "cis_discretize_prefers_split",
     "cis_split_workspace_size", "cis_discretize_split", "cis_batch_plan_discretize_form",
     "cis_batch_run_part", "cis_impact_dims", "cis_impact_linearize", "cis_rkf_workspace_size",
     "cis_discretize_rkf", "cis_paper_dims", "cis_paper_workspace_size", "cis_discretize_paper",
@@ -138,6 +139,8 @@ def load(build_if_missing: bool = True):
     lib.cis_discretize_adjoint_noalloc.restype = St
     lib.cis_discretize_adjoint_noalloc.argtypes = ([P, ctypes.POINTER(Shape), P, P, P, P, P, I32]
                                                    + [P] * 6)
+    lib.cis_discretize_prefers_split.restype = St
+    lib.cis_discretize_prefers_split.argtypes = [P, ctypes.POINTER(Shape), ctypes.POINTER(I32)]
     lib.cis_split_workspace_size.restype = St
     lib.cis_split_workspace_size.argtypes = [P, ctypes.POINTER(Shape),
                                              ctypes.POINTER(ctypes.c_size_t)]

@@ -109,13 +109,42 @@ def _check_inputs(cm, X, U, s, params):
         raise ValueError("params must hold P contiguous values and s must be contiguous")
 
 
+SPLIT_WS_MAX = 8 << 30   # bytes (12,800 quad13 intervals, K = 20, FP64: 2 GB)
+
+
+def _split_workspace(cm, X, s, K, stream):
+    """Workspace of the two-launch form where that is the faster one, else None."""
+    sh = _shape(X, s, K)
+    lib = _lib.load()
+    split = ctypes.c_int32()
+    _lib.check(lib.cis_discretize_prefers_split(cm.handle, ctypes.byref(sh), ctypes.byref(split)))
+    if not split.value:
+        return None
+    nbytes = ctypes.c_size_t()
+    if lib.cis_split_workspace_size(cm.handle, ctypes.byref(sh), ctypes.byref(nbytes)) != 0 \
+            or nbytes.value > SPLIT_WS_MAX:
+        return None
+    try:
+        with _alloc_on(stream):
+            return torch.empty((nbytes.value,), device=X.device, dtype=torch.uint8)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
 def discretize(cm: CisModel, X, U, s, params, K, *, with_xprop=True, layout="rule",
                stream=None):
-    """A, Bm, Bp, S, defect (and F~) of every interval, written by one kernel launch.
-    layout: one of LAYOUTS ("rule": chosen from N and the device's CU count)."""
+    """A, Bm, Bp, S, defect (and F~) of every interval.  layout: one of LAYOUTS
+    ("rule": chosen from N and the device's CU count; past the counts that one
+    launch serves best, the two-launch form, while its workspace stays within
+    SPLIT_WS_MAX and can be had)."""
     _check_inputs(cm, X, U, s, params)
     N, nx, m = s.shape[0], cm.nx, cm.m
     kw = dict(device=X.device, dtype=X.dtype)
+    if layout == "rule":
+        ws = _split_workspace(cm, X, s, K, stream)
+        if ws is not None:
+            return discretize_split(cm, X, U, s, params, K, with_xprop=with_xprop, ws=ws,
+                                    stream=stream)
     with _alloc_on(stream):
         out = dict(A=torch.empty((nx, nx, N), **kw), Bm=torch.empty((nx, m, N), **kw),
                    Bp=torch.empty((nx, m, N), **kw), S=torch.empty((nx, N), **kw),

@@ -814,6 +814,23 @@ static cis_status launch_discretize(const cis_model* m, const cis_shape* sh, con
     return launch_discretize_as<T, TT>(m, sh, X, U, s, prm, A, Bm, Bp, S, d, xp, stream);
 }
 
+// The two-launch form is the faster one past the narrow layout, where the throughput
+// layout starts (us, one launch and two at the counts on either side; K = 20 / 5):
+//   quad13 FP64    N = 32: 102 and 114 / 34 and 41     64: 181 and 116 / 59 and 43
+//   cheetah7 FP64  128: 96 and 97 / 32 and 34          160: 130 and 97 / 43 and 35
+//   biped5 FP64    128: 111 and 138 / 35 and 45        160: 149 and 138 / 45 and 45
+//   hopper FP64    256: 61 and 87 / 24 and 30          320: 172 and 87 / 51 and 30
+//   quad13 FP32    128: 98 and 97 / 38 and 46          160: 186 and 98 / 65 and 46
+//   biped5 FP32    256: 64 and 111 / 25 and 37         320: 196 and 111 / 60 and 37
+// and a round of workgroups later where FP32 columns fill one wave (hopper at 320:
+// 69 and 66 / 24 and 28).
+template <class T, int L, int D>
+static bool prefers_split(int N) {
+    using TN = NarrowTopo<T, L, D>;
+    const int64_t cus = device_cus();
+    return (int64_t)N * TN::NGRP > (sizeof(T) == 4 && TN::NTW_ALL == 1 ? 2 * cus : cus);
+}
+
 template <class T, int L, int D>
 static cis_status launch_defects(const cis_model* m, const cis_shape* sh, const void* X,
                                  const void* U, const void* s, const void* prm, void* d,
@@ -1018,6 +1035,21 @@ static cis_status discretize_impl(const cis_model* model, const cis_shape* shape
     CIS_TOPOLOGIES(CIS_DISPATCH_DISC)
 #undef CIS_DISPATCH_DISC
     return fail(CIS_ERR_UNSUPPORTED, "cis_discretize: topology has no compiled kernel");
+}
+
+extern "C" cis_status cis_discretize_prefers_split(const cis_model* model, const cis_shape* shape,
+                                                   int32_t* split) {
+    if (!model || !shape || !split)
+        return fail(CIS_ERR_NULL, "cis_discretize_prefers_split: null argument");
+    *split = 0;
+    if (shape->layout != 0 || !split_form_supported(model)) return CIS_OK;
+#define CIS_PREFERS(LL, DD)                                                           \
+    if (model->L == LL && model->D == DD)                                             \
+        *split = (shape->dtype == CIS_F64 ? prefers_split<double, LL, DD>(shape->N)    \
+                                          : prefers_split<float, LL, DD>(shape->N)) ? 1 : 0;
+    CIS_TOPOLOGIES(CIS_PREFERS)
+#undef CIS_PREFERS
+    return CIS_OK;
 }
 
 // Debug mode (CIS_DEBUG_FINITE): the non-finite scan after the launch.
