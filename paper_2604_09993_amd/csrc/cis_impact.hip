@@ -3,17 +3,21 @@
 // elimination of the joint impulse that follows it; Sec. IV-C eq. FB-relax,
 // eq. cito-impulse and the constraint families Theta^delta and Psi^{delta,eps}).
 //
-// One wave per node.  Per node the joint-impulse system
-//     A Lambda = -grad h M^-1 (M v- + J^T R Phi),   A = grad h M^-1 grad h^T,
-// is solved once by Gauss-Jordan elimination with one lane per column of the
-// augmented matrix [A | grad h M^-1 | grad h f]: the pivot column is broadcast
-// with lane reads, so the elimination runs in registers.  It leaves
-// X = A^-1 grad h M^-1 (whose transpose is W = M^-1 grad h^T A^-1) and Lambda.
-// Every Jacobian column of the velocity jump then follows from the identity
-//     dv* = du - W (dgrad_h v* + grad h du),
-// where du = df + d(M^-1) grad h^T Lambda + M^-1 dgrad_h^T Lambda lives on the
-// one body a direction touches and dgrad_h on the joints at that body, so a
-// lane forms its column from at most max(L, 2) joint columns of W.  The
+// One wave per node.  The joint impulses are eliminated leg by leg: grad h v* = 0 gives
+// every link's translation from the torso's velocity a0 = (v_0, w_0) and the angular
+// velocities of its leg,
+//     v_l = v_0 + w_0 E a_p1 + sum_{i<=l} w_i E r_li,  r_li = a_p,i+1 - a_c,i (i < l),
+//     r_ll = -a_c,l,  E a = (-a_y, a_x),
+// and the momenta along the w_i leave, per leg, H w = f - H0 a0 (as many rows as the leg
+// has links) and a 3 x 3 system of the torso.  So v* = T a0 + (the leg's own response),
+// with T the motion of every body row under the torso's.
+// A Jacobian column of the velocity jump touches one body: its momenta m du, du = df +
+// d(M^-1) grad h^T Lambda + M^-1 dgrad_h^T Lambda, and for an angle the change of grad h
+// act on that body's leg, and the rest of the machine follows through T.  One lane
+// forms a column: the response of one leg, the torso's, then three products a row.
+// Bound by FP64 issue up to some thousand nodes (4,000 quad13 nodes: 98 -> 44 us), then
+// by the stores (470 MB of 12,864 nodes: 252 -> 182 us); before, a Gauss-Jordan
+// elimination of the 24 joint rows and eight products a row.  The
 // impact conditions of a contact depend on 14 node variables; one lane per
 // (contact, variable) evaluates them in dual numbers.
 #include <hip/hip_runtime.h>
@@ -24,6 +28,7 @@
 #include "../../include/cis.h"
 #include "cis_host.hpp"
 #include "cis_model.hpp"
+#include "cis_reduced.hpp"
 
 namespace cis {
 
@@ -32,11 +37,12 @@ struct ImpTopo {
     static constexpr int L = L_, D = D_;
     static constexpr int NB = 1 + L * D, NJ = L * D, NC = L;
     static constexpr int NQ = 3 * NB, NY = NC + 1, NXT = 6 * NB + NY;
-    static constexpr int NJ2 = 2 * NJ, P = NB + 2;
+    static constexpr int NJ2 = 2 * NJ, P = NB + 2, DM = cmax(D, 1), LM = cmax(L, 1);
+    static constexpr int NTV = (3 * NQ + 15) / 16;     // T in vectors of 16
+    static constexpr int NQP = NQ + (NQ & 1);          // row stride of X in LDS
     static constexpr int NCV = 2 * NQ + 2 * NC + NB;   // columns of JGv
     static constexpr int NTH = 10 * NC;                // rows of Theta
     static constexpr int NCT = 14;                     // columns of JTc
-    static constexpr int NQP = NQ + (NQ & 1);          // row stride of X in LDS
     static constexpr int ADJ = L > 2 ? L : 2;          // joints at one body, at most
     static constexpr int NIN = 2 * NXT + 3 * NC;       // node inputs (x+, x-, Phi, Gamma)
     static_assert(NJ2 + NQ + 1 <= 64, "one lane per column of the augmented system");
@@ -81,12 +87,13 @@ __device__ __forceinline__ Dual operator*(Dual a, Dual b) {
 }
 __device__ __forceinline__ Dual operator*(double a, Dual b) { return {a * b.v, a * b.d}; }
 __device__ __forceinline__ Dual operator/(Dual a, Dual b) {
-    const double q = a.v / b.v;
-    return {q, (a.d - q * b.d) / b.v};
+    const double r = 1.0 / b.v, q0 = a.v * r, q = fma(fma(-q0, b.v, a.v), r, q0);
+    return {q, (a.d - q * b.d) * r};
 }
 __device__ __forceinline__ Dual dsqrt(Dual a) {   // a.v > 0 wherever it is used
-    const double s = sqrt(a.v);
-    return {s, a.d / (2.0 * s)};
+    // hardware estimate, two residual steps, and one on the root itself
+    const double y = rsqrt_t(a.v), s = a.v * y;
+    return {fma(fma(-s, s, a.v), 0.5 * y, s), a.d * (0.5 * y)};
 }
 __device__ __forceinline__ void dsincos(Dual a, Dual& s, Dual& c) {
     double sv, cv;
@@ -113,10 +120,12 @@ __device__ __forceinline__ void frame_d(const MC& mc, Dual Px, Dual Py, Dual& sd
     dsincos(mc.kappa * Px, sw, cw);
     const Dual H = Py - mc.A * sw;
     const Dual Hx = (-mc.A * mc.kappa) * cw;
-    const Dual G = dsqrt(dn(1.0) + Hx * Hx);
-    sd = H / G;
-    nx = Hx / G;
-    ny = dn(1.0) / G;
+    const Dual w = dn(1.0) + Hx * Hx;
+    const double y = rsqrt_t(w.v);
+    const Dual rG = dn(y, -0.5 * (y * y * y) * w.d);   // 1 / ||grad h||
+    sd = H * rG;
+    nx = Hx * rG;
+    ny = rG;
     tx = ny;
     ty = -nx;
 }
@@ -139,6 +148,16 @@ __device__ __forceinline__ void contact_wrench(const MC& mc, int i, Dual x, Dual
 }
 
 template <class TP>
+struct ImpLegs {
+    // links: r_li (l > i), sum_{l >= i} m_l r_li, their momenta's f, then w of the node
+    double rho[cmax(TP::NJ, 1)][2], sig[cmax(TP::NJ, 1)][2], hd[cmax(TP::NJ, 1)];
+    double fg[cmax(TP::NJ, 1)], w[cmax(TP::NJ, 1)];
+    double Hi[TP::LM][TP::DM][TP::DM], G[TP::LM][TP::DM][3];   // H^-1, H^-1 H0
+    double S[TP::LM][9];                // the legs' parts of the torso's system
+    double T[16 * TP::NTV];             // [NQ][3]
+};
+
+template <class TP>
 struct ImpShared {
     double z[TP::NIN];                  // x+ | x- | Phi | Gamma of the node
     double ynext[TP::NY];               // integral states of x- at the next node
@@ -150,7 +169,10 @@ struct ImpShared {
     double f[TP::NQ];                   // v- + M^-1 J^T R Phi
     double vs[TP::NQ];                  // v*
     double lam[cmax(TP::NJ2, 1)];       // Lambda
-    double X[cmax(TP::NJ2, 1)][TP::NQP];   // A^-1 grad h M^-1
+    union {
+        ImpLegs<TP> leg;
+        double X[cmax(TP::NJ2, 1)][TP::NQP];   // A^-1 grad h M^-1 (heavy bodies)
+    };
     double dw[cmax(TP::NC, 1)][5][3];   // d(contact wrench)/d(x_b, y_b, th_b, Phi_t, Phi_n)
 };
 
@@ -183,10 +205,79 @@ struct ImpactArgs {
     double delta, eps;
 };
 
+// A link far heavier than the rest (or fixed: an infinite mass) cancels in the torso's
+// system, which is a difference; the joint rows' system takes 1/m and stays exact.
+// It is kept for that case with its columns in memory (the node's part of JGv), so
+// that the kernel's registers are those of the other form.
 template <class TP>
-__global__ void __launch_bounds__(64) k_impact(ImpactArgs a, MConst<TP::NB, TP::NJ, TP::NC> mc) {
+__device__ __forceinline__ bool heavy_body(const double* prm) {
+    double lo = prm[2], hi = lo;
+#pragma unroll
+    for (int b = 1; b < TP::NB; ++b) {
+        const double m = prm[2 + b];
+        lo = m < lo ? m : lo;
+        hi = m > hi ? m : hi;
+    }
+    return __builtin_amdgcn_readfirstlane(hi < 1e4 * lo ? 0 : 1) != 0;
+}
+
+// X = A^-1 grad h M^-1, A = grad h M^-1 grad h^T, and Lambda = -A^-1 grad h f by
+// Gauss-Jordan elimination of [A | grad h M^-1 | grad h f], a lane per column, the
+// pivot column by lane reads; then v* = f + M^-1 grad h^T Lambda.
+template <class TP>
+__device__ __forceinline__ void impact_dense(ImpShared<TP>& sh, double* cols, int lane) {
+    constexpr int NJ = TP::NJ, NJ2 = TP::NJ2, NQ = TP::NQ, W = NJ2 + NQ + 1;
+    static_assert(NJ2 * W <= NQ * TP::NCV, "the columns fit the node's Jacobian");
+    const int l = lane < W ? lane : W - 1;   // (spare lanes repeat the last column)
+    double* col = cols + l;
+    // entry r of grad h^T row j2 (joint j2 / 2, component j2 & 1)
+    auto jrow = [&](int j2, int r) {
+        const int j = j2 >> 1, c = j2 & 1, b = r / 3, q = r - 3 * b;
+        const double ep = c == 0 ? -sh.arm[j][1] : sh.arm[j][0];
+        const double ec = c == 0 ? -sh.arm[j][3] : sh.arm[j][2];
+        if (b == TP::parent(j)) return q == c ? 1.0 : (q == 2 ? ep : 0.0);
+        if (b == j + 1) return q == c ? -1.0 : (q == 2 ? -ec : 0.0);
+        return 0.0;
+    };
+    auto y = [&](int r) {
+        if (l < NJ2) return sh.minv[r] * jrow(l, r);
+        if (l < NJ2 + NQ) return l - NJ2 == r ? sh.minv[r] : 0.0;
+        return sh.f[r];
+    };
+#pragma unroll 1
+    for (int i = 0; i < NJ2; ++i) {
+        const int j = i >> 1, c = i & 1, p = TP::parent(j), ch = j + 1;
+        const double ep = c == 0 ? -sh.arm[j][1] : sh.arm[j][0];
+        const double ec = c == 0 ? -sh.arm[j][3] : sh.arm[j][2];
+        col[i * W] = (y(3 * p + c) + y(3 * p + 2) * ep) - (y(3 * ch + c) + y(3 * ch + 2) * ec);
+    }
+#pragma unroll 1
+    for (int kk = 0; kk < NJ2; ++kk) {
+        const double own = col[kk * W], t = own / bcast(own, kk);
+#pragma unroll 1
+        for (int i = 0; i < NJ2; ++i) {
+            const double v = col[i * W];
+            col[i * W] = i == kk ? t : fma(-bcast(v, kk), t, v);
+        }
+    }
+    if (lane >= NJ2 && lane < NJ2 + NQ)
+        for (int i = 0; i < NJ2; ++i) sh.X[i][lane - NJ2] = col[i * W];
+    if (lane == NJ2 + NQ)
+        for (int i = 0; i < NJ2; ++i) sh.lam[i] = -col[i * W];
+    lds_sync();
+    if (lane < NQ) {
+        double jt = 0.0;
+#pragma unroll 1
+        for (int i = 0; i < NJ2; ++i) jt += jrow(i, lane) * sh.lam[i];
+        sh.vs[lane] = sh.f[lane] + sh.minv[lane] * jt;
+    }
+}
+
+template <class TP>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
+    k_impact(ImpactArgs a, MConst<TP::NB, TP::NJ, TP::NC> mc) {
     constexpr int NB = TP::NB, NJ = TP::NJ, NC = TP::NC, NQ = TP::NQ, NY = TP::NY;
-    constexpr int NXT = TP::NXT, NJ2 = TP::NJ2, NCV = TP::NCV, NIN = TP::NIN;
+    constexpr int NXT = TP::NXT, NCV = TP::NCV, NIN = TP::NIN;
     __shared__ ImpShared<TP> sh;
     const int lane = threadIdx.x;
     const int k = xcd_slot(blockIdx.x, gridDim.x);
@@ -261,74 +352,159 @@ __global__ void __launch_bounds__(64) k_impact(ImpactArgs a, MConst<TP::NB, TP::
     }
     lds_sync();
 
-    // ---- joint impulse: Gauss-Jordan on [A | grad h M^-1 | grad h f] --------
+    // ---- v* = f + M^-1 grad h^T Lambda, grad h v* = 0 ------------------------
+    const bool heavy = NJ > 0 && heavy_body<TP>(sh.prm);
+    double si[3][3], Z[3] = {0.0, 0.0, 0.0};   // the torso's inverse; its system by a_p1
     if constexpr (NJ > 0) {
-        // grad h row l (joint l/2, component l&1) restricted to body coordinate r
-        double y[NQ];
-        {
-            const int jl = (lane < NJ2 ? lane : 0) >> 1, cl = lane & 1;
-            const int pl = TP::parent(jl), chl = jl + 1;
-            // (E a)_c with E a = (-a_y, a_x)
-            const double eap = cl == 0 ? -sh.arm[jl][1] : sh.arm[jl][0];
-            const double eac = cl == 0 ? -sh.arm[jl][3] : sh.arm[jl][2];
+        if (heavy) {
+            impact_dense<TP>(sh, a.JGv + (int64_t)k * NQ * NCV, lane);
+        } else {
+            constexpr int D = TP::D, L = TP::L;
+            const double* mass = sh.prm + 2;
+            if (lane < NJ) {
+                const int c = lane + 1, lk = lane % D;
+                const double m = mass[c], I = m * mc.ipm[c];
+                const double acx = sh.arm[lane][2], acy = sh.arm[lane][3];
+                double msub = 0.0, qx = 0.0, qy = 0.0;   // links beyond: mass, momentum
 #pragma unroll
-            for (int r = 0; r < NQ; ++r) {
-                const int b = r / 3, q = r % 3;
-                double row = 0.0;
-                if (b == pl) row += q == cl ? 1.0 : (q == 2 ? eap : 0.0);
-                if (b == chl) row -= q == cl ? 1.0 : (q == 2 ? eac : 0.0);
-                const double mi = sh.minv[r];
-                y[r] = lane < NJ2 ? mi * row
-                     : lane < NJ2 + NQ ? (lane - NJ2 == r ? mi : 0.0)
-                                       : sh.f[r];
+                for (int e = 1; e < D; ++e)
+                    if (lk + e < D) {
+                        const double me = mass[c + e];
+                        msub += me;
+                        qx += me * sh.f[3 * (c + e)];
+                        qy += me * sh.f[3 * (c + e) + 1];
+                    }
+                const bool inner = lk + 1 < D;
+                const int nx = inner ? lane + 1 : lane;
+                const double rx = inner ? sh.arm[nx][0] - acx : 0.0;
+                const double ry = inner ? sh.arm[nx][1] - acy : 0.0;
+                const double px = m * sh.f[3 * c], py = m * sh.f[3 * c + 1];
+                sh.leg.rho[lane][0] = rx;
+                sh.leg.rho[lane][1] = ry;
+                sh.leg.sig[lane][0] = msub * rx - m * acx;
+                sh.leg.sig[lane][1] = msub * ry - m * acy;
+                sh.leg.hd[lane] = I + m * (acx * acx + acy * acy) + msub * (rx * rx + ry * ry);
+                sh.leg.fg[lane] = I * sh.f[3 * c + 2] + (acy * px - acx * py) + (rx * qy - ry * qx);
+            }
+            lds_sync();
+            if (lane < L) {   // a leg's system
+                const int j0 = lane * D;
+                const double a1x = sh.arm[j0][0], a1y = sh.arm[j0][1];
+                double H[D][D], H0[D][3], f[D], ml = 0.0, tx = 0.0, ty = 0.0;
+#pragma unroll
+                for (int i = 0; i < D; ++i) {
+                    const double ex = sh.leg.sig[j0 + i][0], ey = sh.leg.sig[j0 + i][1];
+                    H[i][i] = sh.leg.hd[j0 + i];
+                    f[i] = sh.leg.fg[j0 + i];
+                    H0[i][0] = -ey;
+                    H0[i][1] = ex;
+                    H0[i][2] = ex * a1x + ey * a1y;
+#pragma unroll
+                    for (int l = i + 1; l < D; ++l)
+                        H[i][l] = H[l][i] = sh.leg.rho[j0 + i][0] * sh.leg.sig[j0 + l][0] +
+                                            sh.leg.rho[j0 + i][1] * sh.leg.sig[j0 + l][1];
+                    const double m = mass[j0 + i + 1];
+                    ml += m;
+                    tx += m * sh.f[3 * (j0 + i + 1)];
+                    ty += m * sh.f[3 * (j0 + i + 1) + 1];
+                }
+                spd_inverse<D>(H);
+                double S[9] = {ml, 0.0, -ml * a1y, ml, ml * a1x, ml * (a1x * a1x + a1y * a1y),
+                               tx, ty, a1x * ty - a1y * tx};
+#pragma unroll
+                for (int i = 0; i < D; ++i) {
+                    double y = 0.0, g[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int l = 0; l < D; ++l) {
+                        y += H[i][l] * f[l];
+#pragma unroll
+                        for (int e = 0; e < 3; ++e) g[e] += H[i][l] * H0[l][e];
+                        sh.leg.Hi[lane][i][l] = H[i][l];
+                    }
+                    sh.leg.w[j0 + i] = y;
+                    S[0] -= H0[i][0] * g[0];
+                    S[1] -= H0[i][0] * g[1];
+                    S[2] -= H0[i][0] * g[2];
+                    S[3] -= H0[i][1] * g[1];
+                    S[4] -= H0[i][1] * g[2];
+                    S[5] -= H0[i][2] * g[2];
+#pragma unroll
+                    for (int e = 0; e < 3; ++e) {
+                        S[6 + e] -= H0[i][e] * y;
+                        sh.leg.G[lane][i][e] = g[e];
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 9; ++e) sh.leg.S[lane][e] = S[e];
+            }
+            lds_sync();
+            double s[9] = {mass[0], 0.0, 0.0, mass[0], 0.0, mass[0] * mc.ipm[0],
+                           mass[0] * sh.f[0], mass[0] * sh.f[1], mass[0] * mc.ipm[0] * sh.f[2]};
+#pragma unroll
+            for (int l = 0; l < L; ++l) {
+                double v[9];
+#pragma unroll
+                for (int e = 0; e < 9; ++e) {
+                    v[e] = sh.leg.S[l][e];
+                    s[e] += v[e];
+                }
+                const double ax = sh.arm[l * D][0], ay = sh.arm[l * D][1];
+                Z[0] += v[0] * ax + v[1] * ay;
+                Z[1] += v[1] * ax + v[3] * ay;
+                Z[2] += v[2] * ax + v[4] * ay;
+            }
+            si[0][0] = s[0];
+            si[1][1] = s[3];
+            si[2][2] = s[5];
+            si[0][1] = si[1][0] = s[1];
+            si[0][2] = si[2][0] = s[2];
+            si[1][2] = si[2][1] = s[4];
+            spd_inverse<3>(si);
+            double a0[3];
+#pragma unroll
+            for (int e = 0; e < 3; ++e) a0[e] = si[e][0] * s[6] + si[e][1] * s[7] + si[e][2] * s[8];
+            if (lane < NQ) {
+                const int b = lane / 3, q = lane - 3 * b;
+                const int leg = b > 0 ? (b - 1) / D : 0, lk = b > 0 ? (b - 1) % D : 0, j0 = leg * D;
+                double t[3] = {q == 0 ? 1.0 : 0.0, q == 1 ? 1.0 : 0.0, q == 2 ? 1.0 : 0.0}, own = 0.0;
+                if (b > 0) {
+                    t[2] = q == 0 ? -sh.arm[j0][1] : (q == 1 ? sh.arm[j0][0] : 0.0);
+#pragma unroll
+                    for (int i = 0; i < D; ++i) {
+                        // row of E r_li (or the angle itself)
+                        const double rx = i < lk ? sh.leg.rho[j0 + i][0] : -sh.arm[j0 + i][2];
+                        const double ry = i < lk ? sh.leg.rho[j0 + i][1] : -sh.arm[j0 + i][3];
+                        double er = q == 0 ? -ry : (q == 1 ? rx : 0.0);
+                        if (i > lk) er = 0.0;
+                        if (q == 2 && i == lk) er = 1.0;
+                        own += er * sh.leg.w[j0 + i];
+#pragma unroll
+                        for (int e = 0; e < 3; ++e) t[e] -= er * sh.leg.G[leg][i][e];
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 3; ++e) sh.leg.T[3 * lane + e] = t[e];
+                sh.vs[lane] = (t[0] * a0[0] + t[1] * a0[1] + t[2] * a0[2]) + own;
+            }
+            lds_sync();
+            if (lane < NJ) {   // joint impulses, from the tip
+                double lx = 0.0, ly = 0.0;
+#pragma unroll
+                for (int e = D - 1; e >= 0; --e)
+                    if (lane % D + e < D) {
+                        const int r = 3 * (lane + 1 + e);
+                        lx += mass[lane + 1 + e] * (sh.f[r] - sh.vs[r]);
+                        ly += mass[lane + 1 + e] * (sh.f[r + 1] - sh.vs[r + 1]);
+                    }
+                sh.lam[2 * lane] = lx;
+                sh.lam[2 * lane + 1] = ly;
             }
         }
-        double col[NJ2];
-#pragma unroll
-        for (int i = 0; i < NJ2; ++i) {
-            const int j = i >> 1, c = i & 1, p = TP::parent(j), ch = j + 1;
-            const double eap = c == 0 ? -sh.arm[j][1] : sh.arm[j][0];
-            const double eac = c == 0 ? -sh.arm[j][3] : sh.arm[j][2];
-            col[i] = (y[3 * p + c] + y[3 * p + 2] * eap) - (y[3 * ch + c] + y[3 * ch + 2] * eac);
-        }
-#pragma unroll
-        for (int kk = 0; kk < NJ2; ++kk) {
-            double piv[NJ2];
-#pragma unroll
-            for (int i = 0; i < NJ2; ++i) piv[i] = bcast(col[i], kk);
-            const double t = col[kk] / piv[kk];
-#pragma unroll
-            for (int i = 0; i < NJ2; ++i) col[i] = i == kk ? t : fma(-piv[i], t, col[i]);
-        }
-        if (lane >= NJ2 && lane < NJ2 + NQ) {
-#pragma unroll
-            for (int i = 0; i < NJ2; ++i) sh.X[i][lane - NJ2] = col[i];
-        }
-        if (lane == NJ2 + NQ) {
-#pragma unroll
-            for (int i = 0; i < NJ2; ++i) sh.lam[i] = -col[i];
-        }
-        lds_sync();
-    }
-
-    // ---- v* = f + M^-1 grad h^T Lambda; node residual G~ --------------------
-    if (lane < NQ) {
-        const int b = lane / 3, q = lane - 3 * b;
-        double jt = 0.0;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int p = TP::parent(j), ch = j + 1;
-            const double lx = sh.lam[2 * j], ly = sh.lam[2 * j + 1];
-            const double tp = sh.arm[j][0] * ly - sh.arm[j][1] * lx;   // a_p x Lambda_j
-            const double tc = sh.arm[j][2] * ly - sh.arm[j][3] * lx;
-            const double vpar = q == 0 ? lx : (q == 1 ? ly : tp);
-            const double vch = q == 0 ? lx : (q == 1 ? ly : tc);
-            if (b == p) jt += vpar;
-            if (b == ch) jt -= vch;
-        }
-        sh.vs[lane] = sh.f[lane] + sh.minv[lane] * jt;
+    } else {
+        if (lane < NQ) sh.vs[lane] = sh.f[lane];
     }
     lds_sync();
+    // ---- node residual G~ ---------------------------------------------------
     {
         double* Gk = a.G + (int64_t)k * NXT;
         for (int r = lane; r < NXT; r += 64) {
@@ -345,10 +521,14 @@ __global__ void __launch_bounds__(64) k_impact(ImpactArgs a, MConst<TP::NB, TP::
 
     // ---- JGv: columns of dG~_v / d(q+, v-, Phi, masses) ---------------------
     double* Jk = a.JGv + (int64_t)k * NQ * NCV;
+    double tv[TP::NTV];   // T, element lane & 15 of each vector
+    if constexpr (NJ > 0)
+#pragma unroll
+        for (int q = 0; q < TP::NTV; ++q) tv[q] = heavy ? 0.0 : sh.leg.T[16 * q + (lane & 15)];
 #pragma unroll 1
     for (int c0 = 0; c0 < NCV; c0 += 64) {
-        const int cj = c0 + lane;
-        if (cj >= NCV) break;
+        // (spare lanes repeat the last column: T's broadcasts need every lane)
+        const int cj = c0 + lane < NCV ? c0 + lane : NCV - 1;
         int b, kind, comp;   // kind 0: q+, 1: v-, 2: Phi, 3: mass
         if (cj < NQ) { kind = 0; b = cj / 3; comp = cj % 3; }
         else if (cj < 2 * NQ) { kind = 1; b = (cj - NQ) / 3; comp = (cj - NQ) % 3; }
@@ -370,16 +550,52 @@ __global__ void __launch_bounds__(64) k_impact(ImpactArgs a, MConst<TP::NB, TP::
             for (int q = 0; q < 3; ++q) du[q] = -(sh.vs[3 * b + q] - vm[3 * b + q]) * rm;
         }
         const bool thdir = kind == 0 && comp == 2;
-        // joints at b: d(grad h)^T Lambda (angle direction) and the columns of W
-        int js[TP::ADJ];
-        double bx[TP::ADJ], by[TP::ADJ];
-        if constexpr (NJ > 0) {
+        if constexpr (NJ == 0) {
+#pragma unroll
+            for (int r = 0; r < NQ; ++r)
+                Jk[(int64_t)r * NCV + cj] = (r / 3 == b) ? -du[r % 3] : 0.0;
+        } else if (heavy) {
+            // joints at b: d(grad h)^T Lambda (angle direction), grad h du + d(grad h) v*
+            double dtq = 0.0;
+            auto slot = [&](int q, bool& par, double& ax, double& ay) {
+                const int j = TP::slot_joint(b, q, par);
+                if (j >= 0) {
+                    ax = par ? sh.arm[j][0] : sh.arm[j][2];
+                    ay = par ? sh.arm[j][1] : sh.arm[j][3];
+                }
+                return j;
+            };
+            bool par;
+            double ax = 0.0, ay = 0.0;
+            for (int q = 0; q < TP::ADJ; ++q) {
+                const int j = slot(q, par, ax, ay);
+                if (j >= 0 && thdir)   // d(E a)/dth = -a: parent side -a_p, child side +a_c
+                    dtq += (par ? -1.0 : 1.0) * (ax * sh.lam[2 * j] + ay * sh.lam[2 * j + 1]);
+            }
+            du[2] += sh.minv[3 * b + 2] * dtq;
+            const double om = thdir ? sh.vs[3 * b + 2] : 0.0;
+#pragma unroll 1
+            for (int r = 0; r < NQ; ++r) {
+                const int q3 = r % 3;
+                double acc = r / 3 != b ? 0.0 : (q3 == 0 ? -du[0] : (q3 == 1 ? -du[1] : -du[2]));
+                for (int q = 0; q < TP::ADJ; ++q) {
+                    const int j = slot(q, par, ax, ay);
+                    if (j < 0) continue;
+                    const double sg = par ? 1.0 : -1.0;
+                    const double bx = sg * ((du[0] - du[2] * ay) - ax * om);
+                    const double by = sg * ((du[1] + du[2] * ax) - ay * om);
+                    acc = fma(sh.X[2 * j][r], bx, fma(sh.X[2 * j + 1][r], by, acc));
+                }
+                Jk[(int64_t)r * NCV + cj] = acc;
+            }
+        } else {
+            constexpr int D = TP::D, L = TP::L;
+            // joints at b: d(grad h)^T Lambda (angle direction)
             double dtq = 0.0;
 #pragma unroll
             for (int s = 0; s < TP::ADJ; ++s) {
                 bool par;
                 const int j = TP::slot_joint(b, s, par);
-                js[s] = j < 0 ? 0 : j;
                 if (j >= 0 && thdir) {
                     // d(E a)/dth = -a: parent side -a_p, child side +a_c
                     const double ax = par ? -sh.arm[j][0] : sh.arm[j][2];
@@ -387,38 +603,76 @@ __global__ void __launch_bounds__(64) k_impact(ImpactArgs a, MConst<TP::NB, TP::
                     dtq += ax * sh.lam[2 * j] + ay * sh.lam[2 * j + 1];
                 }
             }
-            du[2] += sh.minv[3 * b + 2] * dtq;
-            const double om = sh.vs[3 * b + 2];
+            const double m = sh.prm[2 + b], I = m * mc.ipm[b];
+            const double Fx = m * du[0], Fy = m * du[1], Tq = I * du[2] + dtq;
+            // turning a link by dth moves the links from it on by -w dth r, a torso
+            // the first joints by -w dth a_p
+            const double w = thdir ? sh.vs[3 * b + 2] : 0.0;
+            const bool link = b > 0;
+            const int leg = link ? (b - 1) / D : 0, lk = link ? (b - 1) % D : 0, j0 = leg * D;
+            const int jb = j0 + lk;
+            const double lx = link ? Fx : 0.0, ly = link ? Fy : 0.0, lt = link ? Tq : 0.0;
+            const double wl = link ? w : 0.0, w0 = link ? 0.0 : w;
+            const double rbx = sh.leg.rho[jb][0], rby = sh.leg.rho[jb][1];
+            const double gx = fma(wl, sh.leg.sig[jb][0], lx), gy = fma(wl, sh.leg.sig[jb][1], ly);
+            const double acx = sh.arm[jb][2], acy = sh.arm[jb][3];
+            const double a1x = sh.arm[j0][0], a1y = sh.arm[j0][1];
+            double f[D], R[3], rx[D], ry[D], cx[D], cy[D];
 #pragma unroll
-            for (int s = 0; s < TP::ADJ; ++s) {
-                bool par;
-                const int j = TP::slot_joint(b, s, par);
-                double vx = 0.0, vy = 0.0;
-                if (j >= 0) {
-                    const double ax = par ? sh.arm[j][0] : sh.arm[j][2];
-                    const double ay = par ? sh.arm[j][1] : sh.arm[j][3];
-                    const double sg = par ? 1.0 : -1.0;
-                    // grad h_j du  (+ d(grad h_j) v* for the angle direction)
-                    vx = sg * (du[0] - du[2] * ay);
-                    vy = sg * (du[1] + du[2] * ax);
-                    if (thdir) {
-                        vx -= sg * ax * om;
-                        vy -= sg * ay * om;
-                    }
-                }
-                bx[s] = vx;
-                by[s] = vy;
+            for (int i = 0; i < D; ++i) {
+                rx[i] = sh.leg.rho[j0 + i][0];
+                ry[i] = sh.leg.rho[j0 + i][1];
+                cx[i] = sh.arm[j0 + i][2];
+                cy[i] = sh.arm[j0 + i][3];
+                const double ax = i < lk ? rx[i] : sh.leg.sig[j0 + i][0];
+                const double ay = i < lk ? ry[i] : sh.leg.sig[j0 + i][1];
+                const double bx = i < lk ? gx : wl * rbx, by = i < lk ? gy : wl * rby;
+                f[i] = i == lk ? lt + (acy * lx - acx * ly) : ax * by - ay * bx;
             }
-        }
+            R[0] = link ? gx : Fx + w0 * Z[0];
+            R[1] = link ? gy : Fy + w0 * Z[1];
+            R[2] = link ? a1x * gy - a1y * gx : Tq + w0 * Z[2];
+            double y[D];
 #pragma unroll
-        for (int r = 0; r < NQ; ++r) {
-            double acc = (r / 3 == b) ? -du[r % 3] : 0.0;
-            if constexpr (NJ > 0) {
+            for (int i = 0; i < D; ++i) {
+                y[i] = 0.0;
 #pragma unroll
-                for (int s = 0; s < TP::ADJ; ++s)
-                    acc = fma(sh.X[2 * js[s]][r], bx[s], fma(sh.X[2 * js[s] + 1][r], by[s], acc));
+                for (int l = 0; l < D; ++l) y[i] += sh.leg.Hi[leg][i][l] * f[l];
+#pragma unroll
+                for (int e = 0; e < 3; ++e) R[e] -= sh.leg.G[leg][i][e] * f[i];
             }
-            Jk[(int64_t)r * NCV + cj] = acc;
+            double n0[3];   // -a0
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                n0[e] = -(si[e][0] * R[0] + si[e][1] * R[1] + si[e][2] * R[2]);
+            // the leg's own response
+            double own[3 * D], sx = 0.0, sy = 0.0;
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                const double mx = i == lk ? wl * acx : (i > lk ? -wl * rbx : 0.0);
+                const double my = i == lk ? wl * acy : (i > lk ? -wl * rby : 0.0);
+                own[3 * i] = mx + (sx + cy[i] * y[i]);
+                own[3 * i + 1] = my + (sy - cx[i] * y[i]);
+                own[3 * i + 2] = y[i];
+                sx -= ry[i] * y[i];
+                sy += rx[i] * y[i];
+            }
+#pragma unroll
+            for (int r = 0; r < 3; ++r) Jk[(int64_t)r * NCV + cj] = n0[r];
+            unrolled<L>([&](auto l_c) {
+                constexpr int l = decltype(l_c)::value;
+                const double on = link && leg == l ? -1.0 : 0.0;
+                const double nx = fma(w0, sh.arm[l * D][0], n0[0]);
+                const double ny = fma(w0, sh.arm[l * D][1], n0[1]);
+                unrolled<3 * D>([&](auto q_c) {
+                    constexpr int r = 3 + 3 * D * l + decltype(q_c)::value, t = 3 * r;
+                    double acc = on * own[decltype(q_c)::value];
+                    fma_row<t & 15>(acc, tv[t >> 4], nx);
+                    fma_row<(t + 1) & 15>(acc, tv[(t + 1) >> 4], ny);
+                    fma_row<(t + 2) & 15>(acc, tv[(t + 2) >> 4], n0[2]);
+                    Jk[(int64_t)r * NCV + cj] = acc;
+                });
+            });
         }
     }
 

@@ -181,6 +181,28 @@ struct PackConst {
     Pair v[N][64];
 };
 
+// a <- a^-1 (symmetric positive definite, without pivoting)
+template <int N>
+__device__ __forceinline__ void spd_inverse(double (&a)[N][N]) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const double p = 1.0 / a[k][k];
+        a[k][k] = p;
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            if (j != k) a[k][j] *= p;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if (i == k) continue;
+            const double t = a[i][k];
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+                if (j != k) a[i][j] = fma(-t, a[k][j], a[i][j]);
+            a[i][k] = -t * p;
+        }
+    }
+}
+
 // Body lane of one of the wave's four intervals (lane & 15 is the body) and its
 // place in the tree.
 template <class T, class TP>

@@ -109,28 +109,6 @@ struct PShared {
     double g[N][64];
 };
 
-// a <- a^-1 (symmetric positive definite, without pivoting)
-template <int N>
-__device__ __forceinline__ void spd_inverse(double (&a)[N][N]) {
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const double p = 1.0 / a[k][k];
-        a[k][k] = p;
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-            if (j != k) a[k][j] *= p;
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            if (i == k) continue;
-            const double t = a[i][k];
-#pragma unroll
-            for (int j = 0; j < N; ++j)
-                if (j != k) a[i][j] = fma(-t, a[k][j], a[i][j]);
-            a[i][k] = -t * p;
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------
 // k_paper_rec: four intervals, one wave, lane & 15 the body.  Sums along a leg run
 // by lane shifts (links of a leg are consecutive lanes); every lane then forms its
