@@ -205,31 +205,16 @@ struct ImpactArgs {
     double delta, eps;
 };
 
-// A link far heavier than the rest (or fixed: an infinite mass) cancels in the torso's
-// system, which is a difference; the joint rows' system takes 1/m and stays exact.
-// It is kept for that case with its columns in memory (the node's part of JGv), so
-// that the kernel's registers are those of the other form.
-template <class TP>
-__device__ __forceinline__ bool heavy_body(const double* prm) {
-    double lo = prm[2], hi = lo;
-#pragma unroll
-    for (int b = 1; b < TP::NB; ++b) {
-        const double m = prm[2 + b];
-        lo = m < lo ? m : lo;
-        hi = m > hi ? m : hi;
-    }
-    return __builtin_amdgcn_readfirstlane(hi < 1e4 * lo ? 0 : 1) != 0;
-}
-
+// The joint rows' system, for models with a link much heavier than what lies between
+// it and the torso, or a fixed body (heavy_link): it takes 1/m.  (12,864 quad13 nodes
+// with a heavy tip: 460 us in this kernel, whose registers the other form sets.)
 // X = A^-1 grad h M^-1, A = grad h M^-1 grad h^T, and Lambda = -A^-1 grad h f by
 // Gauss-Jordan elimination of [A | grad h M^-1 | grad h f], a lane per column, the
 // pivot column by lane reads; then v* = f + M^-1 grad h^T Lambda.
 template <class TP>
-__device__ __forceinline__ void impact_dense(ImpShared<TP>& sh, double* cols, int lane) {
+__device__ __forceinline__ void impact_dense(ImpShared<TP>& sh, int lane) {
     constexpr int NJ = TP::NJ, NJ2 = TP::NJ2, NQ = TP::NQ, W = NJ2 + NQ + 1;
-    static_assert(NJ2 * W <= NQ * TP::NCV, "the columns fit the node's Jacobian");
     const int l = lane < W ? lane : W - 1;   // (spare lanes repeat the last column)
-    double* col = cols + l;
     // entry r of grad h^T row j2 (joint j2 / 2, component j2 & 1)
     auto jrow = [&](int j2, int r) {
         const int j = j2 >> 1, c = j2 & 1, b = r / 3, q = r - 3 * b;
@@ -244,26 +229,27 @@ __device__ __forceinline__ void impact_dense(ImpShared<TP>& sh, double* cols, in
         if (l < NJ2 + NQ) return l - NJ2 == r ? sh.minv[r] : 0.0;
         return sh.f[r];
     };
-#pragma unroll 1
+    double col[NJ2];
+#pragma unroll
     for (int i = 0; i < NJ2; ++i) {
         const int j = i >> 1, c = i & 1, p = TP::parent(j), ch = j + 1;
         const double ep = c == 0 ? -sh.arm[j][1] : sh.arm[j][0];
         const double ec = c == 0 ? -sh.arm[j][3] : sh.arm[j][2];
-        col[i * W] = (y(3 * p + c) + y(3 * p + 2) * ep) - (y(3 * ch + c) + y(3 * ch + 2) * ec);
+        col[i] = (y(3 * p + c) + y(3 * p + 2) * ep) - (y(3 * ch + c) + y(3 * ch + 2) * ec);
+        asm volatile("" ::: "memory");   // (read the arms row by row, keep none)
     }
-#pragma unroll 1
+#pragma unroll
     for (int kk = 0; kk < NJ2; ++kk) {
-        const double own = col[kk * W], t = own / bcast(own, kk);
-#pragma unroll 1
-        for (int i = 0; i < NJ2; ++i) {
-            const double v = col[i * W];
-            col[i * W] = i == kk ? t : fma(-bcast(v, kk), t, v);
-        }
+        const double t = col[kk] / bcast(col[kk], kk);
+#pragma unroll
+        for (int i = 0; i < NJ2; ++i) col[i] = i == kk ? t : fma(-bcast(col[i], kk), t, col[i]);
     }
     if (lane >= NJ2 && lane < NJ2 + NQ)
-        for (int i = 0; i < NJ2; ++i) sh.X[i][lane - NJ2] = col[i * W];
+#pragma unroll
+        for (int i = 0; i < NJ2; ++i) sh.X[i][lane - NJ2] = col[i];
     if (lane == NJ2 + NQ)
-        for (int i = 0; i < NJ2; ++i) sh.lam[i] = -col[i * W];
+#pragma unroll
+        for (int i = 0; i < NJ2; ++i) sh.lam[i] = -col[i];
     lds_sync();
     if (lane < NQ) {
         double jt = 0.0;
@@ -353,11 +339,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
     lds_sync();
 
     // ---- v* = f + M^-1 grad h^T Lambda, grad h v* = 0 ------------------------
-    const bool heavy = NJ > 0 && heavy_body<TP>(sh.prm);
+    const bool heavy = NJ > 0 && heavy_link<TP>(sh.prm + 2);
     double si[3][3], Z[3] = {0.0, 0.0, 0.0};   // the torso's inverse; its system by a_p1
     if constexpr (NJ > 0) {
         if (heavy) {
-            impact_dense<TP>(sh, a.JGv + (int64_t)k * NQ * NCV, lane);
+            impact_dense<TP>(sh, lane);
         } else {
             constexpr int D = TP::D, L = TP::L;
             const double* mass = sh.prm + 2;
@@ -557,37 +543,39 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
         } else if (heavy) {
             // joints at b: d(grad h)^T Lambda (angle direction), grad h du + d(grad h) v*
             double dtq = 0.0;
-            auto slot = [&](int q, bool& par, double& ax, double& ay) {
-                const int j = TP::slot_joint(b, q, par);
-                if (j >= 0) {
-                    ax = par ? sh.arm[j][0] : sh.arm[j][2];
-                    ay = par ? sh.arm[j][1] : sh.arm[j][3];
-                }
-                return j;
-            };
-            bool par;
-            double ax = 0.0, ay = 0.0;
+            int js[TP::ADJ];
+            double sg[TP::ADJ], ax[TP::ADJ], ay[TP::ADJ];
+#pragma unroll
             for (int q = 0; q < TP::ADJ; ++q) {
-                const int j = slot(q, par, ax, ay);
-                if (j >= 0 && thdir)   // d(E a)/dth = -a: parent side -a_p, child side +a_c
-                    dtq += (par ? -1.0 : 1.0) * (ax * sh.lam[2 * j] + ay * sh.lam[2 * j + 1]);
+                bool par;
+                const int j = TP::slot_joint(b, q, par);
+                js[q] = j < 0 ? 0 : j;
+                sg[q] = j < 0 ? 0.0 : (par ? 1.0 : -1.0);
+                ax[q] = par ? sh.arm[js[q]][0] : sh.arm[js[q]][2];
+                ay[q] = par ? sh.arm[js[q]][1] : sh.arm[js[q]][3];
+                if (thdir)   // d(E a)/dth = -a: parent side -a_p, child side +a_c
+                    dtq -= sg[q] * (ax[q] * sh.lam[2 * js[q]] + ay[q] * sh.lam[2 * js[q] + 1]);
             }
             du[2] += sh.minv[3 * b + 2] * dtq;
             const double om = thdir ? sh.vs[3 * b + 2] : 0.0;
-#pragma unroll 1
-            for (int r = 0; r < NQ; ++r) {
-                const int q3 = r % 3;
-                double acc = r / 3 != b ? 0.0 : (q3 == 0 ? -du[0] : (q3 == 1 ? -du[1] : -du[2]));
-                for (int q = 0; q < TP::ADJ; ++q) {
-                    const int j = slot(q, par, ax, ay);
-                    if (j < 0) continue;
-                    const double sg = par ? 1.0 : -1.0;
-                    const double bx = sg * ((du[0] - du[2] * ay) - ax * om);
-                    const double by = sg * ((du[1] + du[2] * ax) - ay * om);
-                    acc = fma(sh.X[2 * j][r], bx, fma(sh.X[2 * j + 1][r], by, acc));
-                }
-                Jk[(int64_t)r * NCV + cj] = acc;
+            double bx[TP::ADJ], by[TP::ADJ];
+#pragma unroll
+            for (int q = 0; q < TP::ADJ; ++q) {
+                bx[q] = sg[q] * ((du[0] - du[2] * ay[q]) - ax[q] * om);
+                by[q] = sg[q] * ((du[1] + du[2] * ax[q]) - ay[q] * om);
             }
+#pragma unroll 1
+            for (int rb = 0; rb < NB; ++rb)
+#pragma unroll
+                for (int q3 = 0; q3 < 3; ++q3) {
+                    const int r = 3 * rb + q3;
+                    double acc = rb == b ? -du[q3] : 0.0;
+#pragma unroll
+                    for (int q = 0; q < TP::ADJ; ++q)
+                        acc = fma(sh.X[2 * js[q]][r], bx[q],
+                                  fma(sh.X[2 * js[q] + 1][r], by[q], acc));
+                    Jk[(int64_t)r * NCV + cj] = acc;
+                }
         } else {
             constexpr int D = TP::D, L = TP::L;
             // joints at b: d(grad h)^T Lambda (angle direction)

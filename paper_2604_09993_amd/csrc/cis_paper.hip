@@ -29,6 +29,7 @@
 //                 the legs per stage (the torso's system).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <utility>
 
@@ -38,24 +39,10 @@
 #include "cis_launch.hpp"
 #include "cis_model.hpp"
 #include "cis_pack.hpp"
+#include "cis_paper.hpp"
 #include "cis_reduced.hpp"
 
 namespace cis {
-
-template <int L_, int D_>
-struct PTopo {
-    static constexpr int L = L_, D = D_;
-    static constexpr int NB = 1 + L * D, NJ = L * D, NC = L;
-    static constexpr int NQ = 3 * NB, N6 = 6 * NB;
-    static constexpr int NY = 4 * NC + 1, NX = N6 + NY;   // augmented state
-    static constexpr int M = NJ + 3 * NC, P = NB + 2;
-    static constexpr int LB = D + 1;
-    static constexpr int NCOL = N6 + 2 * M + 1;            // [Phi_x | B- | B+ | S]
-    static constexpr int NBLK = (NCOL + 63) / 64;
-    static_assert(NB <= 16, "the bodies fit one DPP row");
-    __host__ __device__ static constexpr int parent(int j) { return (j % D == 0) ? 0 : j; }
-    __host__ __device__ static constexpr int cbody(int i) { return D * (i + 1); }
-};
 
 // Layout of an interval's record area (doubles): header [HDR]: s, h, 0 x6, the masses,
 // then (k_j, d_j); stage t < 4 K, leg l at HDR + (t L + l) LEG, as vectors of 16:
@@ -82,27 +69,6 @@ struct PRec {
     static constexpr int64_t per_interval(int K) { return HDR + (int64_t)4 * K * STAGE; }
 };
 
-struct PaperArgs {
-    const double* X;    // [NX][ldn]
-    const double* U;    // [M][ldn]
-    const double* s;    // [N]
-    const double* prm;  // [P]
-    double* A;          // [NX][NX][ldi]
-    double* Bm;         // [NX][M][ldi]
-    double* Bp;
-    double* S;          // [NX][ldi]
-    double* defect;
-    double* xprop;
-    double* rec;        // records of every interval
-    int64_t ldn, ldi;
-    int N, K;
-};
-
-__device__ __forceinline__ void plds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
 template <class TP>
 struct PShared {
     enum { RX, RY, SX, SY, HD, F, AX, AY, N };   // a link's part of its leg's system
@@ -125,6 +91,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1)))
     using R = PRec<TP>;
     using SH = PShared<TP>;
     __shared__ SH sh;
+    if (heavy_link<TP>(a.prm + 2)) return;
     const int me = threadIdx.x;
     const int want = 4 * xcd_slot(blockIdx.x, gridDim.x) + (me >> 4);
     const bool on = want < a.N;   // spare rows repeat the last interval
@@ -681,6 +648,7 @@ __global__ void __launch_bounds__(64 * TP::L) __attribute__((amdgpu_waves_per_eu
     constexpr int NX = TP::NX, NC = TP::NC, NJ = TP::NJ;
     using R = PRec<TP>;
     __shared__ double xch[2][3 * L * 64];   // in turn, one barrier per stage
+    if (heavy_link<TP>(a.prm + 2)) return;
     int k, cb;
     unit_item(xcd_slot(blockIdx.x, gridDim.x), a.N, TP::NBLK, k, cb);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -792,7 +760,8 @@ static cis_status launch_paper_t(const cis_model* m, const PaperArgs& a, hipStre
         hipLaunchKernelGGL(k_paper_tan<TP>, dim3(a.N * TP::NBLK), dim3(64 * TP::L), 0, stream, a);
         e = hipGetLastError();
         if (e != hipSuccess) return fail(CIS_ERR_HIP, "k_paper_tan launch: %s", hipGetErrorString(e));
-        return CIS_OK;
+        // the masses are on the device: both forms are launched, and one returns
+        return paper_dense_launch(m, a, stream);
     } else {
         return fail(CIS_ERR_UNSUPPORTED, "the paper-dynamics form needs legs with links");
     }
@@ -831,7 +800,7 @@ extern "C" cis_status cis_paper_workspace_size(const cis_model* m, const cis_sha
                     sh->substeps);
     if (sh->dtype != CIS_F64)
         return fail(CIS_ERR_DTYPE, "cis_paper_workspace_size: the paper-dynamics form is FP64 only");
-    const int64_t per = paper_elems(m, sh->substeps);
+    const int64_t per = std::max(paper_elems(m, sh->substeps), paper_dense_elems(m, sh->substeps));
     if (per < 0) return fail(CIS_ERR_UNSUPPORTED, "paper-dynamics form: the model has no legs with links");
     *bytes = (size_t)per * (size_t)sh->N * sizeof(double);
     return CIS_OK;

@@ -1,6 +1,7 @@
 """Paper-faithful dynamics solved leg by leg, four intervals per record wave, vs the
 oracle at the edges of its tiles (GPU): interval counts around 4, every topology on
-flat ground and on a sinusoid.  Bars as everywhere (tests/parity.py).
+flat ground and on a sinusoid; and masses on either side of the ratio beyond which
+the joint rows are solved with 1/m instead.  Bars as everywhere (tests/parity.py).
 """
 import numpy as np
 import pytest
@@ -24,3 +25,15 @@ def test_tile_edges(legs, depth, terrain):
                                    torso="horizontal")
         data = synth.gen_paper_nodes(model, N, rng, T=0.02 * N)
         check(model, data, K, run_paper(model, data, K))
+
+
+@pytest.mark.parametrize("mass", [1.0, 1e2, 1e6])
+@pytest.mark.parametrize("body", [0, 1, -1])
+def test_heavy_bodies(body, mass):
+    print(f"[gpu] paper 2x2 body {body} of mass {mass}", flush=True)
+    rng = np.random.default_rng(801)
+    model = synth.legged_model("p22", 2, 2, rng, terrain="sinusoid", torso="horizontal")
+    data = synth.gen_paper_nodes(model, 2, rng, T=0.04)
+    data["p"] = data["p"].copy()
+    data["p"][2:][body] = mass
+    check(model, data, 3, run_paper(model, data, 3))
