@@ -454,7 +454,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1)))
 // body 0 is the torso, 1..D the links of the leg; rows zs[3 lb + q] (pose) and
 // zs[3 LB + 3 lb + q] (velocity); the leg's contact rows y[0..3] and its share of
 // the violation row y[4].  Bound by FP64 issue (280 instructions of a stage, 150 of
-// them with a coefficient).  1,603 quad13 intervals, K = 20: 1.00 ms; the product with
+// them with a coefficient, which issue at half rate).  1,603 quad13 intervals, K = 20:
+// 0.95 ms; the product with
 // the dense M^-1 grad h^T A^-1 of every stage, read by scalar loads, took 5.6 ms.
 // ---------------------------------------------------------------------------
 template <class TP>
@@ -473,6 +474,21 @@ template <int IDX, int IDY, int NV>
 __device__ __forceinline__ void pfma2(double& a, double& b, const double (&v)[NV], double x,
                                       double z) {
     fma_row2<IDX & 15, IDY & 15>(a, b, v[IDX >> 4], v[IDY >> 4], x, z);
+}
+
+// a += coefficient I0 times x0 + coefficient I2 times x1; b likewise by I1, I3
+template <int I0, int I1, int I2, int I3, int NV>
+__device__ __forceinline__ void pfma22(double& a, double& b, const double (&v)[NV], double x0,
+                                       double y0, double x1, double y1) {
+    fma_row_pair2<I0 & 15, I1 & 15, I2 & 15, I3 & 15>(a, b, v[I0 >> 4], v[I1 >> 4], v[I2 >> 4],
+                                                      v[I3 >> 4], x0, y0, x1, y1);
+}
+template <int I0, int I1, int I2, int I3, int NV>
+__device__ __forceinline__ void pfma4(double& a0, double& a1, double& a2, double& a3,
+                                      const double (&v)[NV], double x0, double x1, double x2,
+                                      double x3) {
+    fma_row4<I0 & 15, I1 & 15, I2 & 15, I3 & 15>(a0, a1, a2, a3, v[I0 >> 4], v[I1 >> 4],
+                                                 v[I2 >> 4], v[I3 >> 4], x0, x1, x2, x3);
 }
 
 // What a tangent lane is: hold weights, and its control's selection on this leg.
@@ -509,20 +525,16 @@ __device__ __forceinline__ void paper_tangent_stage(PLane<TP>& z, const PColumn<
         ut[l + 1] += t;
         pfma2<J + 12, J + 13>(ut[l], ut[l + 1], v, -ZQ(l, 2), ZQ(l + 1, 2));
         dx[l] = dy[l] = 0.0;
-        pfma2<J + 4, J + 5>(dx[l], dy[l], v, ZQ(l, 2), ZQ(l, 2));
-        pfma2<J + 6, J + 7>(dx[l], dy[l], v, ZQ(l + 1, 2), ZQ(l + 1, 2));
-        pfma2<J + 8, J + 9>(dx[l], dy[l], v, ZV(l, 2), ZV(l, 2));
-        pfma2<J + 10, J + 11>(dx[l], dy[l], v, ZV(l + 1, 2), ZV(l + 1, 2));
+        pfma22<J + 4, J + 5, J + 6, J + 7>(dx[l], dy[l], v, ZQ(l, 2), ZQ(l, 2), ZQ(l + 1, 2),
+                                           ZQ(l + 1, 2));
+        pfma22<J + 8, J + 9, J + 10, J + 11>(dx[l], dy[l], v, ZV(l, 2), ZV(l, 2), ZV(l + 1, 2),
+                                             ZV(l + 1, 2));
     });
-    double fx = 0.0, fy = 0.0;
-    pfma2<R::FXX, R::FYX>(fx, fy, v, ZQ(D, 0), ZQ(D, 0));
-    pfma2<R::FXT, R::FYT>(fx, fy, v, ZQ(D, 2), ZQ(D, 2));
-    pfma2<R::CTX, R::CTY>(fx, fy, v, wt, wt);
-    pfma2<R::CNX, R::CNY>(fx, fy, v, wn, wn);
-    pfma<R::TQX>(ut[D], v, ZQ(D, 0));
-    pfma<R::TQT>(ut[D], v, ZQ(D, 2));
-    pfma<R::CTT>(ut[D], v, wt);
-    pfma<R::CTN>(ut[D], v, wn);
+    double fx = 0.0, fy = 0.0, tc = 0.0;
+    pfma22<R::FXX, R::FYX, R::FXT, R::FYT>(fx, fy, v, ZQ(D, 0), ZQ(D, 0), ZQ(D, 2), ZQ(D, 2));
+    pfma22<R::CTX, R::CTY, R::CNX, R::CNY>(fx, fy, v, wt, wt, wn, wn);
+    pfma22<R::TQX, R::CTT, R::TQT, R::CTN>(ut[D], tc, v, ZQ(D, 0), wt, ZQ(D, 2), wn);
+    ut[D] += tc;
     // ---- generalized forces f of the leg, and its part of the torso's system ----
     double f[D], px = 0.0, py = 0.0;   // (px, py): sum of u - m Gamma beyond a link
     {
@@ -534,27 +546,32 @@ __device__ __forceinline__ void paper_tangent_stage(PLane<TP>& z, const PColumn<
         }
         unrolled<D>([&](auto e_c) {
             constexpr int l = D - 1 - decltype(e_c)::value, J = R::JN * l;
-            double t = ut[l + 1];
-            if constexpr (l < D - 1) {   // E a_p of the next joint on the links beyond
-                pfma<J + R::JN>(t, v, py);
-                pfma<J + R::JN + 1>(t, v, -px);
+            // with E a_p of the next joint on the links beyond (px, py before)
+            const double qx = px, qy = py;
+            if constexpr (l == D - 1) {
+                px = fma(-mass[l], Gx[l], fx);
+                py = fma(-mass[l], Gy[l], fy);
+            } else {
+                px = fma(-mass[l], Gx[l], px);
+                py = fma(-mass[l], Gy[l], py);
             }
-            const double fl = l == D - 1 ? 1.0 : 0.0;
-            px += fma(-mass[l], Gx[l], fl * fx);
-            py += fma(-mass[l], Gy[l], fl * fy);
-            pfma<J + 3>(t, v, px);
-            pfma<J + 2>(t, v, -py);
-            f[l] = t;
+            double t = ut[l + 1], q = 0.0;
+            if constexpr (l < D - 1)
+                pfma22<J + 3, J + R::JN, J + 2, J + R::JN + 1>(t, q, v, px, qy, -py, -qx);
+            else
+                pfma2<J + 3, J + 2>(t, q, v, px, -py);
+            f[l] = t + q;
         });
     }
-    double r0[3] = {px, py, ut[0]};
-    pfma<0>(r0[2], v, py);
-    pfma<1>(r0[2], v, -px);
+    double r0[3] = {px, py, ut[0]}, rt = 0.0;
+    pfma2<0, 1>(r0[2], rt, v, py, -px);
+    r0[2] += rt;
     unrolled<D>([&](auto l_c) {
         constexpr int l = decltype(l_c)::value;
         const double n = -f[l];
-        pfma2<R::G + 3 * l, R::G + 3 * l + 1>(r0[0], r0[1], v, n, n);
-        pfma<R::G + 3 * l + 2>(r0[2], v, n);
+        fma_row3<(R::G + 3 * l) & 15, (R::G + 3 * l + 1) & 15, (R::G + 3 * l + 2) & 15>(
+            r0[0], r0[1], r0[2], v[(R::G + 3 * l) >> 4], v[(R::G + 3 * l + 1) >> 4],
+            v[(R::G + 3 * l + 2) >> 4], n, n, n);
     });
     // ---- exchange: the legs' parts ----
     if constexpr (L > 1) {
@@ -570,11 +587,12 @@ __device__ __forceinline__ void paper_tangent_stage(PLane<TP>& z, const PColumn<
         }
     }
     double a0[3] = {0.0, 0.0, 0.0}, kv[3 * LB];
-    pfma2<R::SI, R::SI + 1>(a0[0], a0[1], v, r0[0], r0[0]);
-    pfma2<R::SI + 2, R::SI + 1>(a0[2], a0[0], v, r0[0], r0[1]);
-    pfma2<R::SI + 3, R::SI + 4>(a0[1], a0[2], v, r0[1], r0[1]);
-    pfma2<R::SI + 2, R::SI + 4>(a0[0], a0[1], v, r0[2], r0[2]);
-    pfma<R::SI + 5>(a0[2], v, r0[2]);
+    pfma22<R::SI, R::SI + 1, R::SI + 1, R::SI + 3>(a0[0], a0[1], v, r0[0], r0[0], r0[1], r0[1]);
+    fma_row3<(R::SI + 2) & 15, (R::SI + 2) & 15, (R::SI + 4) & 15>(
+        a0[2], a0[0], a0[1], v[(R::SI + 2) >> 4], v[(R::SI + 2) >> 4], v[(R::SI + 4) >> 4], r0[0],
+        r0[2], r0[2]);
+    fma_row_chain<(R::SI + 4) & 15, (R::SI + 5) & 15>(a0[2], v[(R::SI + 4) >> 4],
+                                                      v[(R::SI + 5) >> 4], r0[1], r0[2]);
     // ---- angular accelerations of the leg, then the links' translations ----
     kv[0] = a0[0];
     kv[1] = a0[1];
@@ -583,12 +601,14 @@ __device__ __forceinline__ void paper_tangent_stage(PLane<TP>& z, const PColumn<
     unrolled<D>([&](auto l_c) {
         constexpr int l = decltype(l_c)::value;
         double t = 0.0, q = 0.0;
-        pfma2<R::G + 3 * l, R::G + 3 * l + 1>(t, q, v, n0[0], n0[1]);
-        pfma<R::G + 3 * l + 2>(t, v, n0[2]);
-        unrolled<D>([&](auto i_c) {
-            constexpr int i = decltype(i_c)::value;
-            pfma<(i > l ? R::hi(i, l) : R::hi(l, i))>(q, v, f[i]);
-        });
+        constexpr int h0 = R::hi(l, 0), h1 = D > 1 ? (l >= 1 ? R::hi(l, 1) : R::hi(1, l)) : h0;
+        if constexpr (D > 1)
+            pfma22<R::G + 3 * l, h0, R::G + 3 * l + 1, h1>(t, q, v, n0[0], f[0], n0[1],
+                                                           f[D > 1 ? 1 : 0]);
+        else pfma22<R::G, h0, R::G + 1, R::G + 2>(t, q, v, n0[0], f[0], n0[1], n0[2]);
+        if constexpr (D == 2) pfma<R::G + 3 * l + 2>(t, v, n0[2]);
+        if constexpr (D == 3) pfma2<R::G + 3 * l + 2, R::hi(2, l)>(t, q, v, n0[2], f[D - 1]);
+        static_assert(D <= 3, "a row of H^-1 is written out");
         kv[3 * (l + 1) + 2] = t + q;
     });
     double ax = a0[0], ay = a0[1];
@@ -597,43 +617,46 @@ __device__ __forceinline__ void paper_tangent_stage(PLane<TP>& z, const PColumn<
         const double wp = kv[3 * l + 2], wc = kv[3 * l + 5];
         ax += dx[l];
         ay += dy[l];
-        pfma2<J + 1, J>(ax, ay, v, -wp, wp);
-        pfma2<J + 3, J + 2>(ax, ay, v, wc, -wc);
+        pfma22<J + 1, J, J + 3, J + 2>(ax, ay, v, -wp, wp, wc, -wc);
         kv[3 * l + 3] = ax;
         kv[3 * l + 4] = ay;
     });
     // ---- the leg's integral rows and its share of the violation row ----
-    double ky[5] = {wn, 0.0, wg, 0.0, 0.0};
-    pfma2<R::LX, R::SX>(ky[1], ky[4], v, ZQ(D, 0), ZQ(D, 0));
-    pfma2<R::LT, R::SY>(ky[1], ky[4], v, ZQ(D, 2), ZQ(D, 1));
-    pfma2<R::CTX, R::ST>(ky[1], ky[4], v, ZV(D, 0), ZQ(D, 2));
-    pfma2<R::CTY, R::VN>(ky[1], ky[4], v, ZV(D, 1), wn);
-    pfma2<R::LW, R::VT>(ky[1], ky[4], v, ZV(D, 2), wt);
-    pfma2<R::LCT, R::VG>(ky[1], ky[4], v, wt, wg);
-    pfma2<R::LCG, R::RCN>(ky[1], ky[3], v, wg, wn);
-    pfma<R::RCT>(ky[3], v, wt);
+    double ky[5] = {wn, 0.0, wg, 0.0, 0.0}, rc = 0.0;
+    pfma22<R::LX, R::SX, R::LT, R::SY>(ky[1], ky[4], v, ZQ(D, 0), ZQ(D, 0), ZQ(D, 2), ZQ(D, 1));
+    pfma22<R::CTX, R::ST, R::CTY, R::VN>(ky[1], ky[4], v, ZV(D, 0), ZQ(D, 2), ZV(D, 1), wn);
+    pfma22<R::LW, R::VT, R::LCT, R::VG>(ky[1], ky[4], v, ZV(D, 2), wt, wt, wg);
+    fma_row3<R::LCG & 15, R::RCN & 15, R::RCT & 15>(ky[1], ky[3], rc, v[R::LCG >> 4],
+                                                   v[R::RCN >> 4], v[R::RCT >> 4], wg, wn, wt);
+    ky[3] += rc;
 #pragma unroll
     for (int q = 0; q < 5; ++q) ky[q] *= s;
-    unrolled<5>([&](auto q_c) {
-        constexpr int q = decltype(q_c)::value;
-        pfma<R::YF + q>(ky[q], v, col.fsel);
-    });
+    pfma4<R::YF, R::YF + 1, R::YF + 2, R::YF + 3>(ky[0], ky[1], ky[2], ky[3], v, col.fsel, col.fsel,
+                                                  col.fsel, col.fsel);
+    pfma<R::YF + 4>(ky[4], v, col.fsel);
     // ---- classical RK4 combination ----
     constexpr double wk = (ST == 0 || ST == 3) ? 1.0 : 2.0;
     const double an = ST == 2 ? h : 0.5 * h, h6 = h / 6.0;
-    unrolled<3 * LB>([&](auto r_c) {
-        constexpr int r = decltype(r_c)::value, lb = r / 3, q = r % 3;
-        double kq = s * z.zs[3 * LB + r], ka = s * kv[r];
-        pfma2<R::SF + 6 * lb + q, R::SF + 6 * lb + 3 + q>(kq, ka, v, col.fsel, col.fsel);
-        z.za[r] = ST == 0 ? kq : z.za[r] + wk * kq;
-        z.za[3 * LB + r] = ST == 0 ? ka : z.za[3 * LB + r] + wk * ka;
-        if constexpr (ST < 3) {
-            z.zs[r] = z.zb[r] + an * kq;
-            z.zs[3 * LB + r] = z.zb[3 * LB + r] + an * ka;
-        } else {
-            z.zs[r] = z.zb[r] += h6 * z.za[r];
-            z.zs[3 * LB + r] = z.zb[3 * LB + r] += h6 * z.za[3 * LB + r];
-        }
+    auto combine = [&](int r, double k) {
+        z.za[r] = ST == 0 ? k : z.za[r] + wk * k;
+        if constexpr (ST < 3) z.zs[r] = z.zb[r] + an * k;
+        else z.zs[r] = z.zb[r] += h6 * z.za[r];
+    };
+    unrolled<LB>([&](auto b_c) {
+        constexpr int lb = decltype(b_c)::value, F = R::SF + 6 * lb, r = 3 * lb, p = 3 * LB + r;
+        double q0 = s * z.zs[p], q1 = s * z.zs[p + 1], q2 = s * z.zs[p + 2];
+        double k0 = s * kv[r], k1 = s * kv[r + 1], k2 = s * kv[r + 2];
+        const double fs = col.fsel;
+        fma_row3<F & 15, (F + 1) & 15, (F + 2) & 15>(q0, q1, q2, v[F >> 4], v[(F + 1) >> 4],
+                                                     v[(F + 2) >> 4], fs, fs, fs);
+        fma_row3<(F + 3) & 15, (F + 4) & 15, (F + 5) & 15>(
+            k0, k1, k2, v[(F + 3) >> 4], v[(F + 4) >> 4], v[(F + 5) >> 4], fs, fs, fs);
+        combine(r, q0);
+        combine(r + 1, q1);
+        combine(r + 2, q2);
+        combine(p, k0);
+        combine(p + 1, k1);
+        combine(p + 2, k2);
     });
 #pragma unroll
     for (int q = 0; q < 5; ++q) z.yc[q] += (h6 * wk) * ky[q];

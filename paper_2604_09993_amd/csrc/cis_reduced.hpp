@@ -205,6 +205,29 @@ struct RedLane {
             : "+v"(a)                                                                       \
             : "v"(c0), "v"(c1), "v"(x0), "v"(x1), "n"(N0), "n"(N1));                        \
     }                                                                                       \
+    template <int N0, int N1, int N2>                                                       \
+    __device__ __forceinline__ void fma_row3(TYPE& a0, TYPE& a1, TYPE& a2, TYPE c0, TYPE c1, \
+                                             TYPE c2, TYPE x0, TYPE x1, TYPE x2) {          \
+        asm("s_nop 1\n\t" INS "_dpp %0, %3, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t" \
+            INS "_dpp %1, %4, %7 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"           \
+            INS "_dpp %2, %5, %8 row_newbcast:%11 row_mask:0xf bank_mask:0xf"               \
+            : "+v"(a0), "+v"(a1), "+v"(a2)                                                  \
+            : "v"(c0), "v"(c1), "v"(c2), "v"(x0), "v"(x1), "v"(x2), "n"(N0), "n"(N1),       \
+              "n"(N2));                                                                     \
+    }                                                                                       \
+    /* a += c0[N0] x0; b += c1[N1] y0; a += c2[N2] x1; b += c3[N3] y1 */                    \
+    template <int N0, int N1, int N2, int N3>                                               \
+    __device__ __forceinline__ void fma_row_pair2(TYPE& a, TYPE& b, TYPE c0, TYPE c1,       \
+                                                  TYPE c2, TYPE c3, TYPE x0, TYPE y0,       \
+                                                  TYPE x1, TYPE y1) {                       \
+        asm("s_nop 1\n\t" INS "_dpp %0, %2, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t" \
+            INS "_dpp %1, %3, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"           \
+            INS "_dpp %0, %4, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"           \
+            INS "_dpp %1, %5, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf"               \
+            : "+v"(a), "+v"(b)                                                              \
+            : "v"(c0), "v"(c1), "v"(c2), "v"(c3), "v"(x0), "v"(y0), "v"(x1), "v"(y1),       \
+              "n"(N0), "n"(N1), "n"(N2), "n"(N3));                                          \
+    }                                                                                       \
     /* a chain on two accumulators: a += c[N] x; b += c[N+2] x; a += c[N+1] y; b += c[N+3] y */ \
     template <int N>                                                                        \
     __device__ __forceinline__ void fma_row_joint(TYPE& a, TYPE& b, TYPE c, TYPE x, TYPE y) { \
