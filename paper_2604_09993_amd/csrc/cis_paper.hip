@@ -455,8 +455,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1)))
 // zs[3 LB + 3 lb + q] (velocity); the leg's contact rows y[0..3] and its share of
 // the violation row y[4].  Bound by FP64 issue (280 instructions of a stage, 150 of
 // them with a coefficient, which issue at half rate).  1,603 quad13 intervals, K = 20:
-// 0.95 ms; the product with
-// the dense M^-1 grad h^T A^-1 of every stage, read by scalar loads, took 5.6 ms.
+// 0.95 ms; the product with the dense M^-1 grad h^T A^-1 of every stage, read by
+// scalar loads, took 5.6 ms.
 // ---------------------------------------------------------------------------
 template <class TP>
 struct PLane {
