@@ -89,6 +89,8 @@ def kernel_stats(folder):
 
 
 def counter_means(folder, counter):
+    """Mean per kernel name over its largest dispatches (at least half the most: a
+    batch's launch and a short trajectory's share a name)."""
     vals = defaultdict(list)
     for db in _dbs(folder):
         c = sqlite3.connect(db).cursor()
@@ -98,6 +100,7 @@ def counter_means(folder, counter):
         for r in c.execute("select * from counters_collection"):
             if r[ci["counter_name"]] == counter:
                 vals[_short(r[kcol])].append(float(r[ci["value"]]))
+    vals = {k: [x for x in v if 2 * x >= max(v)] for k, v in vals.items()}
     return {k: sum(v) / len(v) for k, v in vals.items()}
 
 
@@ -178,13 +181,15 @@ def bench_algorithmic_bytes():
 
 def split_bytes(model, dsize=8):
     """Algorithmic bytes of one interval in the two launches of the split form:
-    the record launch reads the interval's inputs and writes S, the defect,
-    F~ and the integral-state columns of A; the tangent launch writes the
-    x-state columns of A and B-, B+ (the stage records between them are
-    intermediate, not algorithmic, traffic)."""
-    nx, m, n, P = model.nx, model.m, model.n, model.n_params
-    rec = dsize * ((2 * nx + 2 * m + 1 + P) + 3 * nx + nx * (nx - n))
-    tan = dsize * (nx * n + 2 * nx * m)
+    the record launch reads the interval's inputs and writes S, the defect, F~,
+    the integral-state columns of A and the rows of A, B- and B+ with a closed
+    form (translations: of every body on flat ground, else of those without a
+    contact); the tangent launch writes the other rows (the stage records
+    between them are intermediate, not algorithmic, traffic)."""
+    nx, m, n, P, nb, nc = model.nx, model.m, model.n, model.n_params, model.nb, model.nc
+    closed = 4 * (nb if model.terrain_amplitude == 0.0 else nb - nc)
+    rec = dsize * ((2 * nx + 2 * m + 1 + P) + 3 * nx + nx * (nx - n) + closed * (n + 2 * m))
+    tan = dsize * (nx - closed) * (n + 2 * m)
     return rec, tan
 
 
