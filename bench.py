@@ -71,19 +71,19 @@ def rkf_flops_per_interval(model, K):
 
 
 def paper_flops_per_interval(model, K):
-    """Per-interval FLOPs of the paper-faithful dynamics variant:
-    4K [c (2 n_q 2 n_j + 2 nnz(J) + 14 nx) + 2 (2 n_j)^2 (2 n_j + n_q + 1)] with
-    c = 6 n_b + 2 m + 1 tangent columns (m = n_j + 3 n_c, nx = 6 n_b + 4 n_c + 1):
-    per stage and column the dense joint coupling Wm b, the sparse local terms
-    and the RK4 combination; per stage the Gauss-Jordan elimination of
-    [A | grad h M^-1 | r]."""
+    """Per-interval FLOPs of the paper-faithful dynamics variant, joint forces
+    eliminated leg by leg: 4K [c (2 (n_j (14 + d + 6) + 25 n_c + 9) + 14 nx) + n_c (2 d^3
+    + 20 d^2) + phi_fJ] with d = n_j / n_c links per leg and c = 6 n_b + 2 m + 1 tangent
+    columns (m = n_j + 3 n_c, nx = 6 n_b + 4 n_c + 1): per stage and column 14
+    coefficients of every joint, d of its row of H^-1 and 6 of G, 25 of every contact,
+    the torso's 3 x 3 inverse and the RK4 combination; per stage the legs' systems
+    and the nominal evaluation."""
     nb, nj, nc = model.nb, model.nj, model.nc
-    nq = 3 * nb
-    nnz = 2 * nq + 2 * nb + 4 * nj + 4 * nc
     nx = 6 * nb + 4 * nc + 1
     c = 6 * nb + 2 * (nj + 3 * nc) + 1
-    return 4 * K * (c * (2 * nq * 2 * nj + 2 * nnz + 14 * nx)
-                    + 2 * (2 * nj) ** 2 * (2 * nj + nq + 1))
+    d = nj // nc
+    return 4 * K * (c * (2 * (nj * (20 + d) + 25 * nc + 9) + 14 * nx)
+                    + nc * (2 * d ** 3 + 20 * d ** 2) + PHI_FJ.get(nb, 1000))
 
 
 def adjoint_flops_per_interval(model, K):
