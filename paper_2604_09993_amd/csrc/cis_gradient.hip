@@ -177,10 +177,13 @@ __device__ __forceinline__ int pack_most(int K) {
     return most;
 }
 
-// (three waves per SIMD at 60 bytes of scratch and two at none: 250 and 253 us)
+// FP64: three waves per SIMD on flat ground (60 bytes of scratch; at two and none 253
+// us instead of 250 for 12,800 quad13 intervals), two on the sinusoid (188 bytes at
+// three; gradient step of biped5 batches of 300, 3,000 and 12,800 intervals: 195,
+// 355 and 1,137 us at three, 171, 329 and 1,080 at two).
 template <class T, class TP, bool FLAT>
 __global__ void __launch_bounds__(128)
-    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 4)))
+    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? (FLAT ? 3 : 2) : 4)))
     k_defects_pack(ItemList<T> l, MConst<TP::NB, TP::NJ, TP::NC> mc) {
     __shared__ PackShared<T> sh;
     const PackRow r = pack_row_item(l.n);
