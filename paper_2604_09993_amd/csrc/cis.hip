@@ -749,7 +749,7 @@ static FwdArgs<T> make_args(const cis_shape* sh, const void* X, const void* U, c
 }
 
 // Compute units of the current device (cached per device id).
-static int device_cus() {
+int device_cus() {
     static std::atomic<int> cache[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;

@@ -44,5 +44,7 @@ std::map<std::string, TuneChoice> cache_read(const std::string& path);
 bool cache_write(const std::string& path, const std::map<std::string, TuneChoice>& m);
 // "<architecture>/<compute units>cu" of a device
 std::string device_tag(int dev);
+// compute units of the current device (cis.hip)
+int device_cus();
 
 }  // namespace cis

@@ -283,14 +283,28 @@ __device__ __forceinline__ void tangent_item(const T* __restrict__ rec, T* lds,
 }
 
 template <class T, class TP, bool FLAT>
-__global__ void __launch_bounds__(128)
-    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3)))
-    k_coefrec(ItemList<T> l, MConst<TP::NB, TP::NJ, TP::NC> mc) {
+__device__ __forceinline__ void coefrec_block(const ItemList<T>& l,
+                                              const MConst<TP::NB, TP::NJ, TP::NC>& mc) {
     __shared__ PackShared<T> sh;
     red_record_block<T, TP, FLAT>(l, [&](const FwdArgs<T>& a, int item, bool on, int most) {
         coefrec_item<T, TP, FLAT>(a, mc, l.interval(item), l.records(item), l.sums + item, l.n, on,
                                   most, sh);
     });
+}
+
+template <class T, class TP, bool FLAT>
+__global__ void __launch_bounds__(128)
+    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3)))
+    k_coefrec(ItemList<T> l, MConst<TP::NB, TP::NJ, TP::NC> mc) {
+    coefrec_block<T, TP, FLAT>(l, mc);
+}
+
+// The same with all the registers: FP64 on a sinusoid holds 68 bytes of scratch per
+// lane at two waves per SIMD.
+template <class T, class TP>
+__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1)))
+    k_coefrec_sinus(ItemList<T> l, MConst<TP::NB, TP::NJ, TP::NC> mc) {
+    coefrec_block<T, TP, false>(l, mc);
 }
 
 // Registers: six values per pair and lane, so FP64 holds two waves per SIMD up to
@@ -353,6 +367,12 @@ static void split_launches(const cis_model* m, const ItemList<T>& l, KLaunch* ka
     ka->arg(l);
     ka->arg(make_const<TP::NB, TP::NJ, TP::NC>(m));
     ka->func = (const void*)&k_coefrec<T, TP, FLAT>;
+    // Up to about three workgroups per CU (with those of the closed-form rows) a second
+    // wave per SIMD only slows the chain (both launches for biped5, K = 20: 333
+    // intervals 142 us at two waves and 141 at one, 1,000 185 and 144, 1,500 196 and 157,
+    // 2,000 202 and 250).
+    if constexpr (!FLAT && sizeof(T) == 8)
+        if (l.n <= 6 * device_cus()) ka->func = (const void*)&k_coefrec_sinus<T, TP>;
     ka->grid = dim3(RedGrid<TP, FLAT>::rec_blocks(l.n));
     ka->block = dim3(128);
     kb->arg(l);

@@ -138,3 +138,18 @@ def test_non_finite_inputs_reach_the_closed_forms(terrain):
         else:
             rows = list(range(nq))
         assert bad[rows][:, :n].all()
+
+
+@pytest.mark.parametrize("legs,depth", [(1, 1), (2, 2)])
+def test_record_budget_line(legs, depth):
+    """FP64 on the sinusoid: the record launch's register budget changes at six
+    intervals per CU."""
+    from paper_2604_09993_amd import api
+    line = 6 * torch.cuda.get_device_properties(0).multi_processor_count
+    for N in (line, line + 1):
+        print(f"[gpu] reduced {legs}x{depth} sinusoid budget line N={N}", flush=True)
+        model, d = _case(legs, depth, "sinusoid", N)
+        cm, X, U, s, p = _dev(model, d, torch.float64)
+        out = api.discretize_split(cm, X, U, s, p, 1)
+        torch.cuda.synchronize()
+        _check(model, d, 1, out, torch.float64)
