@@ -152,14 +152,16 @@ struct BodyRK {
     T xb[6], xa[6], xs[6];
 };
 
-// 1 / sqrt(w), w >= 1.  FP64: the hardware estimate and two steps on the residual
+// 1 / sqrt(w), w > 0.  FP64: the hardware estimate and two steps on the residual
 // 1 - w y^2 (a square root and a division are some 40 instructions in one chain).
+// The residual takes the largest finite number for an infinite w, whose estimate is 0.
 __device__ __forceinline__ float rsqrt_t(float w) { return 1.0f / sqrt_t(w); }
 __device__ __forceinline__ double rsqrt_t(double w) {
     double y = __builtin_amdgcn_rsq(w);
+    const double wf = fmin(w, DBL_MAX);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const double e = fma(-(w * y), y, 1.0);
+        const double e = fma(-(wf * y), y, 1.0);
         y = fma(y * e, fma(0.375, e, 0.5), y);
     }
     return y;

@@ -86,14 +86,16 @@ __device__ __forceinline__ Dual operator*(Dual a, Dual b) {
     return {a.v * b.v, fma(a.d, b.v, a.v * b.d)};
 }
 __device__ __forceinline__ Dual operator*(double a, Dual b) { return {a * b.v, a * b.d}; }
-__device__ __forceinline__ Dual operator/(Dual a, Dual b) {
-    const double r = 1.0 / b.v, q0 = a.v * r, q = fma(fma(-q0, b.v, a.v), r, q0);
+__device__ __forceinline__ Dual operator/(Dual a, Dual b) {   // |b.v| >= 1 wherever it is used
+    // a residual that is no number: an operand is infinite, and a.v r the quotient
+    const double r = 1.0 / b.v, q0 = a.v * r, e = fma(-q0, b.v, a.v);
+    const double q = e == e ? fma(e, r, q0) : q0;
     return {q, (a.d - q * b.d) * r};
 }
 __device__ __forceinline__ Dual dsqrt(Dual a) {   // a.v > 0 wherever it is used
     // hardware estimate, two residual steps, and one on the root itself
-    const double y = rsqrt_t(a.v), s = a.v * y;
-    return {fma(fma(-s, s, a.v), 0.5 * y, s), a.d * (0.5 * y)};
+    const double y = rsqrt_t(a.v), s = a.v * y, v = fma(fma(-s, s, a.v), 0.5 * y, s);
+    return {a.v < HUGE_VAL ? v : a.v, a.d * (0.5 * y)};
 }
 __device__ __forceinline__ void dsincos(Dual a, Dual& s, Dual& c) {
     double sv, cv;

@@ -17,6 +17,8 @@
 //          into a coefficient buffer read by the tangent lanes.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <float.h>
+#include <math.h>
 #include <stdint.h>
 #include <string.h>
 
@@ -220,6 +222,14 @@ __device__ __forceinline__ void sabs_d(double a, double& val, double& der) {
     q = q * fma(-d, q, 2.0);
     der = a * y;
     val = (a * a) * (y * q);
+}
+// The same with |a| and its sign where a^2 overflows (NaN there otherwise).
+__device__ __forceinline__ void sabs_wide(double a, double& val, double& der) {
+    sabs_d(a, val, der);
+    if (a * a > DBL_MAX) {
+        val = fabs(a);
+        der = a / val;
+    }
 }
 // FP32: the same form with the hardware reciprocal square root and
 // reciprocal (about 1 ulp each, far inside the FP32 tolerance).

@@ -1,0 +1,84 @@
+"""Very large and non-finite inputs (GPU): what does not depend on them stays as it is.
+
+Arguments whose squares overflow: a root is infinite and a quotient by it zero, as in
+the oracle's formulas.
+"""
+import numpy as np
+import pytest
+
+from paper_2604_09993_amd import synth
+from test_gpu_impact import DELTA, run_gpu
+from test_gpu_paper import run_paper
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+BIG = 1e200
+
+
+def _legs(terrain, legs=2, depth=2):
+    rng = np.random.default_rng([970, legs, depth])
+    return synth.legged_model(f"v{legs}{depth}", legs, depth, rng, terrain=terrain,
+                              torso="horizontal"), rng
+
+
+@pytest.mark.parametrize("terrain", ["flat", "sinusoid"])
+def test_impact_arguments_whose_squares_overflow(terrain):
+    """FB(a, b) = a + b - sqrt(a^2 + b^2 + delta) is -inf with slope 1 in the other
+    argument; phi_t / sqrt(phi_t^2 + 1) is 0."""
+    print(f"[gpu] impact overflow {terrain}", flush=True)
+    model, rng = _legs(terrain)
+    d = synth.gen_impact_nodes(model, 3, rng)
+    tip = int(model.contact_body[0])
+    plain = run_gpu(model, d)
+    other = np.arange(plain["Theta"].shape[1]) >= 10
+    for what in ("velocity", "normal", "tangent"):
+        e = {k: v.copy() for k, v in d.items()}
+        if what == "velocity":
+            e["Xp"][1, 3 * model.nb + 3 * tip + 1] = BIG
+            lost = [1]
+        elif what == "normal":
+            e["Phi"][1, 1] = BIG
+            lost = [0, 1]
+        else:
+            e["Phi"][1, 0] = BIG
+            lost = []
+        r = run_gpu(model, e)
+        T, J = r["Theta"][1], r["JTc"][1]
+        assert np.all(T[lost] == -np.inf), (what, T[:10])
+        for k in ("Theta", "JTc"):   # the other contact, the other nodes
+            assert np.array_equal(r[k][1][other], plain[k][1][other])
+            assert np.array_equal(r[k][::2], plain[k][::2])
+        if what == "velocity":
+            # row 1 by everything but Phi_n and the infinite root: w; row 7: -w
+            # (2 w dw, the root's argument's derivative, is finite for dw < 1e100)
+            keep = [c for c in range(14) if c != 10 and abs(J[7][c]) < 1e100]
+            assert len(keep) >= 10
+            assert np.array_equal(J[1][keep], -J[7][keep]) and J[1][10] == 1.0
+            assert np.isfinite(np.delete(T, lost)).all()
+        elif what == "tangent":
+            # lam is the tangential velocity: the difference of rows 2 and 3 over 2 Phi_n
+            pn = e["Phi"][1, 1]
+            e["Gamma"][1, 0] = 0.0
+            free = run_gpu(model, e)["Theta"][1]
+            assert np.array_equal(T[2:4], free[2:4]) and np.isfinite(T[2:4]).all()
+            assert abs(0.5 * (T[2] + T[3]) + DELTA) <= 1e-14 * max(1.0, abs(pn))
+            assert np.isfinite(J[2:4]).all()
+
+
+@pytest.mark.parametrize("terrain", ["flat", "sinusoid"])
+def test_paper_friction_whose_square_overflows(terrain):
+    """mu enters the friction-cone row and the violation row alone, and both stay finite
+    where (mu phi_n)^2 overflows."""
+    print(f"[gpu] paper overflow {terrain}", flush=True)
+    model, rng = _legs(terrain)
+    data = synth.gen_paper_nodes(model, 3, rng, T=0.06)
+    plain = run_paper(model, data, 2)
+    data["p"] = data["p"].copy()
+    data["p"][0] = BIG
+    res = run_paper(model, data, 2)
+    n, nc = model.n, model.nc
+    rows = [r for r in range(n + 4 * nc) if r < n or (r - n) % 4 != 3]
+    for k in ("A", "Bm", "Bp"):
+        assert np.isfinite(res[k]).all(), k
+        assert np.array_equal(res[k][:, rows], plain[k][:, rows]), k
