@@ -536,10 +536,11 @@ __device__ __forceinline__ void pack_accel(const PackBody<T, TP, FLAT>& c,
     kz[0] = f[0];
     kz[1] = f[1];
     kz[2] = f[2] + cth * zs[2] + si * (c.children(tz) - tz);
-    if constexpr (!FLAT) {
-        kz[0] += fxx * (zs[0] - ay * zs[2]);
-        kz[1] += fyx * (zs[0] - ay * zs[2]);
-        kz[2] += ftx * zs[0];
+    if constexpr (!FLAT) {   // (no 0 x NaN on bodies without a contact)
+        auto own = [&](T v) { return c.contact ? v : T(0); };
+        kz[0] += own(fxx * (zs[0] - ay * zs[2]));
+        kz[1] += own(fyx * (zs[0] - ay * zs[2]));
+        kz[2] += own(ftx * zs[0]);
     }
 }
 

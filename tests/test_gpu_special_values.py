@@ -1,7 +1,8 @@
 """Very large and non-finite inputs (GPU): what does not depend on them stays as it is.
 
 Arguments whose squares overflow: a root is infinite and a quotient by it zero, as in
-the oracle's formulas.
+the oracle's formulas.  A NaN reaches what has it in its formula, not what has a zero
+coefficient by it for the lack of a contact, nor other intervals.
 """
 import numpy as np
 import pytest
@@ -82,3 +83,36 @@ def test_paper_friction_whose_square_overflows(terrain):
     for k in ("A", "Bm", "Bp"):
         assert np.isfinite(res[k]).all(), k
         assert np.array_equal(res[k][:, rows], plain[k][:, rows]), k
+
+
+def _nan_run(kind, model, d, K, where):
+    """The outputs of intervals with a NaN at `where` of X's node 2, and of plain ones."""
+    from paper_2604_09993_amd import api
+    cm = api.CisModel(model)
+    out = []
+    for value in (None, float("nan")):
+        X = d["X"].copy()
+        if value is not None:
+            X[2, where] = value
+        args = (cm, api.to_device_soa(X), api.to_device_soa(d["U"]),
+                torch.tensor(d["s"], device="cuda"), torch.tensor(d["p"], device="cuda"), K)
+        r = (api.discretize_split if kind == "split" else api.discretize_rkf)(*args)
+        torch.cuda.synchronize()
+        out.append({k: v.cpu().numpy() for k, v in api.as_interval_major(
+            {k: v for k, v in r.items() if k != "err"}).items()})
+    return out
+
+
+@pytest.mark.parametrize("kind", ["split", "rkf"])
+@pytest.mark.parametrize("terrain", ["flat", "sinusoid"])
+def test_nan_torso_velocity(terrain, kind):
+    """The torso's x rate enters its x row and the violation row alone."""
+    print(f"[gpu] NaN torso velocity {kind} {terrain}", flush=True)
+    model, rng = _legs(terrain)
+    d = synth.gen_nodes(model, 6, rng, T=0.12)
+    nq, n, nx = 3 * model.nb, model.n, model.nx
+    plain, res = _nan_run(kind, model, d, 2, nq)
+    rows = [r for r in range(nx - 1) if r not in (0, nq)]
+    for k in ("A", "Bm", "Bp", "S"):
+        assert np.array_equal(np.delete(res[k], 2, 0), np.delete(plain[k], 2, 0)), k
+        assert np.array_equal(res[k][2][rows], plain[k][2][rows]), k
