@@ -742,7 +742,8 @@ __device__ __forceinline__ void pack_sums(const PackBody<T, TP, FLAT>& c,
             sums[(R::GC + q * TP::NC + c.i) * n] = sm.gc[q];
         }
         sums[(R::EV + c.i) * n] = sm.ev;
-        sums[(R::PZ + 2 + c.i) * n] = T(0) * sm.zcc;
+        // a coefficient of the row that is no number leaves one in these two
+        sums[(R::PZ + 2 + c.i) * n] = T(0) * (sm.ey[0] + (FLAT ? sm.ex[0] : sm.ev));
     }
     if (c.torso) {
         sums[R::PZ * n] = T(0) * angles;

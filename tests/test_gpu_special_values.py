@@ -116,3 +116,16 @@ def test_nan_torso_velocity(terrain, kind):
     for k in ("A", "Bm", "Bp", "S"):
         assert np.array_equal(np.delete(res[k], 2, 0), np.delete(plain[k], 2, 0)), k
         assert np.array_equal(res[k][2][rows], plain[k][2][rows]), k
+
+
+@pytest.mark.parametrize("kind", ["split", "rkf"])
+def test_nan_foot_height(kind):
+    """On flat ground a foot's height enters the value of its integral row, not the
+    row's coefficients, and the violation row."""
+    print(f"[gpu] NaN foot height {kind}", flush=True)
+    model, rng = _legs("flat")
+    d = synth.gen_nodes(model, 6, rng, T=0.12)
+    plain, res = _nan_run(kind, model, d, 2, 3 * int(model.contact_body[0]) + 1)
+    for k in ("A", "Bm", "Bp"):
+        assert np.array_equal(np.delete(res[k], 2, 0), np.delete(plain[k], 2, 0)), k
+    assert np.array_equal(res["A"][2][:model.nx - 1], plain["A"][2][:model.nx - 1])
