@@ -154,11 +154,13 @@ struct BodyRK {
 
 // 1 / sqrt(w), w > 0.  FP64: the hardware estimate and two steps on the residual
 // 1 - w y^2 (a square root and a division are some 40 instructions in one chain).
-// The residual takes the largest finite number for an infinite w, whose estimate is 0.
+// WIDE: 0 for an infinite w (NaN otherwise; the terrain's slope squared, which is
+// model data, does without: 0.5 % of a biped5 gradient step).
 __device__ __forceinline__ float rsqrt_t(float w) { return 1.0f / sqrt_t(w); }
+template <bool WIDE = false>
 __device__ __forceinline__ double rsqrt_t(double w) {
     double y = __builtin_amdgcn_rsq(w);
-    const double wf = fmin(w, DBL_MAX);
+    const double wf = WIDE ? fmin(w, DBL_MAX) : w;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const double e = fma(-(wf * y), y, 1.0);

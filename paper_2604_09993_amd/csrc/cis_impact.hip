@@ -94,7 +94,7 @@ __device__ __forceinline__ Dual operator/(Dual a, Dual b) {   // |b.v| >= 1 wher
 }
 __device__ __forceinline__ Dual dsqrt(Dual a) {   // a.v > 0 wherever it is used
     // hardware estimate, two residual steps, and one on the root itself
-    const double y = rsqrt_t(a.v), s = a.v * y, v = fma(fma(-s, s, a.v), 0.5 * y, s);
+    const double y = rsqrt_t<true>(a.v), s = a.v * y, v = fma(fma(-s, s, a.v), 0.5 * y, s);
     return {a.v < HUGE_VAL ? v : a.v, a.d * (0.5 * y)};
 }
 __device__ __forceinline__ void dsincos(Dual a, Dual& s, Dual& c) {

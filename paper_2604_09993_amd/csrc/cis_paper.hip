@@ -215,7 +215,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1)))
             double vn, dn, vt, dt, v1, d1, v2, d2, v3, d3, v4, d4;
             sabs_wide(mu * pn, vn, dn);
             sabs_d(pt, vt, dt);
-            const double y1 = rsqrt_t(pt * pt + 1.0);
+            const double y1 = rsqrt_t<true>(pt * pt + 1.0);
             const double lc = tx * jvx + ty * jvy + gm * dt;
             const double rr = vn - vt;
             sabs_d(-pn, v1, d1);
