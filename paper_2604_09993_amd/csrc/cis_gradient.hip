@@ -261,7 +261,8 @@ __device__ __forceinline__ void adj_coef(const PackBody<double, TP, FLAT>& c,
         const T ln = omt * l0.a + tau * l0.b, ft = omt * l1.a + tau * l1.b;
         const T dfx = f.dny * ft + f.dnx * ln, dfy = -f.dnx * ft + f.dny * ln;
         cx = s * (lb.a * f.dsd_px + gv * (f.dny * Pdx - f.dnx * Pdy));
-        cy = s * (lb.a * f.dsd_py);
+        // (by itself in the y row: no 0 x NaN of the frame's x without a contact)
+        cy = c.contact ? s * (lb.a * f.dsd_py) : T(0);
         cvx = s * (gv * f.tx);
         cvy = s * (gv * f.ty);
         com = s * (gv * (f.ty * ax - f.tx * ay));

@@ -129,3 +129,30 @@ def test_nan_foot_height(kind):
     for k in ("A", "Bm", "Bp"):
         assert np.array_equal(np.delete(res[k], 2, 0), np.delete(plain[k], 2, 0)), k
     assert np.array_equal(res["A"][2][:model.nx - 1], plain["A"][2][:model.nx - 1])
+
+
+@pytest.mark.parametrize("terrain", ["flat", "sinusoid"])
+def test_nan_torso_position_gradient(terrain):
+    """The torso's x enters the joint rows of the violation by x and y: its own y row of
+    gX, which has the joints' y distances alone, stays as it is."""
+    from paper_2604_09993_amd import api
+    print(f"[gpu] NaN torso position, gradient {terrain}", flush=True)
+    model, rng = _legs(terrain)
+    d = synth.gen_nodes(model, 6, rng, T=0.12)
+    cm = api.CisModel(model)
+    seed = torch.tensor(rng.normal(size=(model.nx, 6)), device="cuda")
+    s, p = torch.tensor(d["s"], device="cuda"), torch.tensor(d["p"], device="cuda")
+    U, res = api.to_device_soa(d["U"]), []
+    for value in (None, float("nan")):
+        X = d["X"].copy()
+        if value is not None:
+            X[2, 0] = value
+        Xd = api.to_device_soa(X)
+        f = api.defects(cm, Xd, U, s, p, 2, ckpt_every=1)
+        g = api.adjoint(cm, Xd, U, s, p, 2, f["ckpt"], 1, seed)
+        torch.cuda.synchronize()
+        res.append({k: v.cpu().numpy() for k, v in g.items()})
+    rows = [1, 3 * model.nb + 1]
+    for k in ("gX", "gs"):   # other intervals
+        assert np.array_equal(np.delete(res[0][k], 2, -1), np.delete(res[1][k], 2, -1)), k
+    assert np.array_equal(res[0]["gX"][rows, 2], res[1]["gX"][rows, 2])
