@@ -204,20 +204,20 @@ __device__ __forceinline__ void spd_inverse(double (&a)[N][N]) {
 }
 
 // Whether a link is much heavier than the torso or a body between them (or a mass is
-// infinite or NaN).  A leg eliminated from its tip by angular rates then cancels:
+// infinite, NaN or not positive).  A leg eliminated from its tip by angular rates then cancels:
 // what the torso feels of it is a difference of its masses.  Errors of the
 // paper-faithful A against 64 bits, a tip 100, 1,000, 1e6 times heavier than the
 // rest: 5e-16, 4e-15, 5e-8 (the joint rows' system, which takes 1/m: 1e-16).
 template <class TP>
 __device__ __forceinline__ bool heavy_link(const double* mass) {
-    bool ok = mass[0] < 1e300;
+    bool ok = mass[0] > 0.0 && mass[0] < 1e300;
 #pragma unroll
     for (int l = 0; l < TP::L; ++l) {
         double lo = mass[0];
 #pragma unroll
         for (int e = 0; e < TP::D; ++e) {
             const double m = mass[1 + l * TP::D + e];
-            ok = ok && m < 16.0 * lo;
+            ok = ok && m > 0.0 && m < 16.0 * lo;
             lo = m < lo ? m : lo;
         }
     }
