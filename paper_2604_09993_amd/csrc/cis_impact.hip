@@ -208,8 +208,9 @@ struct ImpactArgs {
 };
 
 // The joint rows' system, for models with a link much heavier than what lies between
-// it and the torso, or a fixed body (heavy_link): it takes 1/m.  (12,864 quad13 nodes
-// with a heavy tip: 460 us in this kernel, whose registers the other form sets.)
+// it and the torso, or a fixed body (heavy_link): it takes 1/m.  12,864 quad13 nodes
+// with a heavy tip: 251 us (500: 29 us; with every row's reads in flight at once, which
+// held 516 bytes of scratch per lane, 440 us and 54 us).
 // X = A^-1 grad h M^-1, A = grad h M^-1 grad h^T, and Lambda = -A^-1 grad h f by
 // Gauss-Jordan elimination of [A | grad h M^-1 | grad h f], a lane per column, the
 // pivot column by lane reads; then v* = f + M^-1 grad h^T Lambda.
@@ -217,19 +218,21 @@ template <class TP>
 __device__ __forceinline__ void impact_dense(ImpShared<TP>& sh, int lane) {
     constexpr int NJ = TP::NJ, NJ2 = TP::NJ2, NQ = TP::NQ, W = NJ2 + NQ + 1;
     const int l = lane < W ? lane : W - 1;   // (spare lanes repeat the last column)
-    // entry r of grad h^T row j2 (joint j2 / 2, component j2 & 1)
-    auto jrow = [&](int j2, int r) {
-        const int j = j2 >> 1, c = j2 & 1, b = r / 3, q = r - 3 * b;
-        const double ep = c == 0 ? -sh.arm[j][1] : sh.arm[j][0];
-        const double ec = c == 0 ? -sh.arm[j][3] : sh.arm[j][2];
-        if (b == TP::parent(j)) return q == c ? 1.0 : (q == 2 ? ep : 0.0);
-        if (b == j + 1) return q == c ? -1.0 : (q == 2 ? -ec : 0.0);
-        return 0.0;
-    };
+    // the lane's column before grad h, entry by entry: a factor on 1/m (or on f), which
+    // is +-1 or an arm's component at one or two bodies (a joint row), or 1 at one entry
+    const double* base = l < NJ2 + NQ ? sh.minv : sh.f;
+    const int jl = l < NJ2 ? l >> 1 : 0, cl = l & 1;
+    const int pl = l < NJ2 ? TP::parent(jl) : -1, chl = l < NJ2 ? jl + 1 : -1;
+    const double epl = cl == 0 ? -sh.arm[jl][1] : sh.arm[jl][0];
+    const double ecl = cl == 0 ? sh.arm[jl][3] : -sh.arm[jl][2];
     auto y = [&](int r) {
-        if (l < NJ2) return sh.minv[r] * jrow(l, r);
-        if (l < NJ2 + NQ) return l - NJ2 == r ? sh.minv[r] : 0.0;
-        return sh.f[r];
+        const int b = r / 3, q = r - 3 * b;
+        double w = l - NJ2 == r || l == W - 1 ? 1.0 : 0.0;
+        const double wp = q == 2 ? epl : (q == cl ? 1.0 : 0.0);
+        const double wc = q == 2 ? ecl : (q == cl ? -1.0 : 0.0);
+        if (b == pl) w = wp;
+        if (b == chl) w = wc;
+        return base[r] * w;
     };
     double col[NJ2];
 #pragma unroll
@@ -238,7 +241,11 @@ __device__ __forceinline__ void impact_dense(ImpShared<TP>& sh, int lane) {
         const double ep = c == 0 ? -sh.arm[j][1] : sh.arm[j][0];
         const double ec = c == 0 ? -sh.arm[j][3] : sh.arm[j][2];
         col[i] = (y(3 * p + c) + y(3 * p + 2) * ep) - (y(3 * ch + c) + y(3 * ch + 2) * ec);
-        asm volatile("" ::: "memory");   // (read the arms row by row, keep none)
+        // (a few rows at a time: the reads of all of them do not fit the registers)
+        if (i % 4 == 3) {
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
 #pragma unroll
     for (int kk = 0; kk < NJ2; ++kk) {
@@ -253,10 +260,20 @@ __device__ __forceinline__ void impact_dense(ImpShared<TP>& sh, int lane) {
 #pragma unroll
         for (int i = 0; i < NJ2; ++i) sh.lam[i] = -col[i];
     lds_sync();
-    if (lane < NQ) {
+    if (lane < NQ) {   // (the joints at the row's body)
+        const int b = lane / 3, q = lane - 3 * b;
         double jt = 0.0;
-#pragma unroll 1
-        for (int i = 0; i < NJ2; ++i) jt += jrow(i, lane) * sh.lam[i];
+#pragma unroll
+        for (int e = 0; e < TP::ADJ; ++e) {
+            bool par;
+            const int j = TP::slot_joint(b, e, par);
+            if (j < 0) continue;
+            const double lx = sh.lam[2 * j], ly = sh.lam[2 * j + 1];
+            const double ax = par ? sh.arm[j][0] : sh.arm[j][2];
+            const double ay = par ? sh.arm[j][1] : sh.arm[j][3];
+            const double v = q == 0 ? lx : (q == 1 ? ly : ax * ly - ay * lx);
+            jt += par ? v : -v;
+        }
         sh.vs[lane] = sh.f[lane] + sh.minv[lane] * jt;
     }
 }
@@ -566,7 +583,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
                 bx[q] = sg[q] * ((du[0] - du[2] * ay[q]) - ax[q] * om);
                 by[q] = sg[q] * ((du[1] + du[2] * ax[q]) - ay[q] * om);
             }
-#pragma unroll 1
+#pragma unroll 2
             for (int rb = 0; rb < NB; ++rb)
 #pragma unroll
                 for (int q3 = 0; q3 < 3; ++q3) {
