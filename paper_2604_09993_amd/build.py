@@ -10,10 +10,10 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcis.so")
 SOURCES = ["cis.hip", "cis_adjoint.hip", "cis_batch.hip", "cis_blocked.hip", "cis_split.hip",
            "cis_gradient.hip",
-           "cis_impact.hip", "cis_rkf.hip", "cis_paper.hip", "cis_paper_dense.hip", "cis_debug.hip",
+           "cis_impact.hip", "cis_rkf.hip", "cis_paper.hip", "cis_debug.hip",
            "cis_host.cpp", "cis_ldl.cpp"]
 HEADERS = ["cis_model.hpp", "cis_body.hpp", "cis_host.hpp", "cis_launch.hpp",
-           "cis_pack.hpp", "cis_reduced.hpp", "cis_paper.hpp",
+           "cis_pack.hpp", "cis_reduced.hpp", "cis_paper.hpp", "cis_paper_dense.hpp",
            "cis_debug.hpp",
            os.path.join("..", "..", "include", "cis.h")]
 

@@ -31,6 +31,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 #include <utility>
 
 #include "../../include/cis.h"
@@ -40,6 +41,7 @@
 #include "cis_model.hpp"
 #include "cis_pack.hpp"
 #include "cis_paper.hpp"
+#include "cis_paper_dense.hpp"
 #include "cis_reduced.hpp"
 
 namespace cis {
@@ -82,18 +84,28 @@ struct PShared {
 // Bound by the serial chain of a stage (two sines, nine root estimates, six divisions,
 // eight shift sums), 3.4 us of it.  1,603 quad13 intervals, K = 20: 270 us; one interval
 // per wave with a 24 x 24 Gauss-Jordan elimination took 1,650 us.
+// ROWS: the joint rows' form too, one interval per workgroup (the grid has one for each
+// of them, and the legs take the first quarter).
 // ---------------------------------------------------------------------------
-template <class TP>
+template <class TP, bool ROWS>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1)))
     k_paper_rec(PaperArgs a, MConst<TP::NB, TP::NJ, TP::NC> mc) {
     constexpr int NJ = TP::NJ, NC = TP::NC, NQ = TP::NQ, N6 = TP::N6;
     constexpr int NX = TP::NX, NY = TP::NY, D = TP::D;
     using R = PRec<TP>;
     using SH = PShared<TP>;
-    __shared__ SH sh;
-    if (heavy_link<TP>(a.prm + 2)) return;
-    const int me = threadIdx.x;
-    const int want = 4 * xcd_slot(blockIdx.x, gridDim.x) + (me >> 4);
+    __shared__ union {
+        SH legs;
+        std::conditional_t<ROWS, PDenseShared<TP>, char> rows;
+    } lds;
+    if (heavy_link<TP>(a.prm + 2)) {
+        if constexpr (ROWS) paper_dense_rec<TP>(a, mc, lds.rows, xcd_slot(blockIdx.x, gridDim.x));
+        return;
+    }
+    SH& sh = lds.legs;
+    const int me = threadIdx.x, waves = (a.N + 3) / 4;
+    if ((int)blockIdx.x >= waves) return;
+    const int want = 4 * xcd_slot(blockIdx.x, waves) + (me >> 4);
     const bool on = want < a.N;   // spare rows repeat the last interval
     const int k = on ? want : a.N - 1;
     const int64_t ldn = a.ldn, ldi = a.ldi;
@@ -491,6 +503,12 @@ __device__ __forceinline__ void pfma4(double& a0, double& a1, double& a2, double
                                                  v[I2 >> 4], v[I3 >> 4], x0, x1, x2, x3);
 }
 
+// Whether k_paper_tan holds the joint rows' form too: with three links the two do not
+// fit the registers (120 bytes of scratch: 12,800 quad13 intervals 8.1 -> 9.9 ms), and
+// that form has a launch of its own, which returns at once for other masses.
+template <class TP>
+constexpr bool PAPER_ONE = TP::D < 3;
+
 // What a tangent lane is: hold weights, and its control's selection on this leg.
 template <class TP>
 struct PColumn {
@@ -670,10 +688,17 @@ __global__ void __launch_bounds__(64 * TP::L) __attribute__((amdgpu_waves_per_eu
     constexpr int N6 = TP::N6, NQ = TP::NQ, M = TP::M, D = TP::D, L = TP::L, LB = TP::LB;
     constexpr int NX = TP::NX, NC = TP::NC, NJ = TP::NJ;
     using R = PRec<TP>;
-    __shared__ double xch[2][3 * L * 64];   // in turn, one barrier per stage
-    if (heavy_link<TP>(a.prm + 2)) return;
+    __shared__ union {
+        double xch[2][3 * L * 64];   // in turn, one barrier per stage
+        std::conditional_t<PAPER_ONE<TP>, PDenseTan<TP>, char> rows;
+    } lds;
     int k, cb;
     unit_item(xcd_slot(blockIdx.x, gridDim.x), a.N, TP::NBLK, k, cb);
+    if (heavy_link<TP>(a.prm + 2)) {
+        if constexpr (PAPER_ONE<TP>) paper_dense_tan<TP>(a, lds.rows, k, cb);
+        return;
+    }
+    auto& xch = lds.xch;
     const int tid = threadIdx.x, lane = tid & 63;
     const int leg = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = cb * 64 + lane;
@@ -772,19 +797,58 @@ __global__ void __launch_bounds__(64 * TP::L) __attribute__((amdgpu_waves_per_eu
     if (leg == 0) out[((int64_t)(N6 + 4 * NC) * cstride + c0) * ldi + k] = yct;
 }
 
+// The joint rows' form by itself.  (The columns: one workgroup for each part of each interval:
+// in a loop over them the records' reads are no longer scalar loads, 57 -> 815 ms for
+// 12,800 quad13 intervals.)
+template <class TP>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+    k_paper_rec_rows(PaperArgs a, MConst<TP::NB, TP::NJ, TP::NC> mc) {
+    __shared__ PDenseShared<TP> lds;
+    if (heavy_link<TP>(a.prm + 2))
+        paper_dense_rec<TP>(a, mc, lds, xcd_slot(blockIdx.x, gridDim.x));
+}
+
+template <class TP>
+__global__ void __launch_bounds__(64 * TP::L) __attribute__((amdgpu_waves_per_eu(2)))
+    k_paper_tan_rows(PaperArgs a) {
+    __shared__ PDenseTan<TP> lds;
+    if (!heavy_link<TP>(a.prm + 2)) return;
+    int k, cb;
+    unit_item(xcd_slot(blockIdx.x, gridDim.x), a.N, TP::NBLK, k, cb);
+    paper_dense_tan<TP>(a, lds, k, cb);
+}
+
 template <int L, int D>
 static cis_status launch_paper_t(const cis_model* m, const PaperArgs& a, hipStream_t stream) {
     if constexpr (L >= 1 && D >= 1) {
         using TP = PTopo<L, D>;
         const auto mc = make_const<TP::NB, TP::NJ, TP::NC>(m);
-        hipLaunchKernelGGL(k_paper_rec<TP>, dim3((a.N + 3) / 4), dim3(64), 0, stream, a, mc);
+        // The masses are on the device, so both forms are launched and one returns at once.
+        // Up to one interval per SIMD the records of both take one launch (with a launch
+        // each, a call of 8 hopper intervals, K = 1, took 33 us instead of 28); beyond, the
+        // joint rows' form needs the second wave per SIMD that the registers of the other
+        // do not leave (a heavy tip, hopper, K = 20: 1,000 intervals 353 us in one launch
+        // and 355 in two, 5,000 1,452 and 1,043).
+        if (a.N <= 4 * device_cus()) {
+            hipLaunchKernelGGL((k_paper_rec<TP, true>), dim3(a.N), dim3(64), 0, stream, a, mc);
+        } else {
+            hipLaunchKernelGGL((k_paper_rec<TP, false>), dim3((a.N + 3) / 4), dim3(64), 0, stream,
+                               a, mc);
+            hipLaunchKernelGGL(k_paper_rec_rows<TP>, dim3(a.N), dim3(64), 0, stream, a, mc);
+        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(CIS_ERR_HIP, "k_paper_rec launch: %s", hipGetErrorString(e));
         hipLaunchKernelGGL(k_paper_tan<TP>, dim3(a.N * TP::NBLK), dim3(64 * TP::L), 0, stream, a);
         e = hipGetLastError();
         if (e != hipSuccess) return fail(CIS_ERR_HIP, "k_paper_tan launch: %s", hipGetErrorString(e));
-        // the masses are on the device: both forms are launched, and one returns
-        return paper_dense_launch(m, a, stream);
+        if constexpr (!PAPER_ONE<TP>) {
+            hipLaunchKernelGGL(k_paper_tan_rows<TP>, dim3(a.N * TP::NBLK), dim3(64 * TP::L), 0,
+                               stream, a);
+            e = hipGetLastError();
+            if (e != hipSuccess)
+                return fail(CIS_ERR_HIP, "k_paper_tan_rows launch: %s", hipGetErrorString(e));
+        }
+        return CIS_OK;
     } else {
         return fail(CIS_ERR_UNSUPPORTED, "the paper-dynamics form needs legs with links");
     }
@@ -792,7 +856,8 @@ static cis_status launch_paper_t(const cis_model* m, const PaperArgs& a, hipStre
 
 template <int L, int D>
 static int64_t paper_elems_t(int K) {
-    if constexpr (L >= 1 && D >= 1) return PRec<PTopo<L, D>>::per_interval(K);
+    if constexpr (L >= 1 && D >= 1)
+        return std::max(PRec<PTopo<L, D>>::per_interval(K), PDenseRec<PTopo<L, D>>::per_interval(K));
     else return -1;
 }
 
@@ -823,7 +888,7 @@ extern "C" cis_status cis_paper_workspace_size(const cis_model* m, const cis_sha
                     sh->substeps);
     if (sh->dtype != CIS_F64)
         return fail(CIS_ERR_DTYPE, "cis_paper_workspace_size: the paper-dynamics form is FP64 only");
-    const int64_t per = std::max(paper_elems(m, sh->substeps), paper_dense_elems(m, sh->substeps));
+    const int64_t per = paper_elems(m, sh->substeps);
     if (per < 0) return fail(CIS_ERR_UNSUPPORTED, "paper-dynamics form: the model has no legs with links");
     *bytes = (size_t)per * (size_t)sh->N * sizeof(double);
     return CIS_OK;

@@ -1,5 +1,5 @@
 // What the two forms of the paper-faithful dynamics (cis_paper.hip: legs,
-// cis_paper_dense.hip: joint rows) share.
+// cis_paper_dense.hpp: joint rows) share.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -46,10 +46,5 @@ __device__ __forceinline__ void plds_sync() {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
-
-// Joint rows' form (dense): records of an interval in elements, and its launches,
-// which return at once unless heavy_link (cis_pack.hpp) holds (the other form's if it does).
-int64_t paper_dense_elems(const cis_model* m, int K);
-cis_status paper_dense_launch(const cis_model* m, const PaperArgs& a, hipStream_t stream);
 
 }  // namespace cis

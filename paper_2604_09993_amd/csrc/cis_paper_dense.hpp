@@ -1,6 +1,6 @@
 // Joint rows' form of the paper-faithful dynamics (cis_paper.hip states the dynamics;
 // arxiv 2604.09993, Sec. II-A eq. joint-cnstr-acc), for models with a link much
-// heavier than what lies between it and the torso (heavy_link, cis_paper.hpp).
+// heavier than what lies between it and the torso (heavy_link, cis_pack.hpp).
 //
 // With M v' = W + J^T R phi + grad h^T lambda and grad h v' + c = 0
 // (c_j = -w_p^2 a_p + w_c^2 a_c), the joint forces solve A lambda =
@@ -9,26 +9,22 @@
 //     dv' = M^-1 u - Wm b,   Wm = M^-1 grad h^T A^-1,
 //     u = dF + dgrad_h^T lambda,   b = grad h M^-1 u + dgrad_h v' + dc,
 // where u and b are local: u on the bodies z touches and their joint
-// neighbours, b on the joints at those bodies.  Two kernels:
-//   k_paper_dense_rec : one wave per interval; the nominal RK4 on body lanes, and
+// neighbours, b on the joints at those bodies.  The two kernels of cis_paper.hip take
+// these parts instead of their own where the masses ask for it (a launch of each form
+// that returns at once took 2 us of every call, and 28 us of 12,800 quad13 intervals):
+//   paper_dense_rec : one wave per interval; the nominal RK4 on body lanes, and
 //                 per stage the values, A and its Gauss-Jordan elimination in
 //                 registers (one lane per column of [A | grad h M^-1 | r]),
 //                 which leave Wm and lambda; a stage record to device memory;
-//   k_paper_dense_tan : per (interval, block of 64 columns of [Phi_x | B- | B+ | S])
+//   paper_dense_tan : per (interval, block of 64 columns of [Phi_x | B- | B+ | S])
 //                 one wave per leg, a lane holding its column on the torso and
 //                 leg rows; per stage u on those rows (the torso's hip terms
 //                 of the other legs through LDS), b on the leg's joints (all
 //                 joints through LDS), then dv' with the record's Wm rows read
 //                 by scalar loads.
+#pragma once
 #include <hip/hip_runtime.h>
 
-#include <cstring>
-#include <utility>
-
-#include "../../include/cis.h"
-#include "cis_debug.hpp"
-#include "cis_host.hpp"
-#include "cis_launch.hpp"
 #include "cis_model.hpp"
 #include "cis_paper.hpp"
 
@@ -100,19 +96,15 @@ struct PDenseShared {
     double om[TP::NY];                 // Omega at the stage
 };
 
-// ---------------------------------------------------------------------------
-// k_paper_dense_rec: interval k, one wave.
-// ---------------------------------------------------------------------------
+// Interval k, one wave.
 template <class TP>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
-    k_paper_dense_rec(PaperArgs a, MConst<TP::NB, TP::NJ, TP::NC> mc) {
+__device__ __forceinline__ void paper_dense_rec(const PaperArgs& a,
+                                                const MConst<TP::NB, TP::NJ, TP::NC>& mc,
+                                                PDenseShared<TP>& sh, int k) {
     constexpr int NB = TP::NB, NJ = TP::NJ, NC = TP::NC, NQ = TP::NQ, N6 = TP::N6;
     constexpr int NX = TP::NX, NY = TP::NY, M = TP::M, NJ2 = TP::NJ2;
     using R = PDenseRec<TP>;
-    __shared__ PDenseShared<TP> sh;
-    if (!heavy_link<TP>(a.prm + 2)) return;
     const int lane = threadIdx.x;
-    const int k = xcd_slot(blockIdx.x, gridDim.x);
     const int64_t ldn = a.ldn, ldi = a.ldi;
     double* rec = a.rec + (int64_t)k * R::per_interval(a.K);
     for (int e = lane; e < NX; e += 64) {
@@ -391,7 +383,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 }
 
 // ---------------------------------------------------------------------------
-// k_paper_dense_tan: columns [64 cb, 64 cb + 64) of interval k, wave `leg`.  Local
+// paper_dense_tan: columns [64 cb, 64 cb + 64) of interval k, wave `leg`.  Local
 // body lb = 0 is the torso, lb = 1..D the links of the leg; rows zs[3 lb + q]
 // (pose) and zs[3 LB + 3 lb + q] (velocity); the leg's contact rows y[0..3]
 // and its share of the violation row y[4].
@@ -603,17 +595,20 @@ __device__ __forceinline__ void paper_dense_stage(PDenseLane<TP>& z, const doubl
 #undef ZV
 }
 
+// LDS of the tangent part: the exchange areas, and the sink of the warm-up copies.
 template <class TP>
-__global__ void __launch_bounds__(64 * TP::L) __attribute__((amdgpu_waves_per_eu(2)))
-    k_paper_dense_tan(PaperArgs a) {
+struct PDenseTan {
+    double xch[(TP::L + 2 * TP::NJ) * 64];
+    double sink[PWarm<TP>::PW * PWarm<TP>::NT];
+};
+
+template <class TP>
+__device__ __forceinline__ void paper_dense_tan(const PaperArgs& a, PDenseTan<TP>& sh, int k,
+                                                int cb) {
     constexpr int N6 = TP::N6, NQ = TP::NQ, M = TP::M, D = TP::D, L = TP::L, LB = TP::LB;
     constexpr int NX = TP::NX, NC = TP::NC;
     using R = PDenseRec<TP>;
-    __shared__ double xch[(TP::L + 2 * TP::NJ) * 64];
-    __shared__ double sink[PWarm<TP>::PW * PWarm<TP>::NT];
-    if (!heavy_link<TP>(a.prm + 2)) return;
-    int k, cb;
-    unit_item(xcd_slot(blockIdx.x, gridDim.x), a.N, TP::NBLK, k, cb);
+    double *xch = sh.xch, *sink = sh.sink;
     const int tid = threadIdx.x, lane = tid & 63;
     const int leg = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = cb * 64 + lane;
@@ -682,48 +677,6 @@ __global__ void __launch_bounds__(64 * TP::L) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
     for (int q = 0; q < 4; ++q) out[((int64_t)(N6 + 4 * leg + q) * cstride + c0) * ldi + k] = z.yc[q];
     if (leg == 0) out[((int64_t)(N6 + 4 * NC) * cstride + c0) * ldi + k] = yct;
-}
-
-template <int L, int D>
-static cis_status launch_dense_t(const cis_model* m, const PaperArgs& a, hipStream_t stream) {
-    if constexpr (L >= 1 && D >= 1) {
-        using TP = PTopo<L, D>;
-        const auto mc = make_const<TP::NB, TP::NJ, TP::NC>(m);
-        hipLaunchKernelGGL(k_paper_dense_rec<TP>, dim3(a.N), dim3(64), 0, stream, a, mc);
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess) {
-            hipLaunchKernelGGL(k_paper_dense_tan<TP>, dim3(a.N * TP::NBLK), dim3(64 * TP::L), 0,
-                               stream, a);
-            e = hipGetLastError();
-        }
-        if (e != hipSuccess)
-            return fail(CIS_ERR_HIP, "k_paper_dense launch: %s", hipGetErrorString(e));
-        return CIS_OK;
-    } else {
-        return fail(CIS_ERR_UNSUPPORTED, "the paper-dynamics form needs legs with links");
-    }
-}
-
-cis_status paper_dense_launch(const cis_model* m, const PaperArgs& a, hipStream_t stream) {
-#define CIS_DENSE(LL, DD) \
-    if (m->L == LL && m->D == DD) return launch_dense_t<LL, DD>(m, a, stream);
-    CIS_TOPOLOGIES(CIS_DENSE)
-#undef CIS_DENSE
-    return fail(CIS_ERR_UNSUPPORTED, "k_paper_dense: topology has no compiled kernel");
-}
-
-template <int L, int D>
-static int64_t dense_elems_t(int K) {
-    if constexpr (L >= 1 && D >= 1) return PDenseRec<PTopo<L, D>>::per_interval(K);
-    else return -1;
-}
-
-int64_t paper_dense_elems(const cis_model* m, int K) {
-#define CIS_DENSE_SZ(LL, DD) \
-    if (m->L == LL && m->D == DD) return dense_elems_t<LL, DD>(K);
-    CIS_TOPOLOGIES(CIS_DENSE_SZ)
-#undef CIS_DENSE_SZ
-    return -1;
 }
 
 }  // namespace cis

@@ -72,3 +72,19 @@ def test_fixed_body_impact(legs, depth, terrain, body, sign):
     ref = oracle_ref(model, d, [0, 1, 2])
     errs = {k: block_err(res[k], ref[k], PHI64) for k in ref}
     assert all(e <= TOL64 for e in errs.values()), errs
+
+
+@pytest.mark.parametrize("ratio", [1.0, 100.0])
+@pytest.mark.parametrize("legs,depth,terrain", [(1, 2, "sinusoid"), (2, 3, "flat")])
+def test_paper_record_launches(legs, depth, terrain, ratio):
+    """One launch holds both forms' records up to an interval per SIMD, two beyond."""
+    import torch
+    line = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    model, rng = _model(legs, depth, terrain)
+    for N in (line, line + 1):
+        print(f"[gpu] paper records {legs}x{depth} N={N} ratio={ratio}", flush=True)
+        data = synth.gen_paper_nodes(model, N, rng, T=0.02 * N)
+        data["p"] = _weigh(model, data["p"], depth, depth, ratio)
+        res = run_paper(model, data, 1)
+        _finite(res)
+        check_paper(model, data, 1, res, ks=[0, 1, N // 3, N - 2, N - 1])
