@@ -522,10 +522,10 @@ cis_status cis_batch_plan_info(const cis_batch_plan *plan, int32_t g, int32_t *g
  * (architecture, compute units), the topology, dtype, operations, the
  * group's number of intervals, its substep range and, with the reverse sweep,
  * its largest checkpoint spacing.  Found: the choices are used without timing.
- * Not found: the group is timed and its choices are added to the file (JSON,
- * written through a temporary file; a missing or unreadable file counts as
- * empty).  *from_cache = 1 when every tuned choice of group g came from the
- * file.  Errors: CIS_ERR_NULL, CIS_ERR_DIM (g out of range).
+ * What is not found is timed and added to the file (JSON, written through a
+ * temporary file; a missing or unreadable file counts as empty), unless a schedule
+ * bit narrows that choice.  *from_cache = 1 when group g has an entry and nothing of
+ * it was timed.  Errors: CIS_ERR_NULL, CIS_ERR_DIM (g out of range).
  */
 cis_status cis_batch_plan_tuned_from_cache(const cis_batch_plan *plan, int32_t g,
                                            int32_t *from_cache);

@@ -616,8 +616,9 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
         g.dev.sums = g.split_ok ? (void*)(p->recmem + (g.rec_base + g.sums_at) * es) : nullptr;
         cis_status st;
         std::string key;
-        TuneChoice want, made;
-        bool cached_all = false;   // the key's entry is there and every choice from it
+        TuneChoice want, made;     // the file's choices, and with what is timed here
+        bool found = false, timed = false;
+        bool record = false;       // something was timed with no bit to hold it
         if (!cpath.empty()) {
             int kmin = 1 << 30, kmax = 0, cmx = 1;
             for (int i : g.trajs) {
@@ -632,8 +633,8 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
             key = kb;
             auto it = cache.find(key);
             if (it != cache.end()) {
-                want = it->second;
-                cached_all = true;
+                want = made = it->second;
+                found = true;
             }
         }
         if (ops & CIS_BATCH_DISCRETIZE) {
@@ -698,7 +699,7 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
                     }
             }
             if (cands.size() > 1 && !hit) {
-                cached_all = false;
+                timed = true;
                 float tbest = -1.f;
                 for (size_t c = 0; c < cands.size(); ++c) {
                     const float t = cands[c].split ? time_pair(cands[c].l, cands[c].lb, hs, 3)
@@ -718,9 +719,12 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
             g.disc = cands[best].l;
             g.split = cands[best].split;
             if (g.split) g.disc_b = cands[best].lb;
-            made.split = g.split ? 1 : 0;
-            made.waves = g.disc_waves;
-            made.persist = g.persist_blocks > 0 ? 1 : 0;
+            if (cands.size() > 1 && !hit && !waves_force && !split_force) {
+                made.split = g.split ? 1 : 0;
+                made.waves = g.disc_waves;
+                made.persist = g.persist_blocks > 0 ? 1 : 0;
+                record = true;
+            }
         }
         if (ops & CIS_BATCH_ADJOINT) {
             BatchGroupDev dd = g.dev;
@@ -738,7 +742,7 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
             } else if (st == CIS_OK && sched == CIS_SCHED_TUNE && !def_force && want.def_lane >= 0) {
                 g.def = want.def_lane ? def_lane : def_body;
             } else if (st == CIS_OK && sched == CIS_SCHED_TUNE && !def_force) {
-                cached_all = false;
+                timed = record = true;
                 const float tb = time_launch(def_body, hs, 3);
                 const float tl = time_launch(def_lane, hs, 3);
                 if (tb < 0.f || tl < 0.f) {
@@ -746,6 +750,7 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
                     return fail(CIS_ERR_HIP, "cis_batch_plan_create: tuning launch failed");
                 }
                 if (tl < tb) g.def = def_lane;
+                made.def_lane = tl < tb ? 1 : 0;
             }
             int cmax_g = 1, cmin_g = 1 << 30;
             for (int i : g.trajs) {
@@ -765,13 +770,12 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
                 plan_free(p);
                 return st;
             }
-            made.def_lane = g.def.func == def_lane.func ? 1 : 0;
             int best = adj_force ? 4 - adj_force : 1;
             if (pack_adj) {
             } else if (sched == CIS_SCHED_TUNE && !adj_force && want.adj_waves >= 1 && want.adj_waves <= 4) {
                 best = 4 - want.adj_waves;
             } else if (sched == CIS_SCHED_TUNE && !adj_force) {
-                cached_all = false;
+                timed = record = true;
                 if (g.def.launch(hs) != hipSuccess || hipStreamSynchronize(hs) != hipSuccess) {
                     plan_free(p);
                     return fail(CIS_ERR_HIP, "cis_batch_plan_create: tuning launch failed");
@@ -789,15 +793,15 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
                         best = w;
                     }
                 }
+                made.adj_waves = 4 - best;
             }
             g.adj = adjv[best];
             g.adj_waves = adjv[best].block.x / 64;
             g.def_waves = g.def.block.x / 64;
-            made.adj_waves = 4 - best;
         }
         if (!cpath.empty()) {
-            g.from_cache = cached_all;
-            if (!cached_all) {
+            g.from_cache = found && !timed;
+            if (record) {
                 cache[key] = made;
                 cache_dirty = true;
             }
