@@ -366,7 +366,7 @@ typedef struct {
  * fastest in *choice and leaves its outputs in A, Bm, Bp, S, defect, xprop.
  * With CIS_TUNE_CACHE naming a file the choice is looked up first (then
  * nothing is timed) and recorded after tuning, keyed by device, topology,
- * dtype, N and K.  NOT a hot call: allocates the largest workspace any
+ * terrain (flat or not), dtype, N and K.  NOT a hot call: allocates the largest workspace any
  * candidate needs, synchronizes the stream and frees it.  shape->layout must
  * be 0.  Errors: those of the candidates' entry points, CIS_ERR_NULL for a
  * missing choice, CIS_ERR_HIP.
@@ -519,8 +519,8 @@ cis_status cis_batch_plan_info(const cis_batch_plan *plan, int32_t g, int32_t *g
  * CIS_TUNE_CACHE naming a file, cis_batch_plan_create looks up each model
  * group's choices (discretize form and register budget, grid or persistent
  * launch, defects form, reverse-sweep waves) under a key made of the device
- * (architecture, compute units), the topology, dtype, operations, the
- * group's number of intervals, its substep range and, with the reverse sweep,
+ * (architecture, compute units), the topology, the terrain's kind, dtype, operations,
+ * the group's number of intervals, its substep range and, with the reverse sweep,
  * its largest checkpoint spacing.  Found: the choices are used without timing.
  * What is not found is timed and added to the file (JSON, written through a
  * temporary file; a missing or unreadable file counts as empty), unless a schedule

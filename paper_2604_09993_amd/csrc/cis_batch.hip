@@ -58,7 +58,7 @@ namespace cis {
 //                                        "def_lane": d, "adj_waves": a,
 //                                        "blocks": b, "compose": c,
 //                                        "form": f, "layout": l}, ...}}
-// keyed by device (architecture, compute units), topology, dtype, operations,
+// keyed by device (architecture, compute units), topology, terrain, dtype, operations,
 // work-list length and substep range (and checkpoint spacing with the reverse
 // sweep); -1 marks a choice that was not made.  A missing or unreadable file
 // is an empty cache; writes replace the file through a temporary.
@@ -627,8 +627,8 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
                 cmx = std::max(cmx, p->ckpt_every[i]);
             }
             char kb[256];
-            std::snprintf(kb, sizeof(kb), "%s|L%dD%d|%s|ops%d|items%zu|K%d-%d|C%d", dtag.c_str(),
-                          g.model->L, g.model->D, dtype == CIS_F64 ? "f64" : "f32", (int)ops,
+            std::snprintf(kb, sizeof(kb), "%s|L%dD%d|%s|%s|ops%d|items%zu|K%d-%d|C%d",
+                          dtag.c_str(), g.model->L, g.model->D, terrain_tag(g.model), dtype == CIS_F64 ? "f64" : "f32", (int)ops,
                           g.items.size(), kmin, kmax, (ops & CIS_BATCH_ADJOINT) ? cmx : 0);
             key = kb;
             auto it = cache.find(key);

@@ -420,8 +420,8 @@ extern "C" cis_status cis_single_tune(const cis_model* model, const cis_shape* s
     // cache lookup
     const char* cpath = std::getenv("CIS_TUNE_CACHE");
     char key[256];
-    std::snprintf(key, sizeof(key), "single|%s|L%dD%d|%s|N%d|K%d", device_tag(dev).c_str(),
-                  model->L, model->D, f64 ? "f64" : "f32", shape->N, K);
+    std::snprintf(key, sizeof(key), "single|%s|L%dD%d|%s|%s|N%d|K%d", device_tag(dev).c_str(),
+                  model->L, model->D, terrain_tag(model), f64 ? "f64" : "f32", shape->N, K);
     bool hit = false;
     if (cpath && *cpath) {
         std::lock_guard<std::mutex> lk(g_cache_mu);

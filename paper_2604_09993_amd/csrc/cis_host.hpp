@@ -44,6 +44,8 @@ std::map<std::string, TuneChoice> cache_read(const std::string& path);
 bool cache_write(const std::string& path, const std::map<std::string, TuneChoice>& m);
 // "<architecture>/<compute units>cu" of a device
 std::string device_tag(int dev);
+// the terrain's kind, by which the two-launch forms differ
+inline const char* terrain_tag(const cis_model* m) { return m->A == 0.0 ? "flat" : "sinusoid"; }
 // compute units of the current device (cis.hip)
 int device_cus();
 

@@ -66,3 +66,22 @@ def test_a_forced_part_leaves_the_rest(tmp_path, monkeypatch):
     (f,) = _entries(path).values()
     assert f["def_lane"] == e["def_lane"] and f["adj_waves"] >= 1
     assert _groups(api, trajs, ("adjoint",))[0]["from_cache"] == 1
+
+
+def test_entries_by_terrain(tmp_path, monkeypatch):
+    """A flat and a sinusoidal model of one topology, in one plan and for the
+    single-trajectory tuner, have an entry each."""
+    from paper_2604_09993_amd import api
+    print("[gpu] tune cache by terrain", flush=True)
+    path = tmp_path / "tune.json"
+    monkeypatch.setenv("CIS_TUNE_CACHE", str(path))
+    trajs = [_traj(api, synth.legged_model("t22", 2, 2, np.random.default_rng(713),
+                                           terrain=terrain)) for terrain in ("flat", "sinusoid")]
+    g = _groups(api, trajs, ("discretize",))
+    assert [x["from_cache"] for x in g] == [0, 0] and len(_entries(path)) == 2
+    assert [x["from_cache"] for x in _groups(api, trajs, ("discretize",))] == [1, 1]
+    for i, t in enumerate(trajs):
+        args = (t["cm"], t["X"], t["U"], t["s"], t["params"], t["K"])
+        assert not api.single_tune(*args)[1]["from_cache"]
+        assert len(_entries(path)) == 3 + i
+        assert api.single_tune(*args)[1]["from_cache"]
