@@ -470,10 +470,12 @@ enum { CIS_SCHED_SPLIT = 0x800, CIS_SCHED_FUSED = 0x1000 };
 /*
  * Create a plan for n_traj trajectories (all of one dtype; CIS_BATCH_ADJOINT
  * needs CIS_F64).  ckpt_every: substeps between the checkpoints of the reverse
- * sweep; it must divide every trajectory's K, or be 0 to choose, per trajectory: 1
- * (models with legs with links, no CIS_SCHED_ADJ bit, checkpoints of at most 16 GiB
- * and a quarter of the free memory) or the largest divisor of K not above 8.  graph != 0 also builds
- * the HIP graphs used by cis_batch_graph_run.
+ * sweep; it must divide every trajectory's K, or be 0 to choose by the sizes: for
+ * models with legs with links and no CIS_SCHED_ADJ bit, 1 while these checkpoints take
+ * at most 4 GiB, and beyond it one spacing per model (a common divisor of its K up to
+ * 16, if that takes at most 4 GiB or no more than what follows); else, and where
+ * memory for the former cannot be had, the largest divisor of K not above 8 per
+ * trajectory.  graph != 0 also builds the HIP graphs used by cis_batch_graph_run.
  * Errors: CIS_ERR_NULL, CIS_ERR_DIM, CIS_ERR_LAYOUT, CIS_ERR_DTYPE,
  * CIS_ERR_UNSUPPORTED (as for the single-trajectory calls, with the offending
  * trajectory named by cis_last_error), CIS_ERR_HIP (allocation, upload,

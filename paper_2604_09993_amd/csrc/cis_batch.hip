@@ -9,6 +9,7 @@
 #include <fstream>
 #include <map>
 #include <mutex>
+#include <numeric>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -187,6 +188,10 @@ int auto_ckpt(int K) {
         if (K % c == 0) return c;
     return 1;
 }
+
+// Checkpoints of every substep, in bytes, that a plan takes unasked: 330,000 quad13
+// intervals, K = 20.
+constexpr size_t DENSE_CKPT_MAX = (size_t)4 << 30;
 
 }  // namespace
 
@@ -467,42 +472,76 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
     p->ckpt_every.assign(n_traj, 1);
     p->ckpt_off.assign(n_traj, 0);
     p->ws_off.assign(n_traj, 0);
-    if (ops & CIS_BATCH_ADJOINT) {
-        // The packed sweep runs fastest from every substep's start (12,800 quad13
-        // intervals, K = 20: 0.57 ms with 160 MB of them, and one wave less than the
-        // forms that integrate the starts again); sparser ones are kept where these
-        // take more than 16 GiB or a quarter of the free memory.
-        size_t dense = 0, avail = 0, total = 0;
-        for (int i = 0; i < n_traj; ++i)
-            dense += (size_t)trajs[i].substeps * trajs[i].model->n * trajs[i].ld_int * es;
-        if (hipMemGetInfo(&avail, &total) != hipSuccess) avail = 0;
-        const bool every = !adj_force && dense <= std::min((size_t)16 << 30, avail / 4);
+    // Spacing of the checkpoints, where the caller leaves it open.  The packed sweep runs
+    // fastest from every substep's start (12,800 quad13 intervals, K = 20: 0.57 ms with
+    // 160 MB of them, and one wave less than the forms that integrate the starts again):
+    // level 0, up to DENSE_CKPT_MAX.  Level 1: one spacing per model that it can take (a
+    // divisor of all its substep counts) and that keeps no more than either that limit or
+    // level 2, the largest divisors not above 8.  The level goes by the sizes alone,
+    // except that an allocation which fails is tried again a level further.
+    const size_t tail = off;
+    auto ckpt_bytes = [&](int i, int C) {
+        return (size_t)(trajs[i].substeps / C) * trajs[i].model->n * trajs[i].ld_int * es;
+    };
+    auto place = [&](int level) {
+        off = tail;
+        for (const Group& g : p->groups) {
+            int gcd = 0;
+            size_t sparse = 0;
+            for (int i : g.trajs) {
+                gcd = std::gcd(gcd, (int)trajs[i].substeps);
+                sparse += ckpt_bytes(i, auto_ckpt(trajs[i].substeps));
+            }
+            int common = 0;   // 0: level 2
+            if (!adj_force && level < 2 && gradient_pack_supported(g.model)) {
+                common = level == 0 ? 1 : std::min(gcd, gradient_pack_max_ckpt());
+                while (gcd % common) --common;
+                size_t all = 0;
+                for (int i : g.trajs) all += ckpt_bytes(i, common);
+                if (level == 1 && all > std::max(sparse, DENSE_CKPT_MAX)) common = 0;
+            }
+            for (int i : g.trajs)
+                p->ckpt_every[i] = ckpt_every > 0 ? ckpt_every
+                                   : common > 0   ? common
+                                                  : auto_ckpt(trajs[i].substeps);
+        }
         for (int i = 0; i < n_traj; ++i) {
             const cis_traj& t = trajs[i];
-            const int C = ckpt_every > 0 ? ckpt_every
-                          : every && gradient_pack_supported(t.model) ? 1
-                                                                      : auto_ckpt(t.substeps);
-            p->ckpt_every[i] = C;
             p->ckpt_off[i] = off;
-            off = align_up(off + (size_t)(t.substeps / C) * t.model->n * t.ld_int * es);
+            off = align_up(off + ckpt_bytes(i, p->ckpt_every[i]));
             p->ws_off[i] = off;
             off = align_up(off + (size_t)(2 * t.model->m + t.model->np) * t.N * sizeof(double));
         }
+    };
+    constexpr int last = 2;
+    int level = last;
+    if (ops & CIS_BATCH_ADJOINT) {
+        size_t dense = 0;
+        for (int i = 0; i < n_traj; ++i)
+            if (gradient_pack_supported(trajs[i].model)) dense += ckpt_bytes(i, 1);
+        level = ckpt_every > 0 || adj_force ? last : dense <= DENSE_CKPT_MAX ? 0 : 1;
     }
-    hipError_t e = hipMalloc((void**)&p->dmem, off);
-    if (e != hipSuccess) {
-        plan_free(p);
-        return fail(CIS_ERR_HIP, "cis_batch_plan_create: hipMalloc(%zu): %s", off, hipGetErrorString(e));
+    for (;; ++level) {
+        if (ops & CIS_BATCH_ADJOINT) place(level);
+        const char* what = "";
+        size_t bytes = off;
+        hipError_t e = hipMalloc((void**)&p->dmem, off);
+        if (e == hipSuccess && rec_total > 0) {
+            what = " of the stage records";
+            bytes = rec_total * es;
+            e = hipMalloc((void**)&p->recmem, bytes);
+        }
+        if (e == hipSuccess) break;
+        (void)hipGetLastError();   // (reported below, or by nothing)
+        if (level >= last) {
+            plan_free(p);
+            return fail(CIS_ERR_HIP, "cis_batch_plan_create: hipMalloc(%zu)%s: %s", bytes, what,
+                        hipGetErrorString(e));
+        }
+        if (p->dmem) (void)hipFree(p->dmem);
+        p->dmem = nullptr;
     }
     unsigned char* d = p->dmem;
-    if (rec_total > 0) {
-        e = hipMalloc((void**)&p->recmem, rec_total * es);
-        if (e != hipSuccess) {
-            plan_free(p);
-            return fail(CIS_ERR_HIP, "cis_batch_plan_create: hipMalloc(%zu) of the stage records: %s",
-                        rec_total * es, hipGetErrorString(e));
-        }
-    }
 
     // host image of the descriptor part
     std::vector<unsigned char> img(host_part, 0);
@@ -580,7 +619,7 @@ extern "C" cis_status cis_batch_plan_create(const cis_traj* trajs, int32_t n_tra
             std::memcpy(&img[p->rdesc_off + i * sizeof(RedDesc)], &r, sizeof(r));
         }
     }
-    e = hipMemcpyAsync(d, img.data(), host_part, hipMemcpyHostToDevice, hs);
+    hipError_t e = hipMemcpyAsync(d, img.data(), host_part, hipMemcpyHostToDevice, hs);
     if (e == hipSuccess) e = hipStreamSynchronize(hs);
     if (e != hipSuccess) {
         plan_free(p);
