@@ -18,20 +18,23 @@ from . import _lib
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
     if stream is None:
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
+
+
+_CURRENT = contextlib.nullcontext()
 
 
 def _alloc_on(stream):
     """Allocate outputs and workspaces on the stream the kernels run on, so the
     caching allocator does not hand their memory to other work before the
     kernels have finished with it."""
-    return contextlib.nullcontext() if stream is None else torch.cuda.stream(stream)
+    return _CURRENT if stream is None else torch.cuda.stream(stream)
 
 
 class CisModel:
@@ -94,68 +97,73 @@ def _shape(X, s, K, ld_int=None, layout="rule"):
 
 
 def _check_inputs(cm, X, U, s, params):
-    dev = X.device
+    dev, dtype = X.device, X.dtype
     if dev.type != "cuda":
         raise ValueError("inputs must be GPU tensors")
     for t in (U, s, params):
-        if t is not None and (t.device != dev or t.dtype != X.dtype):
+        if t is not None and (t.device != dev or t.dtype != dtype):
             raise ValueError("all inputs must share device and dtype")
-    if X.shape[0] != cm.nx or s.dim() != 1 or X.shape[1] < s.shape[0] + 1:
+    Xs, ss = X.shape, s.shape
+    if Xs[0] != cm.nx or len(ss) != 1 or Xs[1] < ss[0] + 1:
         raise ValueError("X must be [nx, >= N+1] and s [N]")
-    if cm.m and (U is None or U.shape[0] != cm.m or U.stride(1) != 1 or U.stride(0) != X.stride(0)
-                 or U.shape[1] < s.shape[0] + 1):
-        raise ValueError("U must be [m, >= N+1] with the same ld_node as X")
+    if cm.m:
+        if U is None:
+            raise ValueError("U must be [m, >= N+1] with the same ld_node as X")
+        Us, Ud = U.shape, U.stride()
+        if Us[0] != cm.m or Ud[1] != 1 or Ud[0] != X.stride(0) or Us[1] < ss[0] + 1:
+            raise ValueError("U must be [m, >= N+1] with the same ld_node as X")
     if params.numel() != cm.np or not params.is_contiguous() or not s.is_contiguous():
         raise ValueError("params must hold P contiguous values and s must be contiguous")
 
 
-SPLIT_WS_MAX = 8 << 30   # bytes (12,800 quad13 intervals, K = 20, FP64: 2 GB)
+SPLIT_WS_MAX = 8 << 30   # bytes (12,800 quad13 intervals, K = 20, FP64: 0.81 GB on flat ground)
 
 
-def _split_workspace(cm, X, s, K, stream):
-    """Workspace of the two-launch form where that is the faster one, else None."""
-    sh = _shape(X, s, K)
+def _split_bytes(cm, sh):
+    """Workspace of the two-launch form where that is the faster one, else 0."""
     lib = _lib.load()
     split = ctypes.c_int32()
     _lib.check(lib.cis_discretize_prefers_split(cm.handle, ctypes.byref(sh), ctypes.byref(split)))
     if not split.value:
-        return None
+        return 0
     nbytes = ctypes.c_size_t()
-    if lib.cis_split_workspace_size(cm.handle, ctypes.byref(sh), ctypes.byref(nbytes)) != 0 \
-            or nbytes.value > SPLIT_WS_MAX:
-        return None
-    try:
-        with _alloc_on(stream):
-            return torch.empty((nbytes.value,), device=X.device, dtype=torch.uint8)
-    except torch.cuda.OutOfMemoryError:
-        return None
+    if lib.cis_split_workspace_size(cm.handle, ctypes.byref(sh), ctypes.byref(nbytes)) != 0:
+        return 0
+    return nbytes.value if nbytes.value <= SPLIT_WS_MAX else 0
 
 
 def discretize(cm: CisModel, X, U, s, params, K, *, with_xprop=True, layout="rule",
                stream=None):
     """A, Bm, Bp, S, defect (and F~) of every interval.  layout: one of LAYOUTS
-    ("rule": chosen from N and the device's CU count; past the counts that one
+    ("rule": chosen from N, K and the device's CU count; past the counts that one
     launch serves best, the two-launch form, while its workspace stays within
-    SPLIT_WS_MAX and can be had)."""
+    SPLIT_WS_MAX and can be had beside the outputs)."""
     _check_inputs(cm, X, U, s, params)
     N, nx, m = s.shape[0], cm.nx, cm.m
     kw = dict(device=X.device, dtype=X.dtype)
-    if layout == "rule":
-        ws = _split_workspace(cm, X, s, K, stream)
-        if ws is not None:
-            return discretize_split(cm, X, U, s, params, K, with_xprop=with_xprop, ws=ws,
-                                    stream=stream)
+    sh = _shape(X, s, K, layout=layout)
+    nbytes = _split_bytes(cm, sh) if layout == "rule" else 0
+    ws = None
     with _alloc_on(stream):
         out = dict(A=torch.empty((nx, nx, N), **kw), Bm=torch.empty((nx, m, N), **kw),
                    Bp=torch.empty((nx, m, N), **kw), S=torch.empty((nx, N), **kw),
                    d=torch.empty((nx, N), **kw))
         out["xprop"] = torch.empty((nx, N), **kw) if with_xprop else None
-    sh = _shape(X, s, K, layout=layout)
+        if nbytes:
+            try:
+                ws = torch.empty((nbytes,), device=X.device, dtype=torch.uint8)
+            except torch.cuda.OutOfMemoryError:
+                pass
     lib = _lib.load()
-    _lib.check(lib.cis_discretize(cm.handle, ctypes.byref(sh), _ptr(X), _ptr(U), _ptr(s),
-                                  _ptr(params), _ptr(out["A"]), _ptr(out["Bm"] if m else None),
-                                  _ptr(out["Bp"] if m else None), _ptr(out["S"]), _ptr(out["d"]),
-                                  _ptr(out["xprop"]), _stream(stream)))
+    outs = (_ptr(out["A"]), _ptr(out["Bm"] if m else None), _ptr(out["Bp"] if m else None),
+            _ptr(out["S"]), _ptr(out["d"]), _ptr(out["xprop"]))
+    if ws is None:
+        _lib.check(lib.cis_discretize(cm.handle, ctypes.byref(sh), _ptr(X), _ptr(U), _ptr(s),
+                                      _ptr(params), *outs, _stream(stream)))
+    else:
+        _lib.check(lib.cis_discretize_split(cm.handle, ctypes.byref(sh), _ptr(X), _ptr(U), _ptr(s),
+                                            _ptr(params), 1, *outs, _ptr(ws), nbytes,
+                                            _stream(stream)))
     return out
 
 
@@ -263,8 +271,8 @@ def split_workspace_bytes(cm: CisModel, N, K, dtype=torch.float64):
 def discretize_split(cm: CisModel, X, U, s, params, K, *, waves=1, with_xprop=True, ws=None,
                      stream=None):
     """Same outputs as :func:`discretize`, computed by the two-launch split
-    form (stage coefficient records, then one wave per leg over 64 tangent
-    columns).  ws: optional preallocated uint8 workspace."""
+    form (stage coefficient records, then the coupled tangent columns, one per
+    lane).  ws: optional preallocated uint8 workspace."""
     _check_inputs(cm, X, U, s, params)
     N, nx, m = s.shape[0], cm.nx, cm.m
     kw = dict(device=X.device, dtype=X.dtype)
