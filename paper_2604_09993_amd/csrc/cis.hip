@@ -824,11 +824,23 @@ static cis_status launch_discretize(const cis_model* m, const cis_shape* sh, con
 //   biped5 FP32    256: 64 and 111 / 25 and 37         320: 196 and 111 / 60 and 37
 // and a round of workgroups later where FP32 columns fill one wave (hopper at 320:
 // 69 and 66 / 24 and 28).
+// One or two substeps end before a second launch pays, some 28 us of a call in a row of
+// them, until the work is a few rounds of the CUs (calls in a row, us, K = 1 / 2):
+//   hopper FP64    N = 257: 23 and 28 / 25 and 28      513: 24 and 28 / 37 and 28
+//   biped5 FP64    193: 22 and 28 / 24 and 28          257: 29 and 28 / 43 and 28
+//   cheetah7 FP64  193: 22 and 28 / 25 and 28          385: 40 and 28 / 53 and 28
+//   quad13 FP64    64: 25 and 30 / 33 and 32           127: 34 and 31 / 43 and 34
+//   biped5 FP32    385: 24 and 28 / 33 and 28          513: 33 and 29 / 46 and 28
+//   quad13 FP32    193: 35 and 37 / 43 and 39          257: 49 and 37 / 61 and 39
+//   hopper FP32    2,049: 22 and 28 / 28 and 28        4,097: 32 and 28 / 47 and 28
 template <class T, int L, int D>
-static bool prefers_split(int N) {
+static bool prefers_split(int N, int K) {
     using TN = NarrowTopo<T, L, D>;
-    const int64_t cus = device_cus();
-    return (int64_t)N * TN::NGRP > (sizeof(T) == 4 && TN::NTW_ALL == 1 ? 2 * cus : cus);
+    const int64_t cus = device_cus(), units = (int64_t)N * TN::NGRP;
+    constexpr bool one_wave = sizeof(T) == 4 && TN::NTW_ALL == 1;
+    if (units <= (one_wave ? 2 * cus : cus)) return false;
+    constexpr double rounds = one_wave ? 16.0 : (sizeof(T) == 4 ? 2.0 : 3.2);
+    return K > 2 || double(units) * K > rounds * double(cus);
 }
 
 template <class T, int L, int D>
@@ -1045,8 +1057,9 @@ extern "C" cis_status cis_discretize_prefers_split(const cis_model* model, const
     if (shape->layout != 0 || !split_form_supported(model)) return CIS_OK;
 #define CIS_PREFERS(LL, DD)                                                           \
     if (model->L == LL && model->D == DD)                                             \
-        *split = (shape->dtype == CIS_F64 ? prefers_split<double, LL, DD>(shape->N)    \
-                                          : prefers_split<float, LL, DD>(shape->N)) ? 1 : 0;
+        *split = shape->dtype == CIS_F64                                              \
+                     ? prefers_split<double, LL, DD>(shape->N, shape->substeps)       \
+                     : prefers_split<float, LL, DD>(shape->N, shape->substeps);
     CIS_TOPOLOGIES(CIS_PREFERS)
 #undef CIS_PREFERS
     return CIS_OK;
