@@ -307,21 +307,37 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1)))
     coefrec_block<T, TP, false>(l, mc);
 }
 
-// Registers: six values per pair and lane, so FP64 holds two waves per SIMD up to
-// 13 pairs (256 registers, none spilled) and one beyond; FP32 three and two.
-// quad13, 12,800 intervals, K = 20: 1,010 us (VALU busy 69 %; 5,600 us with one
-// wave per leg and every row and column of Z), FP32 700 us (3,000 us).
 template <class T, class TP, bool FLAT>
-__global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu((RedTopo<TP, FLAT>::NP > 14 ? 1 : 2) +
-                                       (sizeof(T) == 4 ? 1 : 0))))
-    k_tangent(ItemList<T> l, const T* __restrict__ recs, const T* __restrict__ sums) {
+__device__ __forceinline__ void tangent_block(const ItemList<T>& l, const T* __restrict__ recs,
+                                              const T* __restrict__ sums) {
     __shared__ T lds[RedTopo<TP, FLAT>::LDS];
     red_tangent_block<T, TP, FLAT>(
         l, recs, sums, lds,
         [](const T* rec, T* g, const RedCol& col, int K, auto& pb, auto& vb, auto& ycc, T& yct) {
             tangent_item<T, TP, FLAT>(rec, g, col, K, pb, vb, ycc, yct);
         });
+}
+
+// Registers: six values per pair and lane, so FP64 holds two waves per SIMD up to
+// 13 pairs (256 registers, none spilled) and one beyond.  FP32 takes three and two,
+// though three cost 336 bytes of scratch per lane for quad13 and 172 for cheetah7, beside
+// the stage loop (both launches of 12,800 intervals, K = 20: 960 us and 404 us; at two
+// waves and none 1,050 and 463).  quad13, 12,800 intervals, K = 20: 1,010 us (VALU busy 69 %; 5,600 us
+// with one wave per leg and every row and column of Z), FP32 700 us (3,000 us).
+template <class T, class TP, bool FLAT>
+__global__ void __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu((RedTopo<TP, FLAT>::NP > 14 ? 1 : 2) +
+                                       (sizeof(T) == 4 ? 1 : 0))))
+    k_tangent(ItemList<T> l, const T* __restrict__ recs, const T* __restrict__ sums) {
+    tangent_block<T, TP, FLAT>(l, recs, sums);
+}
+
+// FP32 at the budget of FP64.
+template <class TP, bool FLAT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+    k_tangent_few(ItemList<float> l, const float* __restrict__ recs,
+                  const float* __restrict__ sums) {
+    tangent_block<float, TP, FLAT>(l, recs, sums);
 }
 
 // ---------------------------------------------------------------------------
@@ -379,6 +395,12 @@ static void split_launches(const cis_model* m, const ItemList<T>& l, KLaunch* ka
     kb->arg((const T*)l.rec);
     kb->arg((const T*)l.sums);
     kb->func = (const void*)&k_tangent<T, TP, FLAT>;
+    // FP32 with 13 pairs: while a third wave per SIMD has nothing to hide, its scratch
+    // only costs (both launches for quad13, K = 1 / 20: 100 intervals 35 and 96 us at
+    // three waves, 29 and 95 at two, 600 46 and 119, 34 and 119, 1,200 51 and 146,
+    // 43 and 158; with 7 pairs the two are equal up to 1,200).
+    if constexpr (sizeof(T) == 4 && RedTopo<TP, FLAT>::NP > 12 && RedTopo<TP, FLAT>::NP <= 14)
+        if (2 * (int64_t)l.n <= 5 * device_cus()) kb->func = (const void*)&k_tangent_few<TP, FLAT>;
     kb->grid = dim3(RedGrid<TP, FLAT>::blocks(l.n));
     kb->block = dim3(64 * RedTopo<TP, FLAT>::IPW);
 }
