@@ -88,6 +88,22 @@ def kernel_stats(folder):
             for k, v in rows.items()}
 
 
+def largest_dispatches(folder):
+    """Per kernel name, the mean time of its dispatches of the largest grid (a batch's
+    launch and a short trajectory's share a name) and the time of all of them."""
+    rows = defaultdict(list)
+    for db in _dbs(folder):
+        c = sqlite3.connect(db).cursor()
+        for name, grid, ns in c.execute(
+                "select name, grid_x * grid_y * grid_z, duration from kernels"):
+            rows[_short(name)].append((grid, ns * 1e-3))
+    out = {}
+    for k, v in rows.items():
+        big = [us for g, us in v if g == max(v)[0]]
+        out[k] = dict(avg_us=sum(big) / len(big), total_us=sum(us for _, us in v))
+    return out
+
+
 def counter_means(folder, counter):
     """Mean per kernel name over its largest dispatches (at least half the most: a
     batch's launch and a short trajectory's share a name)."""
@@ -250,15 +266,21 @@ def valu_summary(a):
     per = defaultdict(lambda: defaultdict(list))   # kernel -> counter -> per-dispatch values
     for path in a.csv:
         vals = defaultdict(lambda: defaultdict(float))
+        grid = {}
         with open(path) as fh:
             for r in csv.DictReader(fh):
-                vals[(_short(r["Kernel_Name"]), r["Dispatch_Id"])][r["Counter_Name"]] += \
-                    float(r["Counter_Value"])
-        for (k, _), cs in vals.items():
-            for c, v in cs.items():
-                per[k][c].append(v)
+                d = (_short(r["Kernel_Name"]), r["Dispatch_Id"])
+                vals[d][r["Counter_Name"]] += float(r["Counter_Value"])
+                grid[d] = int(r["Grid_Size"])
+        most = defaultdict(int)
+        for (k, _), g in grid.items():
+            most[k] = max(most[k], g)
+        for d, cs in vals.items():   # the dispatches of the largest grid, as for the times
+            if grid[d] == most[d[0]]:
+                for c, v in cs.items():
+                    per[d[0]][c].append(v)
     mean = {k: {c: sum(v) / len(v) for c, v in cs.items()} for k, cs in per.items()}
-    stats = kernel_stats(a.trace) if a.trace else {}
+    stats = largest_dispatches(a.trace) if a.trace else {}
     algo = bench_algorithmic_flops()
     clock = 2.4e9
     simds = 1024
@@ -266,6 +288,7 @@ def valu_summary(a):
              "", "Counter passes (one rocprofv3 run each, --pmc only):", ""]
     lines += [f"    {c}" for c in a.commands]
     lines += ["", f"Kernel durations: `{a.cmd_trace}`", "",
+              "Times and counters are means over a kernel's dispatches of the largest grid. "
               "Per dispatch: F64 FLOP = 64 (2 FMA + ADD + MUL) over the F64 VALU instruction counters "
               "(64 lanes per wave instruction, inactive lanes included), likewise F32; "
               "`VALU issue` = SQ_INSTS_VALU x 4 cycles (a 64-lane instruction at 16 lanes per "
