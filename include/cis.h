@@ -220,8 +220,8 @@ cis_status cis_discretize_adjoint_noalloc(const cis_model *model, const cis_shap
                                           int32_t ckpt_every, const void *seed, void *gX,
                                           void *gU, void *gs, void *gparams, void *stream);
 
-/* Which form of the discretize step is the faster one for this shape on the
- * current device, by measured rule: *split = 1 for cis_discretize_split, 0 for
+/* Which form of the discretize step is the faster one for this shape (N, substeps,
+ * dtype) on the current device, by measured rule: *split = 1 for cis_discretize_split, 0 for
  * cis_discretize (also where the first is not offered, or shape->layout names a
  * layout of the second). */
 cis_status cis_discretize_prefers_split(const cis_model *model, const cis_shape *shape,
@@ -506,11 +506,12 @@ cis_status cis_batch_graph_run(cis_batch_plan *plan, int32_t op, void *stream);
 /* Description of a plan: number of model groups, and for group g (if
  * 0 <= g < groups) its trajectories, work items (intervals), units per item,
  * the persistent grid size chosen for it (0 = one workgroup per unit), the
- * waves per interval of its reverse sweep (0 without CIS_BATCH_ADJOINT), the
- * register budget of its discretize kernel in waves per SIMD (1 or 2; 0
- * without CIS_BATCH_DISCRETIZE) and the waves per interval of its defects
- * pass (2: body lanes, 1: element lanes; 0 without CIS_BATCH_ADJOINT).  Any
- * output pointer may be NULL. */
+ * waves per workgroup of its reverse sweep (0 without CIS_BATCH_ADJOINT; the packed
+ * form has 3, or 4 with checkpoints more than a substep apart, for four intervals, the
+ * others 1 to 4 for one), the register budget of its discretize kernel in waves per
+ * SIMD (1 or 2; 0 without CIS_BATCH_DISCRETIZE) and the waves per workgroup of its
+ * defects pass (2: body lanes, for four intervals in models with legs with links; 1:
+ * element lanes; 0 without CIS_BATCH_ADJOINT).  Any output pointer may be NULL. */
 cis_status cis_batch_plan_info(const cis_batch_plan *plan, int32_t g, int32_t *groups,
                                int32_t *n_traj, int32_t *n_items, int32_t *units_per_item,
                                int32_t *persist_blocks, int32_t *adjoint_waves,

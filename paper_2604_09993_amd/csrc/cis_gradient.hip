@@ -16,10 +16,11 @@
 // scatter through LDS.
 //
 // Bound by the serial chain of one step (E and R some 250 FP64 instructions each)
-// with 6 waves per CU: the hand-over buffers take 71 KB of LDS.  12,800 flat quad13
-// intervals, K = 20: sweep 7.81 -> 0.57 ms, defects 0.93 -> 0.25 ms against one
-// interval per workgroup on element lanes; 50 cheetah7 intervals, checkpoints 5
-// apart: 130 -> 82 us and 54 -> 47 us.
+// with 6 waves per CU: at 206 to 224 registers eight waves fit a CU, and so two
+// workgroups of three, which is also what their 71 to 78 KB of LDS leave room for.
+// 12,800 flat quad13 intervals, K = 20: sweep 7.81 -> 0.57 ms, defects 0.93 -> 0.25 ms
+// against one interval per workgroup on element lanes; 50 cheetah7 intervals,
+// checkpoints 5 apart: 130 -> 82 us and 54 -> 47 us.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
