@@ -31,5 +31,12 @@ def test_largest_grid_alone(tmp_path):
     cell = [x.strip() for x in row.split("|")]
     assert cell[2] == "1100.0" and float(cell[3]) == 64 * 2 * 65e6
     # the headline's algorithmic FLOPs over the headline's time
-    algo = profiling.bench_algorithmic_flops()["k_tangent<double, Topo<4, 3"]
-    assert abs(float(cell[7]) - algo / 1.1e-3 / 1e12) <= 0.005
+    algo = profiling.bench_algorithmic_flops()
+    assert abs(float(cell[7]) - algo["k_tangent<double, Topo<4, 3"] / 1.1e-3 / 1e12) <= 0.005
+
+
+def test_only_batches_that_run():
+    """FP32 is timed on the quad13 batch alone: no work of the mixed batch by its name."""
+    for table in (profiling.bench_algorithmic_flops(), profiling.bench_algorithmic_bytes()):
+        assert [k for k in table if k.startswith("k_tangent<float")] == \
+            ["k_tangent<float, Topo<4, 3"]
